@@ -10,7 +10,7 @@ in HBM (setup excluded, reported separately).  A step is one such solve.
 value        = bytes one solve must move in the storage layouts the kernels use
                (summed from the per-kernel models below over the launches of one
                solve) / the solve's wall time, GB/s;
-roofline     = the fine-level fused recurrence step (k_fused<double,0,true,true,1,true>):
+roofline     = the fine-level fused recurrence step (k_fused<double,0,true,true,1,2>):
                the bytes it must move per launch / its average duration, timed
                here with events on the launch stream (degree-5 minus degree-4
                and degree-7 minus degree-6 smoother applications from x = 0,
@@ -57,11 +57,19 @@ WIDE_MIN_STEPS = 24  # streaming offset-aligned levels with this many stored ste
 # ---------------------------------------------------------------------------
 # Byte models: the bytes each kernel must move in the layout it reads (values of w bytes,
 # int32 indices, gathered vectors counted once).  M is the matrix's bytes in its layout:
-# offset-aligned slices w per stored entry plus a 4-byte offset per 64, packed slices w + 4.
+# offset-aligned slices w per stored entry plus a 4-byte offset per 64, packed slices w + 4; with
+# uniform slices an 8-byte descriptor per slice, w + 12 per pattern step, and only the dense
+# slices' entries.
 # ---------------------------------------------------------------------------
+def slice_bytes(n, w, values, patterned, steps):
+    tot = values * w + 4 * (values // 64)
+    return tot + 8 * ((n + 63) // 64) + (w + 12) * steps if patterned else tot
+
+
 def matrix_bytes(amg, h, level, w):
     padded, _, aligned = amg.amg_level_layout(h, level)
-    return padded * w + 4 * (padded // 64) if aligned else padded * (w + 4)
+    n, _ = amg.amg_level_info(h, level)
+    return slice_bytes(n, w, *amg.amg_level_patterns(h, level)) if aligned else padded * (w + 4)
 
 
 def level_table(amg, h, w):
@@ -73,9 +81,10 @@ def level_table(amg, h, w):
         n, _ = amg.amg_level_info(h, l)
         R = 0
         if l < L - 1:
-            form, stored = amg.amg_level_transfer(h, l)
+            form, _ = amg.amg_level_transfer(h, l)
             if form == amg.AMG_TRANSFER_PRODUCT:
-                R = stored * w + 4 * (stored // 64)
+                nc, _ = amg.amg_level_info(h, l + 1)
+                R = slice_bytes(nc, w, *amg.amg_level_patterns(h, l, True))
         out.append((n, matrix_bytes(amg, h, l, w), amg.amg_level_layout(h, l)[1], R))
     return out
 
@@ -564,6 +573,8 @@ def main():
     streams = ((n0 + 255) // 256 + 7) // 8 * 8 > STREAM_MIN_BLOCKS
     # wide slices (at least 24 stored steps per row on average) take the wide-batch variant
     wide = streams and aligned and lanes == 1 and padded >= WIDE_MIN_STEPS * n0
+    values, patterned, steps = amg.amg_level_patterns(h, 0)
+    variant = 2 if patterned else int(wide)  # slices: narrow, wide, uniform
     u_path = wide and args.kind != 0 and args.degree >= 2
     value = solve_bytes(lv64, M0, 8, args.kind, args.degree, it, False, u_path) / (ms * 1e-3) / 1e9
 
@@ -578,11 +589,13 @@ def main():
     ceil = ceiling(amg, stream)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM, "unit": "GB/s",
                 "frac": round(achieved / PEAK_HBM, 4), "traffic": None,
-                "kernel": f"k_fused<double,0,true,{str(streams).lower()},1,{str(wide).lower()}> (fine level, "
+                "kernel": f"k_fused<double,0,true,{str(streams).lower()},1,{variant}> (fine level, "
                           f"{args.workload} {args.size}^3)",
                 "bytes_per_launch": int(step_bytes), "avg_launch_us": round(t_step * 1e3, 2),
-                "layout": {"stored_entries": int(padded), "lanes_per_row": lanes, "offset_aligned": aligned,
-                           "bytes_per_launch": "8 per stored entry + 4 per 64 + 56 per row"},
+                "layout": {"entries": int(padded), "stored_entries": int(values), "uniform_slices": int(patterned),
+                           "pattern_steps": int(steps), "lanes_per_row": lanes, "offset_aligned": aligned,
+                           "bytes_per_launch": "8 per stored entry + 4 per 64, 8 per slice and 20 per pattern step "
+                                               "where slices are uniform, + 56 per row"},
                 "csr_model": {"bytes_per_launch": int(csr_bytes), "formula": "12 nnz + 60 n",
                               "GBps": round(csr_bytes / (t_step * 1e-3) / 1e9, 1),
                               "note": "counts column indices and row pointers the offset-aligned layout "

@@ -150,10 +150,19 @@ int amg_num_levels(const amg_handle* h, int* h_nlevels);
 int amg_level_info(const amg_handle* h, int level, int64_t* h_n, int64_t* h_nnz);
 
 /* Storage of level l's operator in the kernels' sliced-ELL format (host outputs, any may be
- * NULL): *h_padded stored entries including padding, *h_lanes lanes per row (1, 4, 16 or
+ * NULL): *h_padded entries of its slices including padding, *h_lanes lanes per row (1, 4, 16 or
  * 64), *h_aligned 1 when its slices are offset-aligned (columns formed as row + a per-slice
  * offset, no column indices read), else 0. */
 int amg_level_layout(const amg_handle* h, int level, int64_t* h_padded, int* h_lanes, int* h_aligned);
+
+/* Uniform slices of level l's operator (restriction = 0) or of its restriction product (1, where
+ * amg_level_transfer reports AMG_TRANSFER_PRODUCT; AMG_EINVAL otherwise): a 64-row slice whose
+ * rows hold, at every step, one common value or +0 is kept as a pattern (offset, value and lane
+ * mask per step) that equal slices share, when at least half of the matrix's slices are of this
+ * kind.  Host outputs, any may be NULL: *h_values entries stored one by one (including padding),
+ * *h_slices slices kept as patterns, *h_steps steps the patterns hold in all. */
+int amg_level_patterns(const amg_handle* h, int level, int restriction, int64_t* h_values, int64_t* h_slices,
+                       int64_t* h_steps);
 
 /* How the restriction from level l to level l + 1 is computed (host outputs, any may be NULL;
  * AMG_EINVAL on the coarsest level): *h_form = AMG_TRANSFER_RESIDUAL (2x2x2 boxes: the fine

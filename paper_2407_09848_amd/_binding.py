@@ -17,7 +17,7 @@ AMG_TRANSFER_RESIDUAL, AMG_TRANSFER_PRODUCT, AMG_TRANSFER_EXPLICIT = 0, 1, 2
 
 __all__ = [
     "LIB_PATH", "AmgError", "lib", "amg_setup", "amg_destroy", "amg_num_levels", "amg_level_info", "amg_level_layout",
-    "amg_level_transfer", "AMG_TRANSFER_RESIDUAL", "AMG_TRANSFER_PRODUCT", "AMG_TRANSFER_EXPLICIT",
+    "amg_level_transfer", "amg_level_patterns", "AMG_TRANSFER_RESIDUAL", "AMG_TRANSFER_PRODUCT", "AMG_TRANSFER_EXPLICIT",
     "amg_level_export", "amg_level_aggregates", "amg_default_beta", "amg_default_astar", "amg_set_beta",
     "amg_reset_beta",
     "amg_spmv", "smoother_apply", "smoother_apply_f32", "amg_restrict_residual", "amg_prolong_add", "amg_coarse_solve",
@@ -61,6 +61,7 @@ _SIGS = {
     "amg_level_export": (_I, [_P, _I, _P, _P, _P, _P, _P]),
     "amg_level_aggregates": (_I, [_P, _I, _P, _P]),
     "amg_level_layout": (_I, [_P, _I, ctypes.POINTER(_I64), ctypes.POINTER(_I), ctypes.POINTER(_I)]),
+    "amg_level_patterns": (_I, [_P, _I, _I, ctypes.POINTER(_I64), ctypes.POINTER(_I64), ctypes.POINTER(_I64)]),
     "amg_level_transfer": (_I, [_P, _I, ctypes.POINTER(_I), ctypes.POINTER(_I64)]),
     "amg_default_beta": (_I, [_I, ctypes.POINTER(_D)]),
     "amg_default_astar": (_I, [_I, ctypes.POINTER(_D)]),
@@ -186,6 +187,15 @@ def amg_level_transfer(h, level):
     form, stored = _I(), _I64()
     _check(lib().amg_level_transfer(h, level, ctypes.byref(form), ctypes.byref(stored)), "amg_level_transfer")
     return form.value, stored.value
+
+
+def amg_level_patterns(h, level, restriction=False):
+    """(entries stored one by one, slices kept as patterns, steps of all patterns) of level l's operator
+    or of its restriction product."""
+    values, slices, steps = _I64(), _I64(), _I64()
+    _check(lib().amg_level_patterns(h, level, int(bool(restriction)), ctypes.byref(values), ctypes.byref(slices),
+                                    ctypes.byref(steps)), "amg_level_patterns")
+    return values.value, slices.value, steps.value
 
 
 def amg_level_export(h, level):

@@ -40,6 +40,21 @@ constexpr int kQuadMinSteps = 16;
 // 8-byte (FP32) load per lane serves two steps.  The FP32 copy of a slice of 16
 // or more steps keeps them in quads instead (steps 4q .. 4q + 3 of lane l at
 // 256 q + 4 l, then a pair, then a single step), one 16-byte load per four steps.
+//
+// Uniform slices (constant-coefficient stencils): when at every step the rows of an offset-aligned
+// slice hold one common value or exactly +0, the slice is kept as a pattern, per step the offset,
+// the value and the mask of the lanes that hold it, and slices with equal patterns share one
+// copy.  A matrix of which at least half the slices are uniform has one descriptor per slice
+// (`desc`) in place of `sptr`: {beg, 16 * steps + kind}, beg in units of 64 stored values (dense
+// slices) or the first step of the pattern.  The values, their order and the zeros of the padding
+// are those of the dense form, so results are the same bits; a 27-point FP64 row needs no matrix
+// bytes of its own instead of 216.
+enum SliceKind {
+  SLICE_DENSE = 0,
+  SLICE_MASKED = 1,
+  SLICE_FULL = 2,    // every lane holds every step
+  SLICE_TRIPLES = 4  // (with one of the two) the steps are triples of consecutive offsets, the rows consecutive
+};
 template <typename T>
 struct Ell {
   int64_t n = 0;
@@ -55,6 +70,14 @@ struct Ell {
   // instead of the row itself: column = anchor[r * astride] + offset (null: the row)
   const int32_t* anchor = nullptr;
   int astride = 1;
+  // uniform slices (null: none)
+  int2* desc = nullptr;          // [nslices] {beg, 16 * steps + kind}
+  int32_t* poff = nullptr;       // [npat] offsets, values and lane masks of the patterns' steps
+  T* pval = nullptr;
+  unsigned long long* pmask = nullptr;
+  int64_t npat = 0;
+  int64_t dense = 0;             // stored values (dense slices); padded counts all slices' steps
+  int64_t patterned = 0;         // slices kept as patterns
 };
 
 // Per-problem smoother weights for stacked problems: the weight of row i is
@@ -81,11 +104,16 @@ struct EllView {
   const T* __restrict__ val;
   const int32_t* __restrict__ doff;
   int32_t last;  // columns - 1, the clamp of offset-aligned columns
+  const int2* __restrict__ desc;
+  const int32_t* __restrict__ poff;
+  const T* __restrict__ pval;
+  const unsigned long long* __restrict__ pmask;
 };
 
 template <typename T>
 inline EllView<T> view(const Ell<T>& e) {
-  return EllView<T>{e.sptr, e.col, e.val, e.doff, (int32_t)((e.ncols > 0 ? e.ncols : e.n) - 1)};
+  return EllView<T>{e.sptr, e.col, e.val, e.doff, (int32_t)((e.ncols > 0 ? e.ncols : e.n) - 1),
+                    e.desc, e.poff, e.pval, e.pmask};
 }
 
 // Work vectors of one level in one precision.

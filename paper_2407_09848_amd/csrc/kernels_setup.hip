@@ -5,6 +5,7 @@
 
 #include <climits>
 
+#include "graph.h"
 #include "internal.h"
 
 namespace amgp {
@@ -101,84 +102,253 @@ __global__ void k_ell_fill(int64_t n, int64_t ncols, int64_t nslices, int G, con
   }
 }
 
-// Distinct column offsets (col - row, or col - anchor[row * astride]) of every 64-row slice,
-// sorted: offs[s * 64 + t], count width[s] (-1 when there are more than 64).  One wavefront per
-// slice, an LDS hash set.
+// Layout of every 64-row slice, one wavefront per slice, its lanes on consecutive entries of the
+// slice's rows (contiguous in CSR, so the loads coalesce; one row per lane instead read 20 KB a
+// wavefront through its own cache lines, 33 ms against 5 ms for the kinds of the 27-point 320^3
+// matrix).  The slice's distinct column offsets (col - row, or col - anchor[row * astride]) go into
+// an LDS hash set.
+//
+// TABLES = false: the offsets, sorted, offs[s * 64 + t], their count width[s] (-1 when there are more
+// than 64), the longest row lwidth[s], and with kind given the kind of the slice (see Ell): per step
+// the lanes must agree on one value up to +0; FULL when every lane holds an entry at every step
+// and all of one value (zero included); a differing value ends the search (the first entries of
+// a matrix of varying coefficients).
+// TABLES = true (uniform slices alone): per step the value and the lane mask (all ones for a full
+// step), stride records per slice in vtab / mtab, and the hash of offsets, values and masks.
 constexpr int kOffHash = 256;
 constexpr int kOffEmpty = INT_MIN;
 
-__global__ __launch_bounds__(kWave) void k_slice_offsets(int64_t n, const int32_t* __restrict__ ptr,
-                                                         const int32_t* __restrict__ col, const int32_t* anchor,
-                                                         int astride, int32_t* __restrict__ offs,
-                                                         int32_t* __restrict__ width) {
+__device__ __forceinline__ unsigned off_slot(int o) { return ((unsigned)o * 2654435761u) & (kOffHash - 1); }
+
+template <bool TABLES>
+__global__ __launch_bounds__(kWave) void k_slice_layout(
+    int64_t n, const int32_t* __restrict__ ptr, const int32_t* __restrict__ col, const double* __restrict__ val,
+    const int32_t* anchor, int astride, int32_t* __restrict__ offs, int32_t* __restrict__ width,
+    int32_t* __restrict__ lwidth, int32_t* __restrict__ kind, int stride, unsigned long long* __restrict__ vtab,
+    unsigned long long* __restrict__ mtab, unsigned long long* __restrict__ hash) {
   __shared__ int set[kOffHash];
-  __shared__ int list[kOffHash];
-  __shared__ int cnt;
+  __shared__ int at[kOffHash];  // step of a set entry
+  __shared__ int list[kWave];
+  __shared__ int rp[kWave + 1];
+  __shared__ int base[kWave];
+  __shared__ unsigned long long sval[kWave], spres[kWave], snz[kWave];
+  __shared__ int cnt, differ;
   const int64_t s = blockIdx.x;
   const int lane = threadIdx.x;
-  for (int t = lane; t < kOffHash; t += kWave) set[t] = kOffEmpty;
-  if (lane == 0) cnt = 0;
-  __syncthreads();
+  if (TABLES && kind[s] == SLICE_DENSE) return;
   const int64_t r = s * kSlice + lane;
-  if (r < n) {
-    const int base = anchor ? anchor[r * astride] : (int)r;
-    for (int p = ptr[r]; p < ptr[r + 1]; ++p) {
-      const int o = col[p] - base;
-      unsigned h = ((unsigned)o * 2654435761u) & (kOffHash - 1);
-      for (int probe = 0; probe < kOffHash; ++probe) {
-        const int old = atomicCAS(&set[h], kOffEmpty, o);
+  const int64_t rc = r < n ? r : n;
+  rp[lane] = ptr[rc];
+  if (lane == kWave - 1) rp[kWave] = ptr[r + 1 < n ? r + 1 : n];
+  base[lane] = r < n ? (anchor ? anchor[r * astride] : (int)r) : 0;
+  for (int t = lane; t < kOffHash; t += kWave) set[t] = kOffEmpty;
+  if (lane == 0) {
+    cnt = 0;
+    differ = 0;
+  }
+  sval[lane] = spres[lane] = snz[lane] = 0;
+  __syncthreads();
+  const int beg = rp[0], end = rp[kWave];
+  auto row_of = [&](int e) {  // the row (0..63) of entry e
+    int lo = 0;
+#pragma unroll
+    for (int step = kWave / 2; step > 0; step >>= 1)
+      if (rp[lo + step] <= e) lo += step;
+    return lo;
+  };
+  auto insert = [&](int o) {
+    unsigned h = off_slot(o);
+    for (int probe = 0; probe < kOffHash; ++probe) {
+      int old = set[h];
+      if (old == o) return;
+      if (old == kOffEmpty) {
+        old = atomicCAS(&set[h], kOffEmpty, o);
         if (old == kOffEmpty) {
           atomicAdd(&cnt, 1);
-          break;
+          return;
         }
-        if (old == o) break;
-        h = (h + 1) & (kOffHash - 1);
+        if (old == o) return;
       }
+      h = (h + 1) & (kOffHash - 1);
     }
-  }
-  __syncthreads();
-  const int c = cnt;
-  if (c > kSlice) {
-    if (lane == 0) width[s] = -1;
-    return;
-  }
-  // compact (slot order), then an odd-even transposition sort of at most 64 values by the wavefront
-  __shared__ int k;
-  if (lane == 0) k = 0;
-  __syncthreads();
-  for (int t = lane; t < kOffHash; t += kWave) {
-    const int v = set[t];
-    if (v != kOffEmpty) list[atomicAdd(&k, 1)] = v;
-  }
-  __syncthreads();
-  for (int phase = 0; phase < c; ++phase) {
-    const int i = 2 * lane + (phase & 1);
-    if (i + 1 < c && list[i] > list[i + 1]) {
-      const int a = list[i];
-      list[i] = list[i + 1];
-      list[i + 1] = a;
+  };
+  int c;
+  if constexpr (TABLES) {
+    c = width[s];
+    if (lane < c) {
+      list[lane] = offs[s * kSlice + lane];
+      insert(list[lane]);
     }
     __syncthreads();
+  } else {
+    int longest = rp[lane + 1] - rp[lane];
+    for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off, kWave));
+    if (lane == 0) lwidth[s] = longest;
+    for (int e = beg + lane; e < end; e += kWave) {
+      if (cnt > kWave) break;  // too many already
+      insert(col[e] - base[row_of(e)]);
+    }
+    __syncthreads();
+    c = cnt;
+    if (c > kSlice) {
+      if (lane == 0) width[s] = -1;
+      return;
+    }
+    // compact (slot order), then an odd-even transposition sort of at most 64 values by the wavefront
+    __shared__ int k;
+    if (lane == 0) k = 0;
+    __syncthreads();
+    for (int t = lane; t < kOffHash; t += kWave) {
+      const int v = set[t];
+      if (v != kOffEmpty) list[atomicAdd(&k, 1)] = v;
+    }
+    __syncthreads();
+    for (int phase = 0; phase < c; ++phase) {
+      const int i = 2 * lane + (phase & 1);
+      if (i + 1 < c && list[i] > list[i + 1]) {
+        const int a = list[i];
+        list[i] = list[i + 1];
+        list[i + 1] = a;
+      }
+      __syncthreads();
+    }
+    if (lane < c) offs[s * kSlice + lane] = list[lane];
+    if (lane == 0) width[s] = c;
+    if (!kind) return;
   }
-  if (lane < c) offs[s * kSlice + lane] = list[lane];
-  if (lane == 0) width[s] = c;
+  if (lane < c) {  // the step of every offset in the set
+    unsigned h = off_slot(list[lane]);
+    while (set[h] != list[lane]) h = (h + 1) & (kOffHash - 1);
+    at[h] = lane;
+  }
+  __syncthreads();
+  for (int e = beg + lane; e < end; e += kWave) {
+    if (!TABLES && differ) break;
+    const int row = row_of(e);
+    const int o = col[e] - base[row];
+    unsigned h = off_slot(o);
+    while (set[h] != o) h = (h + 1) & (kOffHash - 1);
+    const int t = at[h];
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(val[e]);
+    const unsigned long long bit = 1ull << row;
+    atomicOr(&spres[t], bit);
+    if (bits) {
+      atomicOr(&snz[t], bit);
+      unsigned long long old = sval[t];
+      if (old == 0) old = atomicCAS(&sval[t], 0ull, bits);
+      if (old != 0 && old != bits) differ = 1;
+    }
+  }
+  __syncthreads();
+  if (!TABLES && differ) {
+    if (lane == 0) kind[s] = SLICE_DENSE;
+    return;
+  }
+  const bool whole = spres[lane] == ~0ull && (snz[lane] == 0 || snz[lane] == ~0ull);
+  if constexpr (TABLES) {
+    unsigned long long h = 0;
+    if (lane < c) {
+      const unsigned long long v = sval[lane], m = whole ? ~0ull : snz[lane];
+      vtab[s * stride + lane] = v;
+      mtab[s * stride + lane] = m;
+      h = graph::splitmix64(graph::splitmix64(((unsigned long long)lane << 32) + (unsigned)list[lane]) ^ v);
+      h = graph::splitmix64(h ^ m);
+    }
+    for (int off = 32; off > 0; off >>= 1) h += __shfl_xor(h, off, kWave);
+    if (lane == 0) hash[s] = graph::splitmix64(h) | 1;  // 0 marks a free slot
+  } else {
+    const bool full = __ballot(lane < c && !whole) == 0;
+    // triples: a whole slice of consecutive rows whose sorted offsets come in threes
+    const bool third = lane < c && (lane % 3 == 0 || list[lane] == list[lane - 1] + 1);
+    const bool triples = !anchor && (s + 1) * kSlice <= n && c % 3 == 0 && __ballot(lane < c && !third) == 0;
+    if (lane == 0) kind[s] = (full ? SLICE_FULL : SLICE_MASKED) | (triples ? SLICE_TRIPLES : 0);
+  }
+}
+
+// Equal patterns share one copy: a table of cap (a power of two, at least twice the slices) slots
+// keyed by the hash keeps the smallest slice of each key, and a slice whose records equal those of
+// that slice takes them over (rep[s]); one that merely has its hash keeps its own.
+__global__ void k_pattern_insert(int64_t nslices, const int32_t* __restrict__ kind,
+                                 const unsigned long long* __restrict__ hash, unsigned cap,
+                                 unsigned long long* __restrict__ keys, int32_t* __restrict__ first) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= nslices || kind[s] == SLICE_DENSE) return;
+  unsigned q = (unsigned)hash[s] & (cap - 1);
+  // most slices share few patterns: the atomics only where a plain read has not shown the key, or a
+  // smaller slice, to be there (on one address they are served one by one)
+  for (;;) {
+    unsigned long long old = __hip_atomic_load(&keys[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (old == 0) old = atomicCAS(&keys[q], 0ull, hash[s]);
+    if (old == 0 || old == hash[s]) break;
+    q = (q + 1) & (cap - 1);
+  }
+  if (__hip_atomic_load(&first[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > (int32_t)s)
+    atomicMin(&first[q], (int32_t)s);
+}
+
+__global__ void k_pattern_resolve(int64_t nslices, const int32_t* __restrict__ kind,
+                                  const unsigned long long* __restrict__ hash, unsigned cap,
+                                  const unsigned long long* __restrict__ keys, const int32_t* __restrict__ first,
+                                  const int32_t* __restrict__ offs, const int32_t* __restrict__ width, int stride,
+                                  const unsigned long long* __restrict__ vtab,
+                                  const unsigned long long* __restrict__ mtab, int32_t* __restrict__ rep) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= nslices) return;
+  if (kind[s] == SLICE_DENSE) {
+    rep[s] = -1;
+    return;
+  }
+  unsigned q = (unsigned)hash[s] & (cap - 1);
+  while (keys[q] != hash[s]) q = (q + 1) & (cap - 1);
+  const int64_t f = first[q];
+  bool same = kind[f] == kind[s] && width[f] == width[s];
+  for (int t = 0; same && t < width[s]; ++t)
+    same = offs[f * kSlice + t] == offs[s * kSlice + t] && vtab[f * stride + t] == vtab[s * stride + t] &&
+           mtab[f * stride + t] == mtab[s * stride + t];
+  rep[s] = same ? (int32_t)f : (int32_t)s;
+}
+
+// The kept patterns' steps: one wavefront per slice, lane t writes step t.
+__global__ void k_pattern_write(int64_t nslices, const int32_t* __restrict__ rep, const int2* __restrict__ desc,
+                                const int32_t* __restrict__ offs, int stride,
+                                const unsigned long long* __restrict__ vtab,
+                                const unsigned long long* __restrict__ mtab, int32_t* __restrict__ poff,
+                                double* __restrict__ pval, unsigned long long* __restrict__ pmask) {
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t s = g / kSlice;
+  if (s >= nslices || rep[s] != s) return;
+  const int2 d = desc[s];
+  const int t = (int)(g % kSlice);
+  if (t >= d.y >> 4) return;
+  poff[d.x + t] = offs[s * kSlice + t];
+  pval[d.x + t] = __longlong_as_double((long long)vtab[s * stride + t]);
+  pmask[d.x + t] = mtab[s * stride + t];
 }
 
 // Offset-aligned fill: lane l of slice s (row r, anchor a = r or anchor[r * astride]) puts, at
 // step t, its entry of column a + offs[t] (0 when the row has none), with the steps of a lane in
 // pairs: step t at 64 (t - t % 2) + 2 l + t % 2 while t has a partner, an odd last step at 64 t + l.
+// With desc only the dense slices are stored.
 __global__ void k_ell_fill_aligned(int64_t n, int64_t nslices, const int32_t* __restrict__ ptr,
                                    const int32_t* __restrict__ col, const double* __restrict__ val,
                                    const int32_t* anchor, int astride, const int32_t* __restrict__ offs,
-                                   const int32_t* __restrict__ sptr, double* __restrict__ eval,
-                                   int32_t* __restrict__ doff) {
+                                   const int32_t* __restrict__ sptr, const int2* __restrict__ desc,
+                                   double* __restrict__ eval, int32_t* __restrict__ doff) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= nslices * kSlice) return;
   const int64_t s = t / kSlice;
   const int lane = (int)(t % kSlice);
   const int64_t r = s * kSlice + lane;
-  const int base = sptr[s];
-  const int steps = (sptr[s + 1] - base) / kSlice;
+  int base, steps;
+  if (desc) {
+    const int2 d = desc[s];
+    if ((d.y & 15) != SLICE_DENSE) return;
+    base = d.x * kSlice;
+    steps = d.y >> 4;
+  } else {
+    base = sptr[s];
+    steps = (sptr[s + 1] - base) / kSlice;
+  }
   int p = 0, pe = 0;
   int64_t a = r;
   if (r < n) {
@@ -207,14 +377,23 @@ __global__ void k_round_f32(int64_t m, const double* __restrict__ a, float* __re
 // FP32 copy of offset-aligned slices: slices of at least kQuadMinSteps steps put each lane's steps in
 // quads (step t of lane l at 64 (t - t % 4) + 4 l + t % 4 for t below w - w % 4, then a pair at
 // 64 (t - t % 2) + 2 l + t % 2, then a single step at 64 t + l), narrower ones keep the FP64 pairs.
-__global__ void k_round_f32_aligned(int64_t nslices, const int32_t* __restrict__ sptr, const double* __restrict__ a,
+__global__ void k_round_f32_aligned(int64_t nslices, const int32_t* __restrict__ sptr,
+                                    const int2* __restrict__ desc, const double* __restrict__ a,
                                     float* __restrict__ b) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t s = g >> 6;
   const int lane = (int)(g & 63);
   if (s >= nslices) return;
-  const int beg = sptr[s];
-  const int w = (sptr[s + 1] - beg) >> 6;
+  int beg, w;
+  if (desc) {
+    const int2 d = desc[s];
+    if ((d.y & 15) != SLICE_DENSE) return;
+    beg = d.x * kSlice;
+    w = d.y >> 4;
+  } else {
+    beg = sptr[s];
+    w = (sptr[s + 1] - beg) >> 6;
+  }
   const int w2 = w & ~1, w4 = w >= kQuadMinSteps ? (w & ~3) : 0;
   for (int t = 0; t < w; ++t) {
     const int pair = t < w2 ? 64 * (t & ~1) + 2 * lane + (t & 1) : 64 * t + lane;
@@ -358,53 +537,39 @@ int launch_l1_diag(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* 
   return hipGetLastError() == hipSuccess ? AMG_OK : AMG_EHIP;
 }
 
+// Uniform slices are kept as patterns when they are at least half of the matrix's (a matrix of
+// constant coefficients: all but the slices that cross an odd boundary); below that most slices
+// stay dense and the plain kernels, which have no pattern path, serve them faster.
+constexpr int64_t kUniformMaxRows = int64_t(1) << 28;  // 32-bit byte offsets of the full slices' gathers
+
 // Offset-aligned sliced ELL (one row per lane) when every slice has at most 64 distinct column
 // offsets and the layout is at most 10% larger than the packed one; AMG_EINVAL otherwise.
 int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
                       Ell<double>* out, const int32_t* anchor, int astride, int64_t ncols, bool any_size) {
+  using graph::DevBuf;
   const int64_t nslices = (n + kSlice - 1) / kSlice;
-  int32_t *offs = nullptr, *wd = nullptr, *lw = nullptr;
-  auto cleanup = [&]() {
-    hipFree(offs);
-    hipFree(wd);
-    hipFree(lw);
-  };
-  if (hipMalloc(&offs, sizeof(int32_t) * nslices * kSlice) != hipSuccess ||
-      hipMalloc(&wd, sizeof(int32_t) * nslices) != hipSuccess ||
-      hipMalloc(&lw, sizeof(int32_t) * nslices) != hipSuccess) {
-    cleanup();
-    return AMG_ENOMEM;
-  }
-  hipLaunchKernelGGL(k_slice_offsets, dim3((unsigned)nslices), dim3(kWave), 0, s, n, ptr, col, anchor, astride, offs,
-                     wd);
-  hipLaunchKernelGGL(k_slice_width, dim3(grid_for(nslices)), dim3(kBlock), 0, s, n, nslices, kSlice, ptr, lw);
-  std::vector<int32_t> w(nslices), lwh(nslices);
-  if (hipMemcpyAsync(w.data(), wd, sizeof(int32_t) * nslices, hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipMemcpyAsync(lwh.data(), lw, sizeof(int32_t) * nslices, hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess) {
-    cleanup();
-    return AMG_EHIP;
-  }
-  int64_t aligned = 0, packed = 0;
+  // per slice: the sorted offsets (64), their count, the packed width, the kind
+  DevBuf<int32_t> buf;
+  AMGP_TRY(buf.alloc(nslices * (kSlice + 3)));
+  int32_t *offs = buf.p, *wd = offs + nslices * kSlice, *lw = wd + nslices, *kind = lw + nslices;
+  const bool try_uniform = n < kUniformMaxRows && (ncols < 0 ? n : ncols) < kUniformMaxRows;
+  hipLaunchKernelGGL(k_slice_layout<false>, dim3((unsigned)nslices), dim3(kWave), 0, s, n, ptr, col, val, anchor,
+                     astride, offs, wd, lw, try_uniform ? kind : nullptr, 0, nullptr, nullptr, nullptr);
+  std::vector<int32_t> hb(3 * nslices);
+  const int32_t *w = hb.data(), *lwh = w + nslices, *kh = lwh + nslices;
+  AMGP_HIP(hipMemcpyAsync(hb.data(), wd, sizeof(int32_t) * 3 * nslices, hipMemcpyDeviceToHost, s));
+  AMGP_HIP(hipStreamSynchronize(s));
+  int64_t aligned = 0, packed = 0, uniform = 0;
+  int wmax = 1;
   for (int64_t i = 0; i < nslices; ++i) {
-    if (w[i] < 0) {
-      cleanup();
-      return AMG_EINVAL;
-    }
+    if (w[i] < 0) return AMG_EINVAL;
     aligned += (int64_t)w[i] * kSlice;
     packed += (int64_t)lwh[i] * kSlice;
+    wmax = std::max(wmax, w[i]);
+    uniform += try_uniform && kh[i] != SLICE_DENSE;
   }
-  if ((!any_size && aligned > packed + packed / 10) || aligned >= (int64_t)INT32_MAX) {
-    cleanup();
-    return AMG_EINVAL;
-  }
-  std::vector<int32_t> sp(nslices + 1);
-  int64_t acc = 0;
-  for (int64_t i = 0; i < nslices; ++i) {
-    sp[i] = (int32_t)acc;
-    acc += (int64_t)w[i] * kSlice;
-  }
-  sp[nslices] = (int32_t)acc;
+  if ((!any_size && aligned > packed + packed / 10) || aligned >= (int64_t)INT32_MAX) return AMG_EINVAL;
+  const bool compact = 2 * uniform >= nslices;
   Ell<double> e;
   e.n = n;
   e.ncols = ncols < 0 ? n : ncols;
@@ -412,24 +577,80 @@ int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_
   e.astride = astride;
   e.group = 1;
   e.nslices = nslices;
-  e.padded = acc;
-  if (hipMalloc(&e.sptr, sizeof(int32_t) * (nslices + 1)) != hipSuccess ||
-      hipMalloc(&e.val, sizeof(double) * std::max<int64_t>(acc, 1)) != hipSuccess ||
-      hipMalloc(&e.doff, sizeof(int32_t) * std::max<int64_t>(acc / kSlice, 1)) != hipSuccess) {
-    free_ell(e);
-    cleanup();
-    return AMG_ENOMEM;
-  }
-  int rc = AMG_OK;
-  if (hipMemcpyAsync(e.sptr, sp.data(), sizeof(int32_t) * (nslices + 1), hipMemcpyHostToDevice, s) != hipSuccess)
-    rc = AMG_EHIP;
-  if (rc == AMG_OK) {
-    hipLaunchKernelGGL(k_ell_fill_aligned, dim3(grid_for(nslices * kSlice)), dim3(kBlock), 0, s, n, nslices, ptr,
-                       col, val, anchor, astride, offs, e.sptr, e.val, e.doff);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) rc = AMG_EHIP;
-  }
-  cleanup();
+  e.padded = aligned;
+  const int rc = [&]() -> int {
+    if (compact) {
+      unsigned cap = 64;
+      while (cap < 2 * nslices) cap *= 2;
+      // per slice and step the value and the mask, per slice the hash; the table's keys, then its slices, and rep
+      DevBuf<unsigned long long> tab;
+      AMGP_TRY(tab.alloc(nslices * (2 * wmax + 1) + cap + (cap + nslices + 1) / 2));
+      unsigned long long *vtab = tab.p, *mtab = vtab + nslices * wmax, *hash = mtab + nslices * wmax,
+                         *keys = hash + nslices;
+      int32_t *first = reinterpret_cast<int32_t*>(keys + cap), *rep = first + cap;
+      hipLaunchKernelGGL(k_slice_layout<true>, dim3((unsigned)nslices), dim3(kWave), 0, s, n, ptr, col, val, anchor,
+                         astride, offs, wd, nullptr, kind, wmax, vtab, mtab, hash);
+      AMGP_HIP(hipMemsetAsync(keys, 0, sizeof(unsigned long long) * cap, s));
+      AMGP_HIP(hipMemsetAsync(first, 0x7f, sizeof(int32_t) * cap, s));
+      hipLaunchKernelGGL(k_pattern_insert, dim3(grid_for(nslices)), dim3(kBlock), 0, s, nslices, kind, hash, cap, keys,
+                         first);
+      hipLaunchKernelGGL(k_pattern_resolve, dim3(grid_for(nslices)), dim3(kBlock), 0, s, nslices, kind, hash, cap, keys,
+                         first, offs, wd, wmax, vtab, mtab, rep);
+      std::vector<int32_t> rh(nslices);
+      AMGP_HIP(hipMemcpyAsync(rh.data(), rep, sizeof(int32_t) * nslices, hipMemcpyDeviceToHost, s));
+      AMGP_HIP(hipStreamSynchronize(s));
+      std::vector<int2> desc(nslices);
+      int64_t steps = 0;
+      for (int64_t i = 0; i < nslices; ++i) {
+        int64_t beg;
+        if (kh[i] == SLICE_DENSE) {
+          beg = steps;
+          steps += w[i];
+        } else if (rh[i] == i) {  // a representative is the smallest slice of its pattern
+          beg = e.npat;
+          e.npat += w[i];
+        } else {
+          beg = desc[rh[i]].x;
+        }
+        desc[i] = int2{(int)beg, w[i] * 16 + kh[i]};
+      }
+      e.dense = steps * kSlice;
+      e.patterned = uniform;
+      if (hipMalloc(&e.desc, sizeof(int2) * nslices) != hipSuccess ||
+          hipMalloc(&e.poff, sizeof(int32_t) * e.npat) != hipSuccess ||
+          hipMalloc(&e.pval, sizeof(double) * e.npat) != hipSuccess ||
+          hipMalloc(&e.pmask, sizeof(unsigned long long) * e.npat) != hipSuccess)
+        return AMG_ENOMEM;
+      AMGP_HIP(hipMemcpyAsync(e.desc, desc.data(), sizeof(int2) * nslices, hipMemcpyHostToDevice, s));
+      hipLaunchKernelGGL(k_pattern_write, dim3(grid_for(nslices * kSlice)), dim3(kBlock), 0, s, nslices, rep, e.desc,
+                         offs, wmax, vtab, mtab, e.poff, e.pval, e.pmask);
+      AMGP_HIP(hipGetLastError());
+      AMGP_HIP(hipStreamSynchronize(s));  // desc and tab leave scope
+    } else {
+      e.dense = aligned;
+      std::vector<int32_t> sp(nslices + 1);
+      int64_t acc = 0;
+      for (int64_t i = 0; i < nslices; ++i) {
+        sp[i] = (int32_t)acc;
+        acc += (int64_t)w[i] * kSlice;
+      }
+      sp[nslices] = (int32_t)acc;
+      if (hipMalloc(&e.sptr, sizeof(int32_t) * (nslices + 1)) != hipSuccess) return AMG_ENOMEM;
+      AMGP_HIP(hipMemcpyAsync(e.sptr, sp.data(), sizeof(int32_t) * (nslices + 1), hipMemcpyHostToDevice, s));
+      AMGP_HIP(hipStreamSynchronize(s));  // sp leaves scope
+    }
+    if (hipMalloc(&e.val, sizeof(double) * std::max<int64_t>(e.dense, 1)) != hipSuccess ||
+        hipMalloc(&e.doff, sizeof(int32_t) * std::max<int64_t>(e.dense / kSlice, 1)) != hipSuccess)
+      return AMG_ENOMEM;
+    if (e.dense > 0)
+      hipLaunchKernelGGL(k_ell_fill_aligned, dim3(grid_for(nslices * kSlice)), dim3(kBlock), 0, s, n, nslices, ptr,
+                         col, val, anchor, astride, offs, e.sptr, e.desc, e.val, e.doff);
+    AMGP_HIP(hipGetLastError());
+    AMGP_HIP(hipStreamSynchronize(s));
+    return AMG_OK;
+  }();
   if (rc != AMG_OK) {
+    hipStreamSynchronize(s);
     free_ell(e);
     return rc;
   }
@@ -501,42 +722,59 @@ int build_ell32(hipStream_t s, const Ell<double>& a, Ell<float>* out) {
   e.nslices = a.nslices;
   e.padded = a.padded;
   e.group = a.group;
-  if (hipMalloc(&e.sptr, sizeof(int32_t) * (e.nslices + 1)) != hipSuccess) return AMG_ENOMEM;
-  if (hipMalloc(&e.val, sizeof(float) * std::max<int64_t>(e.padded, 1)) != hipSuccess) return AMG_ENOMEM;
-  AMGP_HIP(hipMemcpyAsync(e.sptr, a.sptr, sizeof(int32_t) * (e.nslices + 1), hipMemcpyDeviceToDevice, s));
-  if (a.col) {
-    if (hipMalloc(&e.col, sizeof(int32_t) * std::max<int64_t>(e.padded, 1)) != hipSuccess) return AMG_ENOMEM;
-    AMGP_HIP(hipMemcpyAsync(e.col, a.col, sizeof(int32_t) * e.padded, hipMemcpyDeviceToDevice, s));
+  e.npat = a.npat;
+  e.dense = a.dense;
+  e.patterned = a.patterned;
+  const int64_t stored = a.doff ? a.dense : a.padded;
+  auto copy = [&](auto** to, const auto* from, int64_t count) -> int {
+    if (!from) return AMG_OK;
+    if (hipMalloc((void**)to, sizeof(**to) * std::max<int64_t>(count, 1)) != hipSuccess) return AMG_ENOMEM;
+    AMGP_HIP(hipMemcpyAsync(*to, from, sizeof(**to) * count, hipMemcpyDeviceToDevice, s));
+    return AMG_OK;
+  };
+  const int rc = [&]() -> int {
+    AMGP_TRY(copy(&e.sptr, a.sptr, e.nslices + 1));
+    AMGP_TRY(copy(&e.col, a.col, stored));
+    AMGP_TRY(copy(&e.doff, a.doff, stored / kSlice));
+    AMGP_TRY(copy(&e.desc, a.desc, e.nslices));
+    AMGP_TRY(copy(&e.poff, a.poff, e.npat));
+    AMGP_TRY(copy(&e.pmask, a.pmask, e.npat));
+    if (hipMalloc(&e.val, sizeof(float) * std::max<int64_t>(stored, 1)) != hipSuccess) return AMG_ENOMEM;
+    if (a.desc) {
+      if (hipMalloc(&e.pval, sizeof(float) * e.npat) != hipSuccess) return AMG_ENOMEM;
+      hipLaunchKernelGGL(k_round_f32, dim3(grid_for(e.npat)), dim3(kBlock), 0, s, e.npat, a.pval, e.pval);
+    }
+    if (a.doff && stored > 0)
+      hipLaunchKernelGGL(k_round_f32_aligned, dim3(grid_for(e.nslices * kSlice)), dim3(kBlock), 0, s, e.nslices,
+                         e.sptr, e.desc, a.val, e.val);
+    else if (!a.doff)
+      hipLaunchKernelGGL(k_round_f32, dim3(grid_for(stored)), dim3(kBlock), 0, s, stored, a.val, e.val);
+    AMGP_HIP(hipGetLastError());
+    return AMG_OK;
+  }();
+  if (rc != AMG_OK) {
+    hipStreamSynchronize(s);
+    free_ell(e);
+    return rc;
   }
-  if (a.doff) {
-    if (hipMalloc(&e.doff, sizeof(int32_t) * std::max<int64_t>(e.padded / kSlice, 1)) != hipSuccess) return AMG_ENOMEM;
-    AMGP_HIP(hipMemcpyAsync(e.doff, a.doff, sizeof(int32_t) * (e.padded / kSlice), hipMemcpyDeviceToDevice, s));
-  }
-  if (a.doff)
-    hipLaunchKernelGGL(k_round_f32_aligned, dim3(grid_for(e.nslices * kSlice)), dim3(kBlock), 0, s, e.nslices, e.sptr,
-                       a.val, e.val);
-  else
-    hipLaunchKernelGGL(k_round_f32, dim3(grid_for(e.padded)), dim3(kBlock), 0, s, e.padded, a.val, e.val);
-  AMGP_HIP(hipGetLastError());
   *out = e;
   return AMG_OK;
 }
 
-void free_ell(Ell<double>& e) {
+template <typename T>
+static void free_ell_of(Ell<T>& e) {
   hipFree(e.sptr);
   hipFree(e.col);
   hipFree(e.val);
   hipFree(e.doff);
-  e = Ell<double>();
+  hipFree(e.desc);
+  hipFree(e.poff);
+  hipFree(e.pval);
+  hipFree(e.pmask);
+  e = Ell<T>();
 }
-
-void free_ell(Ell<float>& e) {
-  hipFree(e.sptr);
-  hipFree(e.col);
-  hipFree(e.val);
-  hipFree(e.doff);
-  e = Ell<float>();
-}
+void free_ell(Ell<double>& e) { free_ell_of(e); }
+void free_ell(Ell<float>& e) { free_ell_of(e); }
 
 int launch_aggregates(hipStream_t s, int nx, int ny, int nz, int nbatch, int e, int32_t* agg, int32_t* children,
                       int* cnx, int* cny, int* cnz) {

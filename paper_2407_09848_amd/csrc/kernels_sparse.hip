@@ -84,9 +84,9 @@ __device__ __forceinline__ void st(T* p, T v) {
 // (27-point) FP64 levels and on FP32 levels, a nontemporal one on the other streaming FP64
 // levels.  Measured: 320^3 27-point solve 482.5 -> 480.5 ms, the 256^3 diffusion solve with the
 // FP32 hierarchy 61.2 -> 60.7 ms; on the 7-point FP64 level ordinary loads cost 5% (294 -> 310 us).
-template <bool NT, bool W, typename T>
+template <bool NT, int V, typename T>
 __device__ __forceinline__ T ld_minv(const T* p) {
-  if constexpr (W || std::is_same_v<T, float>) return *p; else return ld<NT>(p);
+  if constexpr (V != 0 || std::is_same_v<T, float>) return *p; else return ld<NT>(p);
 }
 
 // Offset-aligned slices keep each lane's steps in pairs: steps 2q and 2q + 1 of lane l sit at
@@ -268,6 +268,141 @@ __device__ __forceinline__ double aligned_sum_f64(const double* __restrict__ val
   return acc;
 }
 
+// Gathers of the products: g(c) by column, g.at(off, r) at column r + off with a wave-uniform
+// offset known to be in range (the offset then goes into the scalar base address and the row into
+// a 32-bit byte offset, n < 2^28).
+template <typename T>
+struct GatherVec {
+  const T* __restrict__ x;
+  __device__ __forceinline__ T operator()(int c) const { return x[c]; }
+  __device__ __forceinline__ T at(int off, int r) const { return at_row(x + off, r); }
+  static __device__ __forceinline__ T at_row(const T* p, int r) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (uint32_t)r * (uint32_t)sizeof(T));
+  }
+};
+// Kernel variants of the one-row-per-lane levels: narrow and wide dense slices (kWideBatch), and
+// levels with uniform slices, whose kernels also request the row's own vectors first.
+enum Variant { V_NARROW = 0, V_WIDE = 1, V_UNIFORM = 2 };
+
+// The value of the lane below (DPP wave_shr) or above (wave_shl); the lane at the end, which has no
+// such neighbour, keeps `end`.
+constexpr int kDppFromBelow = 0x138, kDppFromAbove = 0x130;
+template <int CTRL>
+__device__ __forceinline__ float dpp_shift(float end, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_shift(double end, double v) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(end), __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(end), __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
+// Sums over the steps of a uniform slice, in ascending order with the products of the dense form
+// (the lanes outside a step's mask multiply by +0).  The pattern is wave-uniform and comes through
+// scalar loads; a batch's gathers are issued together, with no branch among them (one would wait
+// for the loads before it).  FULL: every lane holds every step, so no column needs the clamp.
+// Without the matrix's bytes a step is bound by its row vectors (40 to 56 bytes per FP64 row) and,
+// at 27 points, by the gathers' way through the L1.  Measured on the 27-point 320^3 level, dense
+// slices -> patterns: x-updating step 1639 -> 536 us, step that keeps x 1558 -> 457 us, the CG's
+// product 1448 -> 330 us; with one gather per step instead of triples 677, 594 and 443 us, with
+// nine triples per batch instead of three the whole solve took 177 instead of 160 ms (473 ms with
+// dense slices).  7-point 128^3 level: step that keeps x 28.1 -> 18.6 us.
+
+// Any pattern: one gather per step.
+template <bool FULL, typename T, typename Gf>
+__device__ __forceinline__ T pattern_sum(EllView<T> A, int beg, int w, int r, Gf g) {
+  constexpr int B = 8;
+  T acc = T(0);
+  for (int t = 0; t < w; t += B) {
+    T gv[B], v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int q = beg + min(t + u, w - 1);
+      v[u] = A.pval[q];
+      if constexpr (!FULL) v[u] = __builtin_amdgcn_inverse_ballot_w64(A.pmask[q]) ? v[u] : T(0);
+      gv[u] = FULL ? g.at(A.poff[q], r) : g(min(max(r + A.poff[q], 0), A.last));
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u)
+      if (t + u < w) acc += v[u] * gv[u];
+  }
+  return acc;
+}
+
+// N triples of steps at consecutive offsets from step q on: a triple costs one gather of the whole
+// wavefront (its middle step) and one of the two end lanes; the other left and right neighbours are
+// the middle entries of the adjacent lanes (rows of consecutive lanes are consecutive, and so are
+// their clamped columns).  All 64 lanes are active.
+template <int N, bool FULL, typename T, typename Gf>
+__device__ __forceinline__ T pattern_triples(EllView<T> A, int q, int lane, int r, T acc, Gf g) {
+  T mid[N], end[N];
+  auto gather = [&](int off, int shift) {  // column r + off + shift
+    return FULL ? g.at(off, r + shift) : g(min(max(r + off + shift, 0), A.last));
+  };
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    mid[u] = gather(A.poff[q + 3 * u], 1);
+    end[u] = T(0);
+  }
+  if (((lane + 1) & (kWave - 2)) == 0) {  // lanes 0 and 63
+    const int shift = lane == 0 ? 0 : 2;
+#pragma unroll
+    for (int u = 0; u < N; ++u) end[u] = gather(A.poff[q + 3 * u], shift);
+  }
+  auto value = [&](int t) {
+    return FULL || __builtin_amdgcn_inverse_ballot_w64(A.pmask[q + t]) ? A.pval[q + t] : T(0);
+  };
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    acc += value(3 * u) * dpp_shift<kDppFromBelow>(end[u], mid[u]);
+    acc += value(3 * u + 1) * mid[u];
+    acc += value(3 * u + 2) * dpp_shift<kDppFromAbove>(end[u], mid[u]);
+  }
+  return acc;
+}
+
+constexpr int kTripleBatch = 3;
+template <bool FULL, typename T, typename Gf>
+__device__ __forceinline__ T pattern_triples_sum(EllView<T> A, int beg, int w, int lane, int r, Gf g) {
+  T acc = T(0);
+  int t = 0;
+  for (; t + 3 * kTripleBatch <= w; t += 3 * kTripleBatch)
+    acc = pattern_triples<kTripleBatch, FULL>(A, beg + t, lane, r, acc, g);
+  for (; t < w; t += 3) acc = pattern_triples<1, FULL>(A, beg + t, lane, r, acc, g);
+  return acc;
+}
+
+// The aligned sum of slice s for the row r (its anchor) on this lane; s is wave-uniform.
+template <bool NT, int V, typename T, typename Gf>
+__device__ __forceinline__ T slice_sum(EllView<T> A, int s, int lane, int r, Gf g) {
+  int beg, end;
+  const int32_t* off;
+  if constexpr (V == V_UNIFORM) {
+    const int2 d = A.desc[s];
+    const int b = __builtin_amdgcn_readfirstlane(d.x), info = __builtin_amdgcn_readfirstlane(d.y);
+    const int w = info >> 4;
+    if (info & SLICE_TRIPLES) {
+      if (info & SLICE_FULL) return pattern_triples_sum<true>(A, b, w, lane, r, g);
+      return pattern_triples_sum<false>(A, b, w, lane, r, g);
+    }
+    if (info & SLICE_FULL) return pattern_sum<true>(A, b, w, r, g);
+    if (info & SLICE_MASKED) return pattern_sum<false>(A, b, w, r, g);
+    beg = b << 6;
+    end = (b + w) << 6;
+    off = A.doff + b;
+  } else {
+    beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
+    end = __builtin_amdgcn_readfirstlane(A.sptr[s + 1]);
+    off = A.doff + (beg >> 6);
+  }
+  if constexpr (std::is_same_v<T, float>)
+    return aligned_sum_f32<NT>(A.val, beg, end, lane, off, r, A.last, g);
+  else
+    return aligned_sum_f64<NT, Gf, true, V == V_WIDE ? kWideBatch : V == V_UNIFORM ? 4 : kAlignedBatch>(A.val, beg, end, lane, off, r,
+                                                                                   A.last, g);
+}
+
 // Rows with G lanes each (Ell::group): thread t of the grid serves row t / G, and a
 // wavefront covers exactly one slice of 64 / G rows.
 template <int G>
@@ -284,28 +419,19 @@ __device__ __forceinline__ bool exit_rows(int64_t i, int64_t n) {
   return (logical_block() * kBlock + (threadIdx.x & ~(kWave - 1))) / G >= n;
 }
 
-// (A x)_row; with G > 1 every lane of the row's group returns the sum.  AB: the batch of the
-// FP64 offset-aligned sum.
-template <bool NT, int G, int AB = kAlignedBatch, typename T>
+// (A x)_row; with G > 1 every lane of the row's group returns the sum.
+template <bool NT, int G, int V = V_NARROW, typename T>
 __device__ __forceinline__ T ell_dot(EllView<T> A, int64_t row, const T* __restrict__ x) {
   constexpr int R = kSlice / G;
   // every lane of the wavefront is in the same slice: read its bounds once, as scalars
   const int s = __builtin_amdgcn_readfirstlane((int)(row / R));
+  // offset-aligned slice: the column is the row plus the step's (uniform) offset
+  if constexpr (V == V_UNIFORM) return slice_sum<NT, V>(A, s, (int)(row & 63), (int)row, GatherVec<T>{x});
+  if (G == 1 && A.doff) return slice_sum<NT, V>(A, s, (int)(row & 63), (int)row, GatherVec<T>{x});
   const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
   const int end = __builtin_amdgcn_readfirstlane(A.sptr[s + 1]);
   const int lane = G == 1 ? (int)(row & 63) : (int)(threadIdx.x & 63);
   T acc = T(0);
-  if (G == 1 && A.doff) {
-    // offset-aligned slice: the column is the row plus the step's (uniform) offset
-    const int32_t* off = A.doff + (beg >> 6);
-    const int r = (int)row;
-    if constexpr (std::is_same_v<T, float>) {
-      return aligned_sum_f32<NT>(A.val, beg, end, lane, off, r, A.last, [&](int c) { return x[c]; });
-    } else {
-      auto g = [&](int c) { return x[c]; };
-      return aligned_sum_f64<NT, decltype(g), true, AB>(A.val, beg, end, lane, off, r, A.last, g);
-    }
-  }
 #pragma unroll 4
   for (int p = beg + lane; p < end; p += kSlice) {
     acc += ld<NT>(A.val + p) * x[ld<NT>(A.col + p)];
@@ -340,21 +466,21 @@ __device__ __forceinline__ double block_sum(double v) {
 // ---------------------------------------------------------------------------
 // SpMV and residual
 // ---------------------------------------------------------------------------
-template <typename T, bool NT, int G>
+template <typename T, bool NT, int G, int V = V_NARROW>
 __global__ __launch_bounds__(kBlock) void k_spmv(int64_t n, EllView<T> A, const T* __restrict__ x,
                                                  T* __restrict__ y) {
   const int64_t i = row_of_thread<G>();
   if (exit_rows<G>(i, n)) return;
-  const T v = ell_dot<NT, G>(A, i, x);
+  const T v = ell_dot<NT, G, V>(A, i, x);
   if (row_owner<G>(i, n)) st<NT>(y + i, v);
 }
 
-template <typename T, bool NT, int G>
+template <typename T, bool NT, int G, int V = V_NARROW>
 __global__ __launch_bounds__(kBlock) void k_residual(int64_t n, EllView<T> A, const T* __restrict__ b,
                                                      const T* __restrict__ x, T* __restrict__ r) {
   const int64_t i = row_of_thread<G>();
   if (exit_rows<G>(i, n)) return;
-  const T v = ell_dot<NT, G>(A, i, x);
+  const T v = ell_dot<NT, G, V>(A, i, x);
   if (row_owner<G>(i, n)) r[i] = ld<NT>(b + i) - v;
 }
 
@@ -377,25 +503,24 @@ __global__ __launch_bounds__(kBlock) void k_residual(int64_t n, EllView<T> A, co
 // STORE = false on the last step of an application: only x is needed.
 // Returns the x it stores (0 on rows that store none).
 // ---------------------------------------------------------------------------
-// W: wide slices (one row per lane): the row's vectors are requested before the product, whose
-// steps go in batches of kWideBatch.
-template <typename T, int MODE, bool STORE, bool NT, int G, bool XUPD, bool W>
+// V: wide and uniform slices (one row per lane): the row's vectors are requested before the product.
+template <typename T, int MODE, bool STORE, bool NT, int G, bool XUPD, int V>
 __device__ __forceinline__ T fused_step(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                           const T* __restrict__ gold, T* __restrict__ gnew, const T* rin, T* rout,
                                           T* __restrict__ x, T alpha, T c, T w, T wprev, Wt wv, Wt wpv, Prol<T> pr) {
   const int64_t i = row_of_thread<G>();
   if (exit_rows<G>(i, n)) return T(0);
   T mi, go, ri, xi = T(0);
-  if constexpr (W) {
-    mi = ld_minv<NT, W>(minv + i);
+  if constexpr (V != V_NARROW) {
+    mi = ld_minv<NT, V>(minv + i);
     go = gold[i];
     ri = ld<NT>(rin + i);
     if constexpr (XUPD) xi = ld<NT>(x + i);
   }
-  const T ag = ell_dot<NT, G, W ? kWideBatch : kAlignedBatch>(A, i, gold);
+  const T ag = ell_dot<NT, G, V>(A, i, gold);
   if (!row_owner<G>(i, n)) return T(0);
-  if constexpr (!W) {
-    mi = ld_minv<NT, W>(minv + i);
+  if constexpr (V == V_NARROW) {
+    mi = ld_minv<NT, V>(minv + i);
     go = gold[i];
     ri = ld<NT>(rin + i);
   }
@@ -405,7 +530,7 @@ __device__ __forceinline__ T fused_step(int64_t n, EllView<T> A, const T* __rest
   if constexpr (XUPD) {
     w = wsel(wv, w, i);
     wprev = wsel(wpv, wprev, i);
-    if constexpr (!W) xi = ld<NT>(x + i);
+    if constexpr (V == V_NARROW) xi = ld<NT>(x + i);
     if (pr.agg) xi = xi + pr.xc[pr.agg[i]];
     xn = xi + wprev * go + w * g;
     st<NT>(x + i, xn);
@@ -417,21 +542,21 @@ __device__ __forceinline__ T fused_step(int64_t n, EllView<T> A, const T* __rest
   return xn;
 }
 
-template <typename T, int MODE, bool STORE, bool NT, int G, bool W = false>
+template <typename T, int MODE, bool STORE, bool NT, int G, int V = V_NARROW>
 __global__ __launch_bounds__(kBlock) void k_fused(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                   const T* __restrict__ gold, T* __restrict__ gnew,
                                                   const T* rin, T* rout, T* __restrict__ x, T alpha, T c, T w,
                                                   T wprev, Wt wv, Wt wpv, Prol<T> pr) {
-  fused_step<T, MODE, STORE, NT, G, true, W>(n, A, minv, gold, gnew, rin, rout, x, alpha, c, w, wprev, wv, wpv, pr);
+  fused_step<T, MODE, STORE, NT, G, true, V>(n, A, minv, gold, gnew, rin, rout, x, alpha, c, w, wprev, wv, wpv, pr);
 }
 
 // A stored step that leaves x alone: the next step adds this step's weighted direction (which it
 // reads anyway as its own old direction) together with its own.
-template <typename T, int MODE, bool NT, int G, bool W = false>
+template <typename T, int MODE, bool NT, int G, int V = V_NARROW>
 __global__ __launch_bounds__(kBlock) void k_fused_keep_x(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                          const T* __restrict__ gold, T* __restrict__ gnew,
                                                          const T* rin, T* rout, T alpha, T c) {
-  fused_step<T, MODE, true, NT, G, false, W>(n, A, minv, gold, gnew, rin, rout, nullptr, alpha, c, T(0), T(0), Wt(),
+  fused_step<T, MODE, true, NT, G, false, V>(n, A, minv, gold, gnew, rin, rout, nullptr, alpha, c, T(0), T(0), Wt(),
                                              Wt(), Prol<T>());
 }
 
@@ -441,13 +566,13 @@ __global__ __launch_bounds__(kBlock) void k_fused_keep_x(int64_t n, EllView<T> A
 // partials of (dr, x) and, with drold, of (drold, x), over the x this step stores (an FP32 x is
 // converted exactly).  The products, the block order and the sums are those of k_dot2 on the
 // same grid, so the partials are the same numbers.
-template <typename T, int MODE, bool NT, bool W>
+template <typename T, int MODE, bool NT, int V>
 __global__ __launch_bounds__(kBlock) void k_fused_dot(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                       const T* __restrict__ gold, const T* rin, T* __restrict__ x,
                                                       T alpha, T c, T w, T wprev, Wt wv, Wt wpv, Prol<T> pr,
                                                       const double* __restrict__ dr, const double* __restrict__ drold,
                                                       double* __restrict__ partial) {
-  const double xn = (double)fused_step<T, MODE, false, NT, 1, true, W>(n, A, minv, gold, nullptr, rin, nullptr, x,
+  const double xn = (double)fused_step<T, MODE, false, NT, 1, true, V>(n, A, minv, gold, nullptr, rin, nullptr, x,
                                                                         alpha, c, w, wprev, wv, wpv, pr);
   const int64_t i = row_index();
   double v = 0.0, u = 0.0;
@@ -498,7 +623,22 @@ __global__ __launch_bounds__(kBlock) void k_first_zero(int64_t n, const T* __res
 // MODE 1: r0 = M^{-1} b, d0 = r0 / theta, r1 = r0 - M^{-1} A d0, d1 = alpha d0 + c r1, x = d0 + d1.
 // U: u = M^{-1} b (the same products) was written beforehand by the kernel that produced b (the
 // CG's residual update), so the neighbours' step-1 directions gather one vector instead of two.
-template <typename T, int MODE, bool STORE, bool NT, int G, bool W = false, bool U = false>
+// Direction of step 1 of a neighbour, c1 M^{-1} b (MODE 0) or M^{-1} b / c1 (MODE 1)
+template <typename T, int MODE, bool U>
+struct FirstDir {
+  const T* __restrict__ minv;
+  const T* __restrict__ b;
+  const T* __restrict__ u;
+  T c1;
+  __device__ __forceinline__ T dir(T mb) const { return MODE == 0 ? c1 * mb : mb / c1; }
+  __device__ __forceinline__ T operator()(int j) const { return dir(U ? u[j] : minv[j] * b[j]); }
+  __device__ __forceinline__ T at(int off, int r) const {
+    return dir(U ? GatherVec<T>::at_row(u + off, r)
+                 : GatherVec<T>::at_row(minv + off, r) * GatherVec<T>::at_row(b + off, r));
+  }
+};
+
+template <typename T, int MODE, bool STORE, bool NT, int G, int V = V_NARROW, bool U = false>
 __global__ __launch_bounds__(kBlock) void k_first2_zero(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                         const T* __restrict__ b, T* __restrict__ gnew,
                                                         T* __restrict__ r, T* __restrict__ x, T c1, T alpha, T c,
@@ -507,28 +647,19 @@ __global__ __launch_bounds__(kBlock) void k_first2_zero(int64_t n, EllView<T> A,
   if (exit_rows<G>(i, n)) return;
   constexpr int R = kSlice / G;
   const int s = __builtin_amdgcn_readfirstlane((int)(i / R));
-  const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
-  const int end = __builtin_amdgcn_readfirstlane(A.sptr[s + 1]);
-  const int lane = G == 1 ? (int)(i & 63) : (int)(threadIdx.x & 63);
   T mi = T(0), bi = T(0);
-  if constexpr (W) {  // wide slices: the row's own entries first (see kWideBatch)
+  if constexpr (V != V_NARROW) {  // the row's own entries first (see kWideBatch)
     mi = minv[i];
     bi = b[i];
   }
   T ag = T(0);
-  auto g1of = [&](int j) {
-    const T mb = U ? u[j] : minv[j] * b[j];
-    return (MODE == 0) ? c1 * mb : mb / c1;
-  };
-  if (G == 1 && A.doff) {
-    const int32_t* off = A.doff + (beg >> 6);
-    if constexpr (std::is_same_v<T, float>) {
-      ag = aligned_sum_f32<NT>(A.val, beg, end, lane, off, (int)i, A.last, g1of);
-    } else {
-      ag = aligned_sum_f64<NT, decltype(g1of), true, W ? kWideBatch : kAlignedBatch>(A.val, beg, end, lane, off, (int)i,
-                                                                                    A.last, g1of);
-    }
+  const FirstDir<T, MODE, U> g1of{minv, b, u, c1};
+  if (V == V_UNIFORM || (G == 1 && A.doff)) {
+    ag = slice_sum<NT, V>(A, s, (int)(i & 63), (int)i, g1of);
   } else {
+    const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
+    const int end = __builtin_amdgcn_readfirstlane(A.sptr[s + 1]);
+    const int lane = G == 1 ? (int)(i & 63) : (int)(threadIdx.x & 63);
 #pragma unroll 4
     for (int p = beg + lane; p < end; p += kSlice) {
       const int j = ld<NT>(A.col + p);
@@ -541,7 +672,7 @@ __global__ __launch_bounds__(kBlock) void k_first2_zero(int64_t n, EllView<T> A,
   if (!row_owner<G>(i, n)) return;
   w1 = wsel(w1v, w1, i);
   w2 = wsel(w2v, w2, i);
-  if constexpr (!W) {
+  if constexpr (V == V_NARROW) {
     mi = minv[i];
     bi = b[i];
   }
@@ -567,22 +698,22 @@ __global__ __launch_bounds__(kBlock) void k_first2_zero(int64_t n, EllView<T> A,
 // First step from a nonzero x: r^(0) from b - A x.  x is gathered here, so its
 // update is deferred to the next step (or a separate axpy when k = 1).
 // MODE 0: r = b - A x, g = c M^{-1} r.   MODE 1: r = M^{-1}(b - A x), g = r / c (c = theta).
-template <typename T, int MODE, bool NT, int G, bool W = false>
+template <typename T, int MODE, bool NT, int G, int V = V_NARROW>
 __global__ __launch_bounds__(kBlock) void k_first_res(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                       const T* __restrict__ b, const T* __restrict__ x,
                                                       T* __restrict__ r, T* __restrict__ g, T c) {
   const int64_t i = row_of_thread<G>();
   if (exit_rows<G>(i, n)) return;
   T bi = T(0), mi = T(0);
-  if constexpr (W) {  // wide slices: the row's own entries first (see kWideBatch)
+  if constexpr (V != V_NARROW) {  // the row's own entries first (see kWideBatch)
     bi = ld<NT>(b + i);
-    mi = ld_minv<NT, W>(minv + i);
+    mi = ld_minv<NT, V>(minv + i);
   }
-  const T ax = ell_dot<NT, G, W ? kWideBatch : kAlignedBatch>(A, i, x);
+  const T ax = ell_dot<NT, G, V>(A, i, x);
   if (!row_owner<G>(i, n)) return;
-  if constexpr (!W) {
+  if constexpr (V == V_NARROW) {
     bi = ld<NT>(b + i);
-    mi = ld_minv<NT, W>(minv + i);
+    mi = ld_minv<NT, V>(minv + i);
   }
   const T res = bi - ax;
   if (MODE == 0) {
@@ -595,43 +726,43 @@ __global__ __launch_bounds__(kBlock) void k_first_res(int64_t n, EllView<T> A, c
   }
 }
 
+// x + P x_c of the box prolongation, gathered
+template <typename T>
+struct GatherProl {
+  const T* __restrict__ x;
+  const int32_t* __restrict__ agg;
+  const T* __restrict__ xc;
+  __device__ __forceinline__ T operator()(int c) const { return x[c] + xc[agg[c]]; }
+  __device__ __forceinline__ T at(int off, int r) const {
+    return GatherVec<T>::at_row(x + off, r) + xc[GatherVec<int32_t>::at_row(agg + off, r)];
+  }
+};
+
 // (A (x + P x_c))_row for one row per lane (wave-uniform slice, as ell_dot<NT, 1>): the
 // box prolongation x_j + x_c[agg_j] of every gathered entry, in the arithmetic of k_prolong.
-template <bool NT, typename T>
+template <bool NT, int V, typename T>
 __device__ __forceinline__ T ell_dot_prol(EllView<T> A, int64_t row, const T* __restrict__ x, Prol<T> pr) {
   const int s = __builtin_amdgcn_readfirstlane((int)(row / kSlice));
+  const int lane = (int)(row & 63);
+  const GatherProl<T> g{x, pr.agg, pr.xc};
+  if (V == V_UNIFORM || A.doff) return slice_sum<NT, V>(A, s, lane, (int)row, g);
   const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
   const int end = __builtin_amdgcn_readfirstlane(A.sptr[s + 1]);
-  const int lane = (int)(row & 63);
   T acc = T(0);
-  if (A.doff) {
-    const int32_t* off = A.doff + (beg >> 6);
-    const int r = (int)row;
-    if constexpr (std::is_same_v<T, float>) {
-      return aligned_sum_f32<NT>(A.val, beg, end, lane, off, r, A.last,
-                                 [&](int c) { return x[c] + pr.xc[pr.agg[c]]; });
-    } else {
-      return aligned_sum_f64<NT>(A.val, beg, end, lane, off, r, A.last,
-                                 [&](int c) { return x[c] + pr.xc[pr.agg[c]]; });
-    }
-  }
 #pragma unroll 4
-  for (int p = beg + lane; p < end; p += kSlice) {
-    const int c = ld<NT>(A.col + p);
-    acc += ld<NT>(A.val + p) * (x[c] + pr.xc[pr.agg[c]]);
-  }
+  for (int p = beg + lane; p < end; p += kSlice) acc += ld<NT>(A.val + p) * g(ld<NT>(A.col + p));
   return acc;
 }
 
 // k_first_res on x + P x_c (the post-smoothing's first step takes over the prolongation;
 // x itself is left for the next kernel, which adds the row's own x_c term).
-template <typename T, int MODE, bool NT>
+template <typename T, int MODE, bool NT, int V>
 __global__ __launch_bounds__(kBlock) void k_first_res_prol(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                            const T* __restrict__ b, const T* __restrict__ x,
                                                            Prol<T> pr, T* __restrict__ r, T* __restrict__ g, T c) {
   const int64_t i = row_index();
   if (i >= n) return;
-  const T res = ld<NT>(b + i) - ell_dot_prol<NT>(A, i, x, pr);
+  const T res = ld<NT>(b + i) - ell_dot_prol<NT, V>(A, i, x, pr);
   const T mi = ld<NT>(minv + i);
   if (MODE == 0) {
     st<NT>(r + i, res);
@@ -644,13 +775,13 @@ __global__ __launch_bounds__(kBlock) void k_first_res_prol(int64_t n, EllView<T>
 }
 
 // One l1-Jacobi sweep x_new = x_old + M^{-1}(b - A x_old) (eq. l1smooth).
-template <typename T, int G>
+template <typename T, int G, int V = V_NARROW>
 __global__ __launch_bounds__(kBlock) void k_jacobi(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                    const T* __restrict__ b, const T* __restrict__ xold,
                                                    T* __restrict__ xnew) {
   const int64_t i = row_of_thread<G>();
   if (exit_rows<G>(i, n)) return;
-  const T ax = ell_dot<false, G>(A, i, xold);
+  const T ax = ell_dot<false, G, V>(A, i, xold);
   if (row_owner<G>(i, n)) xnew[i] = xold[i] + minv[i] * (b[i] - ax);
 }
 
@@ -689,7 +820,7 @@ __global__ __launch_bounds__(kBlock) void k_restrict(int64_t nc, const int32_t* 
 // 27-point fine level has 64 entries per aggregate in R (8 per fine row, against 27 in A), a
 // 7-point one 32; R is the same matrix as P^T A, summed in another order, so b_c equals
 // P^T (b - A x) up to rounding.
-template <typename T, bool NT>
+template <typename T, bool NT, int V>
 __global__ __launch_bounds__(kBlock) void k_restrict_product(int64_t nc, EllView<T> R, const int32_t* __restrict__ ch,
                                                              const T* __restrict__ b, const T* __restrict__ x,
                                                              T* __restrict__ bc) {
@@ -698,16 +829,7 @@ __global__ __launch_bounds__(kBlock) void k_restrict_product(int64_t nc, EllView
   const int4 c0 = reinterpret_cast<const int4*>(ch)[2 * I];
   const int4 c1 = reinterpret_cast<const int4*>(ch)[2 * I + 1];
   const int s = __builtin_amdgcn_readfirstlane((int)(I >> 6));
-  const int beg = __builtin_amdgcn_readfirstlane(R.sptr[s]);
-  const int end = __builtin_amdgcn_readfirstlane(R.sptr[s + 1]);
-  const int32_t* off = R.doff + (beg >> 6);
-  const int lane = (int)(I & 63);
-  auto gx = [&](int j) { return x[j]; };
-  T rx;
-  if constexpr (std::is_same_v<T, float>)
-    rx = aligned_sum_f32<NT>(R.val, beg, end, lane, off, c0.x, R.last, gx);
-  else
-    rx = aligned_sum_f64<NT>(R.val, beg, end, lane, off, c0.x, R.last, gx);
+  const T rx = slice_sum<NT, V>(R, s, (int)(I & 63), c0.x, GatherVec<T>{x});
   const int c[kMaxChildren] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
   T sb = T(0);
 #pragma unroll
@@ -720,20 +842,36 @@ __global__ __launch_bounds__(kBlock) void k_restrict_product(int64_t nc, EllView
 // (A x)_row for a row of any slice: the rows of a wavefront may lie in different slices,
 // so the bounds and offsets are per-lane loads.  Same products in the same order as
 // ell_dot<NT, 1>.
-template <bool NT, typename T>
+template <bool NT, int V, typename T>
 __device__ __forceinline__ T ell_dot_any(EllView<T> A, int row, const T* __restrict__ x) {
   const int s = row >> 6;
-  const int beg = A.sptr[s], end = A.sptr[s + 1];
+  int beg, end;
+  const int32_t* off;
   T acc = T(0);
-  if (A.doff) {
-    const int32_t* off = A.doff + (beg >> 6);
-    if constexpr (std::is_same_v<T, float>) {
-      auto g = [&](int c) { return x[c]; };
-      return aligned_sum_f32<NT, decltype(g), false>(A.val, beg, end, row & 63, off, row, A.last, g);
-    } else {
-      auto g = [&](int c) { return x[c]; };
-      return aligned_sum_f64<NT, decltype(g), false>(A.val, beg, end, row & 63, off, row, A.last, g);
+  if constexpr (V == V_UNIFORM) {
+    const int2 d = A.desc[s];
+    const int w = d.y >> 4;
+    if ((d.y & 15) != SLICE_DENSE) {
+      for (int t = d.x; t < d.x + w; ++t) {
+        const T v = (A.pmask[t] >> (row & 63)) & 1 ? A.pval[t] : T(0);
+        acc += v * x[min(max(row + A.poff[t], 0), A.last)];
+      }
+      return acc;
     }
+    beg = d.x << 6;
+    end = (d.x + w) << 6;
+    off = A.doff + d.x;
+  } else {
+    beg = A.sptr[s];
+    end = A.sptr[s + 1];
+    off = A.doff + (beg >> 6);
+  }
+  if (V == V_UNIFORM || A.doff) {
+    auto g = [&](int c) { return x[c]; };
+    if constexpr (std::is_same_v<T, float>)
+      return aligned_sum_f32<NT, decltype(g), false>(A.val, beg, end, row & 63, off, row, A.last, g);
+    else
+      return aligned_sum_f64<NT, decltype(g), false>(A.val, beg, end, row & 63, off, row, A.last, g);
   }
 #pragma unroll 4
   for (int p = beg + (row & 63); p < end; p += kSlice) acc += ld<NT>(A.val + p) * x[ld<NT>(A.col + p)];
@@ -749,7 +887,7 @@ __device__ __forceinline__ T ell_dot_any(EllView<T> A, int row, const T* __restr
 // on the fine level; one launch saved on 262144 rows, 6.5 vs 5.0 + 4.8 us).
 constexpr int64_t kFusedRestrictMaxRows = 1 << 20;
 
-template <typename T, bool NT>
+template <typename T, bool NT, int V>
 __global__ __launch_bounds__(kBlock) void k_res_restrict(int64_t nc, EllView<T> A, const int32_t* __restrict__ ch,
                                                          const T* __restrict__ b, const T* __restrict__ x,
                                                          T* __restrict__ bc) {
@@ -758,7 +896,7 @@ __global__ __launch_bounds__(kBlock) void k_res_restrict(int64_t nc, EllView<T> 
   T res = T(0);
   if (I < nc) {
     const int c = ld<NT>(ch + t);
-    if (c >= 0) res = ld<NT>(b + c) - ell_dot_any<NT>(A, c, x);
+    if (c >= 0) res = ld<NT>(b + c) - ell_dot_any<NT, V>(A, c, x);
   }
   const int base = (int)(threadIdx.x & (kWave - 1)) & ~(kMaxChildren - 1);
   T sum = T(0);
@@ -857,6 +995,21 @@ __global__ __launch_bounds__(kBlock) void k_dot2(int64_t n, const double* __rest
   }
 }
 
+// Entries of the CG direction: p_new itself (PRE) or z + beta p_old.
+template <typename TZ, bool PRE>
+struct Direction {
+  const TZ* __restrict__ z;
+  const double* __restrict__ p;
+  double beta;
+  __device__ __forceinline__ double operator()(int j) const {
+    if constexpr (PRE) return p[j]; else return (double)z[j] + beta * p[j];
+  }
+  __device__ __forceinline__ double at(int off, int r) const {
+    const double pr = GatherVec<double>::at_row(p + off, r);
+    if constexpr (PRE) return pr; else return (double)GatherVec<TZ>::at_row(z + off, r) + beta * pr;
+  }
+};
+
 // The CG direction update fused into the next SpMV: p_new = z + beta p_old and
 // q = A p_new, with (p_new, q) partials.  p_new of a neighbour is formed on the
 // fly from z and p_old (exactly the value stored for it), so p_new is written
@@ -867,7 +1020,7 @@ __global__ __launch_bounds__(kBlock) void k_dot2(int64_t n, const double* __rest
 // instead of two (measured on a 27-point level of 32.8M rows: 1.36 ms + 0.13 ms for the separate
 // pass, against 1.77 ms with z and p_old both gathered; 7-point 256^3: 0.191 + 0.071 against
 // 0.284 ms).  The values and the products are the same either way.
-template <bool NT, typename TZ, bool PRE, bool W = false>
+template <bool NT, typename TZ, bool PRE, int V = V_NARROW>
 __global__ __launch_bounds__(kBlock) void k_spmv_dot_p(int64_t n, EllView<double> A, const double* __restrict__ scal,
                                                        const TZ* __restrict__ z, const double* __restrict__ pold,
                                                        double* pnew, double* __restrict__ q,
@@ -878,22 +1031,18 @@ __global__ __launch_bounds__(kBlock) void k_spmv_dot_p(int64_t n, EllView<double
   constexpr bool kStreamVal = NT || std::is_same_v<TZ, float>;
   const int64_t i = row_index();
   const double beta = scal[S_BETA];
-  auto pj = [&](int j) {
-    if constexpr (PRE) return pnew[j]; else return (double)z[j] + beta * pold[j];
-  };
+  const Direction<TZ, PRE> pj{z, PRE ? pnew : pold, beta};
   double v = 0.0;
   if (i < n) {
     const int s = __builtin_amdgcn_readfirstlane((int)(i >> 6));
-    const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
-    const int end = __builtin_amdgcn_readfirstlane(A.sptr[s + 1]);
     double pw = 0.0;
-    if constexpr (PRE && W) pw = pnew[i];  // wide slices: the row's own entry first (see kWideBatch)
+    if constexpr (PRE && V != V_NARROW) pw = pnew[i];  // the row's own entry first (see kWideBatch)
     double acc = 0.0;
-    if (A.doff) {
-      const int32_t* off = A.doff + (beg >> 6);
-      acc = aligned_sum_f64<kStreamVal, decltype(pj), true, W ? kWideBatch : kAlignedBatch>(
-          A.val, beg, end, (int)(i & 63), off, (int)i, A.last, pj);
+    if (V == V_UNIFORM || A.doff) {
+      acc = slice_sum<kStreamVal, V>(A, s, (int)(i & 63), (int)i, pj);
     } else {
+      const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
+      const int end = __builtin_amdgcn_readfirstlane(A.sptr[s + 1]);
 #pragma unroll 4
       for (int p = beg + (int)(i & 63); p < end; p += kSlice) {
         const int j = ld<NT>(A.col + p);
@@ -902,7 +1051,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_dot_p(int64_t n, EllView<double
     }
     double pi;
     if constexpr (PRE) {
-      pi = W ? pw : pnew[i];
+      pi = V != V_NARROW ? pw : pnew[i];
     } else {
       const double po = pold[i];
       pi = z[i] + beta * po;
@@ -1071,10 +1220,37 @@ __global__ __launch_bounds__(kBlock) void k_check_finite(int64_t n, const double
 inline bool streamed(unsigned grid) { return grid > kRemapMaxBlocks; }
 
 // FP64 offset-aligned levels of one row per lane averaging at least kWideMinSteps stored steps
-// per row take the wide-batch kernels (W = true); FP32 levels keep theirs (quads in batches of
+// per row take the wide-batch kernels (V_WIDE); FP32 levels keep theirs (quads in batches of
 // 12 steps already).
 inline bool wide(const Ell<double>& A) {
   return A.doff && A.group == 1 && A.padded >= (int64_t)kWideMinSteps * A.n;
+}
+inline bool wide(const Ell<float>&) { return false; }
+
+// Runs f(NT, V) for a level of one row per lane: the streaming hints of `nt`, and the variant of
+// its slices.  kHasWide: the kernel has a wide form (streaming levels only).
+template <bool kHasWide, typename T, typename F>
+void with_variant(const Ell<T>& A, bool nt, F&& f) {
+  using Narrow = std::integral_constant<int, V_NARROW>;
+  using Wide = std::integral_constant<int, V_WIDE>;
+  using Uniform = std::integral_constant<int, V_UNIFORM>;
+  if (A.desc) {
+    if (nt)
+      f(std::true_type(), Uniform());
+    else
+      f(std::false_type(), Uniform());
+    return;
+  }
+  if constexpr (kHasWide && std::is_same_v<T, double>) {
+    if (nt && wide(A)) {
+      f(std::true_type(), Wide());
+      return;
+    }
+  }
+  if (nt)
+    f(std::true_type(), Narrow());
+  else
+    f(std::false_type(), Narrow());
 }
 
 // The levels whose merged first two steps can read u = M^{-1} b instead of gathering M^{-1} and b
@@ -1101,13 +1277,13 @@ int launch_spmv(hipStream_t s, const Ell<T>& A, const T* x, T* y) {
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const unsigned g = xcd_grid(A.n * G);
-    if constexpr (G == 1) {
-      if (streamed(g)) {
-        hipLaunchKernelGGL((k_spmv<T, true, 1>), dim3(g), dim3(kBlock), 0, s, A.n, view(A), x, y);
-        return;
-      }
-    }
-    hipLaunchKernelGGL((k_spmv<T, false, G>), dim3(g), dim3(kBlock), 0, s, A.n, view(A), x, y);
+    if constexpr (G == 1)
+      with_variant<false>(A, streamed(g), [&](auto nt, auto v) {
+        hipLaunchKernelGGL((k_spmv<T, decltype(nt)::value, 1, decltype(v)::value>), dim3(g), dim3(kBlock), 0, s, A.n,
+                           view(A), x, y);
+      });
+    else
+      hipLaunchKernelGGL((k_spmv<T, false, G>), dim3(g), dim3(kBlock), 0, s, A.n, view(A), x, y);
   });
 }
 
@@ -1116,13 +1292,13 @@ int launch_residual(hipStream_t s, const Ell<T>& A, const T* b, const T* x, T* r
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const unsigned g = xcd_grid(A.n * G);
-    if constexpr (G == 1) {
-      if (streamed(g)) {
-        hipLaunchKernelGGL((k_residual<T, true, 1>), dim3(g), dim3(kBlock), 0, s, A.n, view(A), b, x, r);
-        return;
-      }
-    }
-    hipLaunchKernelGGL((k_residual<T, false, G>), dim3(g), dim3(kBlock), 0, s, A.n, view(A), b, x, r);
+    if constexpr (G == 1)
+      with_variant<false>(A, streamed(g), [&](auto nt, auto v) {
+        hipLaunchKernelGGL((k_residual<T, decltype(nt)::value, 1, decltype(v)::value>), dim3(g), dim3(kBlock), 0, s,
+                           A.n, view(A), b, x, r);
+      });
+    else
+      hipLaunchKernelGGL((k_residual<T, false, G>), dim3(g), dim3(kBlock), 0, s, A.n, view(A), b, x, r);
   });
 }
 
@@ -1151,22 +1327,22 @@ int launch_first_zero(hipStream_t s, int mode, bool store, int64_t n, const T* m
   return LAUNCH_OK();
 }
 
-template <typename T, bool NT, int G, bool W = false, bool U = false>
+template <typename T, bool NT, int G, int V = V_NARROW, bool U = false>
 void go_first2_zero(dim3 gr, hipStream_t s, int mode, bool store, EllView<T> A, int64_t n, const T* minv,
                     const T* b, T* gnew, T* r, T* x, T a1, T a2, T a3, T a4, T a5, Wt w1v, Wt w2v,
                     const T* u = nullptr) {
   dim3 bl(kBlock);
   if (mode == 0 && store)
-    hipLaunchKernelGGL((k_first2_zero<T, 0, true, NT, G, W, U>), gr, bl, 0, s, n, A, minv, b, gnew, r, x, a1, a2,
+    hipLaunchKernelGGL((k_first2_zero<T, 0, true, NT, G, V, U>), gr, bl, 0, s, n, A, minv, b, gnew, r, x, a1, a2,
                        a3, a4, a5, w1v, w2v, u);
   else if (mode == 0)
-    hipLaunchKernelGGL((k_first2_zero<T, 0, false, NT, G, W, U>), gr, bl, 0, s, n, A, minv, b, gnew, r, x, a1, a2,
+    hipLaunchKernelGGL((k_first2_zero<T, 0, false, NT, G, V, U>), gr, bl, 0, s, n, A, minv, b, gnew, r, x, a1, a2,
                        a3, a4, a5, w1v, w2v, u);
   else if (store)
-    hipLaunchKernelGGL((k_first2_zero<T, 1, true, NT, G, W, U>), gr, bl, 0, s, n, A, minv, b, gnew, r, x, a1, a2,
+    hipLaunchKernelGGL((k_first2_zero<T, 1, true, NT, G, V, U>), gr, bl, 0, s, n, A, minv, b, gnew, r, x, a1, a2,
                        a3, a4, a5, w1v, w2v, u);
   else
-    hipLaunchKernelGGL((k_first2_zero<T, 1, false, NT, G, W, U>), gr, bl, 0, s, n, A, minv, b, gnew, r, x, a1, a2,
+    hipLaunchKernelGGL((k_first2_zero<T, 1, false, NT, G, V, U>), gr, bl, 0, s, n, A, minv, b, gnew, r, x, a1, a2,
                        a3, a4, a5, w1v, w2v, u);
 }
 
@@ -1177,40 +1353,35 @@ int launch_first2_zero(hipStream_t s, int mode, bool store, const Ell<T>& A, con
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const dim3 gr(xcd_grid(A.n * G));
+    auto go = [&](auto nt, auto v, auto hu) {
+      go_first2_zero<T, decltype(nt)::value, G, decltype(v)::value, decltype(hu)::value>(
+          gr, s, mode, store, view(A), A.n, minv, b, gnew, r, x, (T)c1, (T)alpha, (T)c, (T)w1, (T)w2, w1v, w2v, u);
+    };
     if constexpr (G == 1) {
-      if (streamed(gr.x)) {
-        if constexpr (std::is_same_v<T, double>) {
-          if (wide(A)) {
-            if (u)
-              go_first2_zero<T, true, 1, true, true>(gr, s, mode, store, view(A), A.n, minv, b, gnew, r, x, (T)c1,
-                                                     (T)alpha, (T)c, (T)w1, (T)w2, w1v, w2v, u);
-            else
-              go_first2_zero<T, true, 1, true>(gr, s, mode, store, view(A), A.n, minv, b, gnew, r, x, (T)c1,
-                                               (T)alpha, (T)c, (T)w1, (T)w2, w1v, w2v);
+      with_variant<true>(A, streamed(gr.x), [&](auto nt, auto v) {
+        // u is given on streaming 27-point levels only (first2_takes_u)
+        if constexpr (decltype(nt)::value &&
+                      (decltype(v)::value != V_NARROW || std::is_same_v<T, float>)) {
+          if (u) {
+            go(nt, v, std::true_type());
             return;
           }
-        } else if (u) {
-          go_first2_zero<T, true, 1, false, true>(gr, s, mode, store, view(A), A.n, minv, b, gnew, r, x, (T)c1,
-                                                  (T)alpha, (T)c, (T)w1, (T)w2, w1v, w2v, u);
-          return;
         }
-        go_first2_zero<T, true, 1>(gr, s, mode, store, view(A), A.n, minv, b, gnew, r, x, (T)c1, (T)alpha, (T)c,
-                                   (T)w1, (T)w2, w1v, w2v);
-        return;
-      }
+        go(nt, v, std::false_type());
+      });
+    } else {
+      go(std::false_type(), std::integral_constant<int, V_NARROW>(), std::false_type());
     }
-    go_first2_zero<T, false, G>(gr, s, mode, store, view(A), A.n, minv, b, gnew, r, x, (T)c1, (T)alpha, (T)c,
-                                (T)w1, (T)w2, w1v, w2v);
   });
 }
 
-template <typename T, bool NT, int G, bool W = false>
+template <typename T, bool NT, int G, int V = V_NARROW>
 void go_first_res(dim3 gr, hipStream_t s, int mode, EllView<T> A, int64_t n, const T* minv, const T* b, const T* x,
                   T* r, T* g, T c) {
   if (mode == 0)
-    hipLaunchKernelGGL((k_first_res<T, 0, NT, G, W>), gr, dim3(kBlock), 0, s, n, A, minv, b, x, r, g, c);
+    hipLaunchKernelGGL((k_first_res<T, 0, NT, G, V>), gr, dim3(kBlock), 0, s, n, A, minv, b, x, r, g, c);
   else
-    hipLaunchKernelGGL((k_first_res<T, 1, NT, G, W>), gr, dim3(kBlock), 0, s, n, A, minv, b, x, r, g, c);
+    hipLaunchKernelGGL((k_first_res<T, 1, NT, G, V>), gr, dim3(kBlock), 0, s, n, A, minv, b, x, r, g, c);
 }
 
 template <typename T>
@@ -1218,64 +1389,52 @@ int launch_first_res(hipStream_t s, int mode, const Ell<T>& A, const T* minv, co
                      T* g, double c, Prol<T> pr) {
   if (pr.agg) {
     if (A.group != 1) return AMG_EINVAL;
-    const dim3 gr(xcd_grid(A.n));
-    const T cc = (T)c;
-    const EllView<T> av = view(A);
-    const dim3 bl(kBlock);
-    if (streamed(gr.x)) {
+    const dim3 gr(xcd_grid(A.n)), bl(kBlock);
+    with_variant<false>(A, streamed(gr.x), [&](auto nt, auto v) {
+      constexpr bool NT = decltype(nt)::value;
+      constexpr int V = decltype(v)::value;
       if (mode == 0)
-        hipLaunchKernelGGL((k_first_res_prol<T, 0, true>), gr, bl, 0, s, A.n, av, minv, b, x, pr, r, g, cc);
+        hipLaunchKernelGGL((k_first_res_prol<T, 0, NT, V>), gr, bl, 0, s, A.n, view(A), minv, b, x, pr, r, g, (T)c);
       else
-        hipLaunchKernelGGL((k_first_res_prol<T, 1, true>), gr, bl, 0, s, A.n, av, minv, b, x, pr, r, g, cc);
-    } else {
-      if (mode == 0)
-        hipLaunchKernelGGL((k_first_res_prol<T, 0, false>), gr, bl, 0, s, A.n, av, minv, b, x, pr, r, g, cc);
-      else
-        hipLaunchKernelGGL((k_first_res_prol<T, 1, false>), gr, bl, 0, s, A.n, av, minv, b, x, pr, r, g, cc);
-    }
+        hipLaunchKernelGGL((k_first_res_prol<T, 1, NT, V>), gr, bl, 0, s, A.n, view(A), minv, b, x, pr, r, g, (T)c);
+    });
     return LAUNCH_OK();
   }
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const dim3 gr(xcd_grid(A.n * G));
-    if constexpr (G == 1) {
-      if (streamed(gr.x)) {
-        if constexpr (std::is_same_v<T, double>) {
-          if (wide(A)) {
-            go_first_res<T, true, 1, true>(gr, s, mode, view(A), A.n, minv, b, x, r, g, (T)c);
-            return;
-          }
-        }
-        go_first_res<T, true, 1>(gr, s, mode, view(A), A.n, minv, b, x, r, g, (T)c);
-        return;
-      }
-    }
-    go_first_res<T, false, G>(gr, s, mode, view(A), A.n, minv, b, x, r, g, (T)c);
+    if constexpr (G == 1)
+      with_variant<true>(A, streamed(gr.x), [&](auto nt, auto v) {
+        go_first_res<T, decltype(nt)::value, 1, decltype(v)::value>(gr, s, mode, view(A), A.n, minv, b, x, r, g,
+                                                                    (T)c);
+      });
+    else
+      go_first_res<T, false, G>(gr, s, mode, view(A), A.n, minv, b, x, r, g, (T)c);
   });
 }
 
-template <typename T, bool NT, int G, bool W = false>
+template <typename T, bool NT, int G, int V = V_NARROW>
 void go_fused(dim3 gr, hipStream_t s, int mode, bool store, EllView<T> A, int64_t n, const T* minv, const T* gold,
               T* gnew, const T* rin, T* rout, T* x, T a_, T c_, T w_, T wp_, Wt wv, Wt wpv, Prol<T> pr) {
   dim3 bl(kBlock);
   if (!x) {  // a stored step that leaves x alone (the caller only passes null x with store set)
     if (mode == 0)
-      hipLaunchKernelGGL((k_fused_keep_x<T, 0, NT, G, W>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, a_, c_);
+      hipLaunchKernelGGL((k_fused_keep_x<T, 0, NT, G, V>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, a_, c_);
     else
-      hipLaunchKernelGGL((k_fused_keep_x<T, 1, NT, G, W>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, a_, c_);
+      hipLaunchKernelGGL((k_fused_keep_x<T, 1, NT, G, V>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, a_, c_);
     return;
   }
   if (mode == 0 && store)
-    hipLaunchKernelGGL((k_fused<T, 0, true, NT, G, W>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, x, a_, c_,
+    hipLaunchKernelGGL((k_fused<T, 0, true, NT, G, V>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, x, a_, c_,
                        w_, wp_, wv, wpv, pr);
   else if (mode == 0)
-    hipLaunchKernelGGL((k_fused<T, 0, false, NT, G, W>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, x, a_, c_,
+    hipLaunchKernelGGL((k_fused<T, 0, false, NT, G, V>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, x, a_, c_,
                        w_, wp_, wv, wpv, pr);
   else if (store)
-    hipLaunchKernelGGL((k_fused<T, 1, true, NT, G, W>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, x, a_, c_,
+    hipLaunchKernelGGL((k_fused<T, 1, true, NT, G, V>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, x, a_, c_,
                        w_, wp_, wv, wpv, pr);
   else
-    hipLaunchKernelGGL((k_fused<T, 1, false, NT, G, W>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, x, a_, c_,
+    hipLaunchKernelGGL((k_fused<T, 1, false, NT, G, V>), gr, bl, 0, s, n, A, minv, gold, gnew, rin, rout, x, a_, c_,
                        w_, wp_, wv, wpv, pr);
 }
 
@@ -1286,22 +1445,15 @@ int launch_fused(hipStream_t s, int mode, bool store, const Ell<T>& A, const T* 
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const dim3 gr(xcd_grid(A.n * G));
-    if constexpr (G == 1) {
-      if (streamed(gr.x)) {
-        if constexpr (std::is_same_v<T, double>) {
-          if (wide(A)) {
-            go_fused<T, true, 1, true>(gr, s, mode, store, view(A), A.n, minv, gold, gnew, rin, rout, x, (T)alpha,
-                                       (T)c, (T)w, (T)wprev, wv, wpv, pr);
-            return;
-          }
-        }
-        go_fused<T, true, 1>(gr, s, mode, store, view(A), A.n, minv, gold, gnew, rin, rout, x, (T)alpha, (T)c, (T)w,
-                             (T)wprev, wv, wpv, pr);
-        return;
-      }
-    }
-    go_fused<T, false, G>(gr, s, mode, store, view(A), A.n, minv, gold, gnew, rin, rout, x, (T)alpha, (T)c, (T)w,
-                          (T)wprev, wv, wpv, pr);
+    if constexpr (G == 1)
+      with_variant<true>(A, streamed(gr.x), [&](auto nt, auto v) {
+        go_fused<T, decltype(nt)::value, 1, decltype(v)::value>(gr, s, mode, store, view(A), A.n, minv, gold, gnew,
+                                                                rin, rout, x, (T)alpha, (T)c, (T)w, (T)wprev, wv,
+                                                                wpv, pr);
+      });
+    else
+      go_fused<T, false, G>(gr, s, mode, store, view(A), A.n, minv, gold, gnew, rin, rout, x, (T)alpha, (T)c, (T)w,
+                            (T)wprev, wv, wpv, pr);
   });
 }
 
@@ -1311,25 +1463,16 @@ int launch_fused_dot(hipStream_t s, int mode, const Ell<T>& A, const T* minv, co
                      const double* drold, double* partial, unsigned* nblocks) {
   if (A.group != 1) return AMG_EINVAL;
   const dim3 gr(xcd_grid(A.n)), bl(kBlock);
-  auto go = [&](auto nt, auto wd) {
-    constexpr bool NT = decltype(nt)::value, W = decltype(wd)::value;
+  with_variant<true>(A, streamed(gr.x), [&](auto nt, auto v) {
+    constexpr bool NT = decltype(nt)::value;
+    constexpr int V = decltype(v)::value;
     if (mode == 0)
-      hipLaunchKernelGGL((k_fused_dot<T, 0, NT, W>), gr, bl, 0, s, A.n, view(A), minv, gold, rin, x, (T)alpha, (T)c,
+      hipLaunchKernelGGL((k_fused_dot<T, 0, NT, V>), gr, bl, 0, s, A.n, view(A), minv, gold, rin, x, (T)alpha, (T)c,
                          (T)w, (T)wprev, wv, wpv, pr, dr, drold, partial);
     else
-      hipLaunchKernelGGL((k_fused_dot<T, 1, NT, W>), gr, bl, 0, s, A.n, view(A), minv, gold, rin, x, (T)alpha, (T)c,
+      hipLaunchKernelGGL((k_fused_dot<T, 1, NT, V>), gr, bl, 0, s, A.n, view(A), minv, gold, rin, x, (T)alpha, (T)c,
                          (T)w, (T)wprev, wv, wpv, pr, dr, drold, partial);
-  };
-  using T_ = std::true_type;
-  using F_ = std::false_type;
-  bool wd = false;
-  if constexpr (std::is_same_v<T, double>) wd = wide(A);  // the wide batches are FP64 only, as in launch_fused
-  if (!streamed(gr.x))
-    go(F_(), F_());
-  else if (wd)
-    go(T_(), std::integral_constant<bool, std::is_same_v<T, double>>());
-  else
-    go(T_(), F_());
+  });
   *nblocks = gr.x;
   return LAUNCH_OK();
 }
@@ -1344,8 +1487,13 @@ template <typename T>
 int launch_jacobi(hipStream_t s, const Ell<T>& A, const T* minv, const T* b, const T* xold, T* xnew) {
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
-    hipLaunchKernelGGL((k_jacobi<T, G>), dim3(xcd_grid(A.n * G)), dim3(kBlock), 0, s, A.n, view(A), minv, b, xold,
-                       xnew);
+    const dim3 gr(xcd_grid(A.n * G)), bl(kBlock);
+    if constexpr (G == 1)
+      with_variant<false>(A, false, [&](auto, auto v) {
+        hipLaunchKernelGGL((k_jacobi<T, 1, decltype(v)::value>), gr, bl, 0, s, A.n, view(A), minv, b, xold, xnew);
+      });
+    else
+      hipLaunchKernelGGL((k_jacobi<T, G>), gr, bl, 0, s, A.n, view(A), minv, b, xold, xnew);
   });
 }
 
@@ -1361,10 +1509,10 @@ int launch_restrict(hipStream_t s, const Ell<T>& A, int64_t nc, const int32_t* c
   static_assert(kMaxChildren == 8 && kWave % kMaxChildren == 0, "eight lanes per aggregate");
   if (A.group == 1 && A.n <= kFusedRestrictMaxRows) {
     const unsigned g = xcd_grid(nc * kMaxChildren);
-    if (streamed(g))
-      hipLaunchKernelGGL((k_res_restrict<T, true>), dim3(g), dim3(kBlock), 0, s, nc, view(A), children, b, x, bc);
-    else
-      hipLaunchKernelGGL((k_res_restrict<T, false>), dim3(g), dim3(kBlock), 0, s, nc, view(A), children, b, x, bc);
+    with_variant<false>(A, streamed(g), [&](auto nt, auto v) {
+      hipLaunchKernelGGL((k_res_restrict<T, decltype(nt)::value, decltype(v)::value>), dim3(g), dim3(kBlock), 0, s,
+                         nc, view(A), children, b, x, bc);
+    });
     return LAUNCH_OK();
   }
   AMGP_TRY(launch_residual<T>(s, A, b, x, tmp));
@@ -1377,10 +1525,10 @@ int launch_restrict_product(hipStream_t s, const Ell<T>& R, const int32_t* child
                             T* bc) {
   // streaming loads when the fine level streams
   const unsigned g = xcd_grid(R.n);
-  if (streamed(xcd_grid(R.ncols)))
-    hipLaunchKernelGGL((k_restrict_product<T, true>), dim3(g), dim3(kBlock), 0, s, R.n, view(R), children, b, x, bc);
-  else
-    hipLaunchKernelGGL((k_restrict_product<T, false>), dim3(g), dim3(kBlock), 0, s, R.n, view(R), children, b, x, bc);
+  with_variant<false>(R, streamed(xcd_grid(R.ncols)), [&](auto nt, auto v) {
+    hipLaunchKernelGGL((k_restrict_product<T, decltype(nt)::value, decltype(v)::value>), dim3(g), dim3(kBlock), 0, s,
+                       R.n, view(R), children, b, x, bc);
+  });
   return LAUNCH_OK();
 }
 
@@ -1464,15 +1612,15 @@ int launch_spmv_dot_p(hipStream_t s, const Ell<double>& A, const double* scal, c
   const unsigned g = xcd_grid(A.n);
   if (streamed(g)) {
     hipLaunchKernelGGL((k_form_p<true, TZ>), dim3(g), dim3(kBlock), 0, s, A.n, scal, z, pold, pnew, x);
-    if (wide(A))
-      hipLaunchKernelGGL((k_spmv_dot_p<true, TZ, true, true>), dim3(g), dim3(kBlock), 0, s, A.n, view(A), scal, z,
-                         pold, pnew, q, partial, nullptr);
-    else
-      hipLaunchKernelGGL((k_spmv_dot_p<true, TZ, true>), dim3(g), dim3(kBlock), 0, s, A.n, view(A), scal, z, pold,
-                         pnew, q, partial, nullptr);
+    with_variant<true>(A, true, [&](auto, auto v) {
+      hipLaunchKernelGGL((k_spmv_dot_p<true, TZ, true, decltype(v)::value>), dim3(g), dim3(kBlock), 0, s, A.n,
+                         view(A), scal, z, pold, pnew, q, partial, nullptr);
+    });
   } else {
-    hipLaunchKernelGGL((k_spmv_dot_p<false, TZ, false>), dim3(g), dim3(kBlock), 0, s, A.n, view(A), scal, z, pold,
-                       pnew, q, partial, x);
+    with_variant<true>(A, false, [&](auto, auto v) {
+      hipLaunchKernelGGL((k_spmv_dot_p<false, TZ, false, decltype(v)::value>), dim3(g), dim3(kBlock), 0, s, A.n,
+                         view(A), scal, z, pold, pnew, q, partial, x);
+    });
   }
   *nblocks = g;
   return LAUNCH_OK();

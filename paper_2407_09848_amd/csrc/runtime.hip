@@ -1111,6 +1111,18 @@ int amg_level_layout(const amg_handle* h, int level, int64_t* h_padded, int* h_l
   return AMG_OK;
 }
 
+int amg_level_patterns(const amg_handle* h, int level, int restriction, int64_t* h_values, int64_t* h_slices,
+                       int64_t* h_steps) {
+  if (!h || level < 0 || level >= h->impl.nlevels || (restriction != 0 && restriction != 1)) return AMG_EINVAL;
+  const amgp::Level& L = h->impl.lv[level];
+  if (restriction && (L.general || !L.R64.val)) return AMG_EINVAL;
+  const amgp::Ell<double>& A = restriction ? L.R64 : L.A64;
+  if (h_values) *h_values = A.desc ? A.dense : A.padded;
+  if (h_slices) *h_slices = A.patterned;
+  if (h_steps) *h_steps = A.npat;
+  return AMG_OK;
+}
+
 int amg_level_transfer(const amg_handle* h, int level, int* h_form, int64_t* h_stored) {
   if (!h || level < 0 || level >= h->impl.nlevels - 1) return AMG_EINVAL;
   const amgp::Level& L = h->impl.lv[level];

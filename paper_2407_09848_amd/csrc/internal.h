@@ -440,10 +440,9 @@ int vbm_aggregates(hipStream_t s, const Csr& A, double theta, int32_t* agg, int6
 void free_ell(Ell<float>& e);
 
 // ---- dense kernels (kernels_dense.hip) ----
-// In place: dense[nbatch][np][np] (SPD, lower part used) -> inverse A^{-1}, full symmetric.
-int dense_spd_inverse(hipStream_t s, int nbatch, int64_t np, double* dense, int* flag);
-// copy the lower 64x64 blocks of each np x np matrix into contiguous tiles (tile J(J+1)/2 + I = block (J, I))
-int pack_lower_tiles(hipStream_t s, int nbatch, int64_t np, const double* dense, double** packed);
+// dense[nbatch][np][np] (SPD, lower tiles read, overwritten) -> *packed: the lower 64x64 blocks of
+// each A^{-1} in contiguous tiles (tile J(J+1)/2 + I = block (J, I)); the caller's, also on error
+int dense_spd_inverse(hipStream_t s, int nbatch, int64_t np, double* dense, double** packed, int* flag);
 // x = A^{-1} b from the lower blocks of the symmetric inverse; part holds nbatch * (np/64)^2 * 64 doubles
 template <typename T>
 int launch_coarse_symv(hipStream_t s, int nbatch, int64_t nl, int64_t np, const double* ainv, const T* b, T* x,

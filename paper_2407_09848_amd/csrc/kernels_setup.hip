@@ -492,6 +492,7 @@ __global__ __launch_bounds__(64) void k_rap(int64_t nc, const int32_t* __restric
   }
 }
 
+// entries of the dense matrices, zeroed beforehand; padding rows get a unit diagonal
 __global__ void k_to_dense(int64_t total_rows, int64_t nl, int64_t np, const int32_t* __restrict__ ptr,
                            const int32_t* __restrict__ col, const double* __restrict__ val,
                            double* __restrict__ dense, int* __restrict__ flag) {
@@ -499,7 +500,6 @@ __global__ void k_to_dense(int64_t total_rows, int64_t nl, int64_t np, const int
   if (r >= total_rows) return;
   const int64_t p = r / np, lr = r % np;
   double* row = dense + p * np * np + lr * np;
-  for (int64_t j = 0; j < np; ++j) row[j] = 0.0;
   if (lr >= nl) {
     row[lr] = 1.0;  // padding: identity
     return;
@@ -830,6 +830,7 @@ int galerkin(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, c
 int launch_to_dense(hipStream_t s, int nbatch, int64_t nl, int64_t np, const int32_t* ptr, const int32_t* col,
                     const double* val, double* dense, int* flag) {
   const int64_t rows = (int64_t)nbatch * np;
+  AMGP_HIP(hipMemsetAsync(dense, 0, sizeof(double) * rows * np, s));
   hipLaunchKernelGGL(k_to_dense, dim3(grid_for(rows)), dim3(kBlock), 0, s, rows, nl, np, ptr, col, val, dense,
                      flag);
   return hipGetLastError() == hipSuccess ? AMG_OK : AMG_EHIP;

@@ -846,8 +846,7 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
     double* dense = nullptr;
     AMGP_TRY(dalloc(&dense, (int64_t)h->nbatch * h->ncp * h->ncp));
     int rc = launch_to_dense(s, h->nbatch, h->ncl, h->ncp, L.csr_ptr, L.csr_col, L.csr_val, dense, h->dflag);
-    if (rc == AMG_OK) rc = dense_spd_inverse(s, h->nbatch, h->ncp, dense, h->dflag);
-    if (rc == AMG_OK) rc = pack_lower_tiles(s, h->nbatch, h->ncp, dense, &h->ainv);
+    if (rc == AMG_OK) rc = dense_spd_inverse(s, h->nbatch, h->ncp, dense, &h->ainv, h->dflag);
     if (rc == AMG_OK && hipStreamSynchronize(s) != hipSuccess) rc = AMG_EHIP;
     hipFree(dense);
     if (rc != AMG_OK) return rc;

@@ -72,9 +72,8 @@ struct Ell {
   int astride = 1;
   // uniform slices (null: none)
   int2* desc = nullptr;          // [nslices] {beg, 16 * steps + kind}
-  int32_t* poff = nullptr;       // [npat] offsets, values and lane masks of the patterns' steps
-  T* pval = nullptr;
-  unsigned long long* pmask = nullptr;
+  unsigned long long* pat = nullptr;  // [npat] lane masks of the patterns' steps, then values (T, [npat]
+                                      // of 8 bytes), then offsets (int32): 20 npat bytes
   int64_t npat = 0;
   int64_t dense = 0;             // stored values (dense slices); padded counts all slices' steps
   int64_t patterned = 0;         // slices kept as patterns
@@ -97,6 +96,8 @@ struct Prol {
   const T* xc = nullptr;
 };
 
+// What the kernels are given (small: the small levels' kernels are bound by their launches).  A
+// matrix with uniform slices has desc and the patterns in the places of sptr and col.
 template <typename T>
 struct EllView {
   const int32_t* __restrict__ sptr;
@@ -104,16 +105,22 @@ struct EllView {
   const T* __restrict__ val;
   const int32_t* __restrict__ doff;
   int32_t last;  // columns - 1, the clamp of offset-aligned columns
-  const int2* __restrict__ desc;
-  const int32_t* __restrict__ poff;
-  const T* __restrict__ pval;
-  const unsigned long long* __restrict__ pmask;
+  int32_t npat;
+  __host__ __device__ const int2* desc() const { return reinterpret_cast<const int2*>(sptr); }
+  __host__ __device__ const unsigned long long* pmask() const {
+    return reinterpret_cast<const unsigned long long*>(col);
+  }
+  __host__ __device__ const T* pval() const { return reinterpret_cast<const T*>(pmask() + npat); }
+  __host__ __device__ const int32_t* poff() const { return reinterpret_cast<const int32_t*>(pmask() + 2 * (int64_t)npat); }
 };
 
 template <typename T>
 inline EllView<T> view(const Ell<T>& e) {
-  return EllView<T>{e.sptr, e.col, e.val, e.doff, (int32_t)((e.ncols > 0 ? e.ncols : e.n) - 1),
-                    e.desc, e.poff, e.pval, e.pmask};
+  const int32_t last = (int32_t)((e.ncols > 0 ? e.ncols : e.n) - 1);
+  if (e.desc)
+    return EllView<T>{reinterpret_cast<const int32_t*>(e.desc), reinterpret_cast<const int32_t*>(e.pat), e.val, e.doff,
+                      last, (int32_t)e.npat};
+  return EllView<T>{e.sptr, e.col, e.val, e.doff, last, 0};
 }
 
 // Work vectors of one level in one precision.

@@ -312,17 +312,18 @@ __global__ void k_pattern_resolve(int64_t nslices, const int32_t* __restrict__ k
 __global__ void k_pattern_write(int64_t nslices, const int32_t* __restrict__ rep, const int2* __restrict__ desc,
                                 const int32_t* __restrict__ offs, int stride,
                                 const unsigned long long* __restrict__ vtab,
-                                const unsigned long long* __restrict__ mtab, int32_t* __restrict__ poff,
-                                double* __restrict__ pval, unsigned long long* __restrict__ pmask) {
+                                const unsigned long long* __restrict__ mtab, int npat,
+                                unsigned long long* __restrict__ pat) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t s = g / kSlice;
   if (s >= nslices || rep[s] != s) return;
   const int2 d = desc[s];
   const int t = (int)(g % kSlice);
   if (t >= d.y >> 4) return;
-  poff[d.x + t] = offs[s * kSlice + t];
-  pval[d.x + t] = __longlong_as_double((long long)vtab[s * stride + t]);
-  pmask[d.x + t] = mtab[s * stride + t];
+  const int64_t q = d.x + t;
+  pat[q] = mtab[s * stride + t];
+  pat[npat + q] = vtab[s * stride + t];
+  reinterpret_cast<int32_t*>(pat + 2 * (int64_t)npat)[q] = offs[s * kSlice + t];
 }
 
 // Offset-aligned fill: lane l of slice s (row r, anchor a = r or anchor[r * astride]) puts, at
@@ -617,13 +618,11 @@ int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_
       e.dense = steps * kSlice;
       e.patterned = uniform;
       if (hipMalloc(&e.desc, sizeof(int2) * nslices) != hipSuccess ||
-          hipMalloc(&e.poff, sizeof(int32_t) * e.npat) != hipSuccess ||
-          hipMalloc(&e.pval, sizeof(double) * e.npat) != hipSuccess ||
-          hipMalloc(&e.pmask, sizeof(unsigned long long) * e.npat) != hipSuccess)
+          hipMalloc(&e.pat, (20 * e.npat + 7) / 8 * 8) != hipSuccess)
         return AMG_ENOMEM;
       AMGP_HIP(hipMemcpyAsync(e.desc, desc.data(), sizeof(int2) * nslices, hipMemcpyHostToDevice, s));
       hipLaunchKernelGGL(k_pattern_write, dim3(grid_for(nslices * kSlice)), dim3(kBlock), 0, s, nslices, rep, e.desc,
-                         offs, wmax, vtab, mtab, e.poff, e.pval, e.pmask);
+                         offs, wmax, vtab, mtab, (int)e.npat, e.pat);
       AMGP_HIP(hipGetLastError());
       AMGP_HIP(hipStreamSynchronize(s));  // desc and tab leave scope
     } else {
@@ -737,12 +736,13 @@ int build_ell32(hipStream_t s, const Ell<double>& a, Ell<float>* out) {
     AMGP_TRY(copy(&e.col, a.col, stored));
     AMGP_TRY(copy(&e.doff, a.doff, stored / kSlice));
     AMGP_TRY(copy(&e.desc, a.desc, e.nslices));
-    AMGP_TRY(copy(&e.poff, a.poff, e.npat));
-    AMGP_TRY(copy(&e.pmask, a.pmask, e.npat));
+    AMGP_TRY(copy(&e.pat, a.pat, (20 * e.npat + 7) / 8));
     if (hipMalloc(&e.val, sizeof(float) * std::max<int64_t>(stored, 1)) != hipSuccess) return AMG_ENOMEM;
     if (a.desc) {
-      if (hipMalloc(&e.pval, sizeof(float) * e.npat) != hipSuccess) return AMG_ENOMEM;
-      hipLaunchKernelGGL(k_round_f32, dim3(grid_for(e.npat)), dim3(kBlock), 0, s, e.npat, a.pval, e.pval);
+      const EllView<double> av = view(a);
+      const EllView<float> ev = view(e);
+      hipLaunchKernelGGL(k_round_f32, dim3(grid_for(e.npat)), dim3(kBlock), 0, s, e.npat, av.pval(),
+                         const_cast<float*>(ev.pval()));
     }
     if (a.doff && stored > 0)
       hipLaunchKernelGGL(k_round_f32_aligned, dim3(grid_for(e.nslices * kSlice)), dim3(kBlock), 0, s, e.nslices,
@@ -768,9 +768,7 @@ static void free_ell_of(Ell<T>& e) {
   hipFree(e.val);
   hipFree(e.doff);
   hipFree(e.desc);
-  hipFree(e.poff);
-  hipFree(e.pval);
-  hipFree(e.pmask);
+  hipFree(e.pat);
   e = Ell<T>();
 }
 void free_ell(Ell<double>& e) { free_ell_of(e); }

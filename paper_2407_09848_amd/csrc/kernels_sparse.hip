@@ -319,9 +319,9 @@ __device__ __forceinline__ T pattern_sum(EllView<T> A, int beg, int w, int r, Gf
 #pragma unroll
     for (int u = 0; u < B; ++u) {
       const int q = beg + min(t + u, w - 1);
-      v[u] = A.pval[q];
-      if constexpr (!FULL) v[u] = __builtin_amdgcn_inverse_ballot_w64(A.pmask[q]) ? v[u] : T(0);
-      gv[u] = FULL ? g.at(A.poff[q], r) : g(min(max(r + A.poff[q], 0), A.last));
+      v[u] = A.pval()[q];
+      if constexpr (!FULL) v[u] = __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q]) ? v[u] : T(0);
+      gv[u] = FULL ? g.at(A.poff()[q], r) : g(min(max(r + A.poff()[q], 0), A.last));
     }
 #pragma unroll
     for (int u = 0; u < B; ++u)
@@ -342,16 +342,16 @@ __device__ __forceinline__ T pattern_triples(EllView<T> A, int q, int lane, int 
   };
 #pragma unroll
   for (int u = 0; u < N; ++u) {
-    mid[u] = gather(A.poff[q + 3 * u], 1);
+    mid[u] = gather(A.poff()[q + 3 * u], 1);
     end[u] = T(0);
   }
   if (((lane + 1) & (kWave - 2)) == 0) {  // lanes 0 and 63
     const int shift = lane == 0 ? 0 : 2;
 #pragma unroll
-    for (int u = 0; u < N; ++u) end[u] = gather(A.poff[q + 3 * u], shift);
+    for (int u = 0; u < N; ++u) end[u] = gather(A.poff()[q + 3 * u], shift);
   }
   auto value = [&](int t) {
-    return FULL || __builtin_amdgcn_inverse_ballot_w64(A.pmask[q + t]) ? A.pval[q + t] : T(0);
+    return FULL || __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q + t]) ? A.pval()[q + t] : T(0);
   };
 #pragma unroll
   for (int u = 0; u < N; ++u) {
@@ -379,7 +379,7 @@ __device__ __forceinline__ T slice_sum(EllView<T> A, int s, int lane, int r, Gf 
   int beg, end;
   const int32_t* off;
   if constexpr (V == V_UNIFORM) {
-    const int2 d = A.desc[s];
+    const int2 d = A.desc()[s];
     const int b = __builtin_amdgcn_readfirstlane(d.x), info = __builtin_amdgcn_readfirstlane(d.y);
     const int w = info >> 4;
     if (info & SLICE_TRIPLES) {
@@ -849,12 +849,12 @@ __device__ __forceinline__ T ell_dot_any(EllView<T> A, int row, const T* __restr
   const int32_t* off;
   T acc = T(0);
   if constexpr (V == V_UNIFORM) {
-    const int2 d = A.desc[s];
+    const int2 d = A.desc()[s];
     const int w = d.y >> 4;
     if ((d.y & 15) != SLICE_DENSE) {
       for (int t = d.x; t < d.x + w; ++t) {
-        const T v = (A.pmask[t] >> (row & 63)) & 1 ? A.pval[t] : T(0);
-        acc += v * x[min(max(row + A.poff[t], 0), A.last)];
+        const T v = (A.pmask()[t] >> (row & 63)) & 1 ? A.pval()[t] : T(0);
+        acc += v * x[min(max(row + A.poff()[t], 0), A.last)];
       }
       return acc;
     }

@@ -40,9 +40,9 @@ __device__ __forceinline__ bool find_entry(const int32_t* ptr, const int32_t* co
 template <typename T>
 struct DevBuf {
   T* p = nullptr;
-  ~DevBuf() { hipFree(p); }
+  ~DevBuf() { dev_free(p); }
   int alloc(int64_t count) {
-    return hipMalloc(&p, sizeof(T) * (size_t)std::max<int64_t>(count, 1)) == hipSuccess ? AMG_OK : AMG_ENOMEM;
+    return temp_malloc(&p, sizeof(T) * (size_t)std::max<int64_t>(count, 1)) == hipSuccess ? AMG_OK : AMG_ENOMEM;
   }
 };
 

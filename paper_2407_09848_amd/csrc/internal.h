@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "amgpoly.h"
+#include "memory.h"
 
 namespace amgp {
 
@@ -193,6 +194,7 @@ struct AdjVecs {
 };
 
 struct Handle {
+  Arena arena;  // the arrays kept from setup on
   int nlevels = 0;
   // per-problem weights for AMG_OPTCHEB4 while a differentiable V-cycle runs:
   // dbeta[(p * nlevels + l) * dbeta_k + j - 1], else null (host table used)
@@ -432,8 +434,14 @@ int tentative_prolongator(hipStream_t s, int64_t n, int64_t nc, const int32_t* a
 // P = (I - omega D^{-1} A) P_hat for a P_hat with one entry per row,
 // omega = 4 / (3 ||D^{-1} A||_inf) per stacked problem
 int smoothed_prolongator(hipStream_t s, const Csr& A, int nbatch, const Csr& Phat, Csr* P, int* flag);
-// host exclusive scan of cnt[0, m) into ptr[0, m]; returns the total (rc = AMG_ECAPACITY beyond int32)
-int64_t scan_ptr(hipStream_t s, int64_t m, const int32_t* cnt, int32_t* ptr, int* rc);
+// exclusive scan of ceil(cnt / div) * scale, cnt[0, m), into ptr[0, m] (ptr may be cnt); returns the
+// total (rc = AMG_ECAPACITY beyond int32); synchronises the stream
+int64_t scan_ptr(hipStream_t s, int64_t m, const int32_t* cnt, int32_t* ptr, int* rc, int div = 1, int scale = 1);
+// P^T of the 2x2x2 box prolongator from its children lists
+int children_transpose(hipStream_t s, int64_t n, int64_t nc, const int32_t* children, Csr* PT);
+// A_c = R P for the box P from R = P^T A, exactly zero sums left out; AMG_EINVAL when a row of R has
+// more than 64 entries (galerkin and drop_small then)
+int galerkin_from_restriction(hipStream_t s, const Csr& R, const int32_t* agg, Csr* Ac);
 // ---- compatible weighted matching (kernels_match.hip) ----
 // composite tentative prolongator of `steps` matching steps on A (structurally symmetric, ascending
 // columns) from the smooth vector w0 (null: ones); *wnext (device, ncols entries) is the coarse one

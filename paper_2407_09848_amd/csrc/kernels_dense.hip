@@ -351,9 +351,9 @@ int dense_spd_inverse(hipStream_t s, int nbatch, int64_t np64, double* dense, do
   double* X = nullptr;     // L^{-1}
   *packed = nullptr;
   const int rc = [&]() -> int {
-    if (hipMalloc(&dinv, sizeof(double) * nbatch * sD) != hipSuccess ||
-        hipMalloc(&X, sizeof(double) * nbatch * sA) != hipSuccess ||
-        hipMalloc(packed, sizeof(double) * (size_t)nbatch * ntiles * TM * TM) != hipSuccess)
+    if (temp_malloc(&dinv, sizeof(double) * nbatch * sD) != hipSuccess ||
+        temp_malloc(&X, sizeof(double) * nbatch * sA) != hipSuccess ||
+        keep_malloc(packed, sizeof(double) * (size_t)nbatch * ntiles * TM * TM) != hipSuccess)
       return AMG_ENOMEM;
     // 1. Cholesky, right looking, on the lower tiles
     for (int k = 0; k < nb; ++k) {
@@ -393,8 +393,8 @@ int dense_spd_inverse(hipStream_t s, int nbatch, int64_t np64, double* dense, do
     return AMG_OK;
   }();
   if (rc != AMG_OK) hipStreamSynchronize(s);
-  hipFree(dinv);
-  hipFree(X);
+  dev_free(dinv);
+  dev_free(X);
   return rc;
 }
 

@@ -14,6 +14,7 @@
 //   transpose sorted by column (unique keys), so the result is deterministic.
 #include <algorithm>
 
+#include "graph.h"
 #include "internal.h"
 
 namespace amgp {
@@ -326,6 +327,159 @@ __global__ void k_identity_rows(int64_t n, const int32_t* __restrict__ agg, int3
   }
 }
 
+// Exclusive scan of counts, each rounded up to a multiple of div in units of it and scaled, in
+// chunks: their sums, the sums' scan by one block (the total last), and the chunks' own scans.
+// ptr may be cnt.
+constexpr int kScanPer = 16;
+constexpr int kScanChunk = kBlock * kScanPer;
+
+__device__ __forceinline__ int64_t scan_value(const int32_t* cnt, int64_t i, int64_t m, int div, int scale) {
+  return i < m ? (int64_t)((cnt[i] + div - 1) / div) * scale : 0;
+}
+
+// inclusive scan over a block of up to 1024 threads; every thread gets the total too
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t* total) {
+  __shared__ int64_t wsum[1024 / kWave];
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int64_t u = __shfl_up(v, off, kWave);
+    if (lane >= off) v += u;
+  }
+  if (lane == kWave - 1) wsum[w] = v;
+  __syncthreads();
+  int64_t before = 0, all = 0;
+  for (int k = 0; k < nw; ++k) {
+    if (k < w) before += wsum[k];
+    all += wsum[k];
+  }
+  __syncthreads();
+  *total = all;
+  return v + before;
+}
+
+__global__ __launch_bounds__(kBlock) void k_scan_part(int64_t m, const int32_t* __restrict__ cnt, int div, int scale,
+                                                      int64_t* __restrict__ part) {
+  int64_t v = 0, total;
+  for (int k = 0; k < kScanPer; ++k)
+    v += scan_value(cnt, (int64_t)blockIdx.x * kScanChunk + k * kBlock + threadIdx.x, m, div, scale);
+  block_scan(v, &total);
+  if (threadIdx.x == 0) part[blockIdx.x] = total;
+}
+
+__global__ __launch_bounds__(1024) void k_scan_top(int64_t nb, int64_t* __restrict__ part) {
+  int64_t carry = 0;
+  for (int64_t b0 = 0; b0 < nb; b0 += 1024) {
+    const int64_t i = b0 + threadIdx.x;
+    const int64_t v = i < nb ? part[i] : 0;
+    int64_t total;
+    const int64_t incl = block_scan(v, &total);
+    if (i < nb) part[i] = carry + incl - v;
+    carry += total;
+  }
+  if (threadIdx.x == 0) part[nb] = carry;
+}
+
+__global__ __launch_bounds__(kBlock) void k_scan_write(int64_t m, int64_t nb, const int32_t* cnt, int div, int scale,
+                                                       const int64_t* __restrict__ part, int32_t* ptr) {
+  int64_t carry = nb > 0 ? part[blockIdx.x] : 0;
+  for (int k = 0; k < kScanPer; ++k) {
+    const int64_t i = (int64_t)blockIdx.x * kScanChunk + k * kBlock + threadIdx.x;
+    const int64_t v = scan_value(cnt, i, m, div, scale);
+    int64_t total;
+    const int64_t incl = block_scan(v, &total);
+    if (i < m) ptr[i] = (int32_t)(carry + incl - v);
+    carry += total;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) ptr[m] = (int32_t)part[nb];
+}
+
+// the largest of m counts into *most (zeroed beforehand)
+__global__ __launch_bounds__(kBlock) void k_max_count(int64_t m, const int32_t* __restrict__ cnt,
+                                                      int32_t* __restrict__ most) {
+  int v = 0;
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < m; i += (int64_t)gridDim.x * kBlock)
+    v = max(v, cnt[i]);
+  for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
+  if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(most, v);
+}
+
+__global__ void k_row_lengths(int64_t m, const int32_t* __restrict__ ptr, int32_t* __restrict__ len) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < m) len[i] = ptr[i + 1] - ptr[i];
+}
+
+// rows longer than kShortRow, in any order: list[0, *count)
+__global__ void k_long_rows(int64_t m, const int32_t* __restrict__ ptr, int32_t* __restrict__ list,
+                            int32_t* __restrict__ count) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < m && ptr[i + 1] - ptr[i] > kShortRow) list[atomicAdd(count, 1)] = (int32_t)i;
+}
+
+// transpose of the box prolongator (one entry 1.0 per row) from the aggregates' rows
+__global__ void k_children_count(int64_t nc, const int32_t* __restrict__ ch, int32_t* __restrict__ cnt) {
+  const int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (I >= nc) return;
+  int c = 0;
+  while (c < kMaxChildren && ch[I * kMaxChildren + c] >= 0) ++c;
+  cnt[I] = c;
+}
+
+__global__ void k_children_rows(int64_t nc, const int32_t* __restrict__ ch, const int32_t* __restrict__ ptr,
+                                int32_t* __restrict__ col, double* __restrict__ val) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t I = t / kMaxChildren;
+  const int c = (int)(t % kMaxChildren);
+  if (I >= nc || c >= ptr[I + 1] - ptr[I]) return;
+  col[ptr[I] + c] = ch[t];
+  val[ptr[I] + c] = 1.0;
+}
+
+// Row I of A_c = R P for the box P (one entry 1.0 per row) from row I of R = P^T A, at most 64
+// entries: one wavefront per row, an entry per lane.  Every lane adds up the entries of its own
+// aggregate J = agg[column] in ascending column order (the other lanes' broadcast one by one); the
+// first lane of each J keeps the sum unless it is exactly zero (or no number).  FILL = false: counts.
+// Measured on the 27-point 320^3 matrix against one thread per coarse row over the eight fine rows
+// (216 entries, sorted by insertion into a list in scratch memory): 79.8 -> 13.9 ms for both passes.
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) void k_galerkin_rows(int64_t nc, const int32_t* __restrict__ rptr,
+                                                          const int32_t* __restrict__ rcol,
+                                                          const double* __restrict__ rval,
+                                                          const int32_t* __restrict__ agg,
+                                                          int32_t* __restrict__ cnt_or_ptr, int32_t* __restrict__ ccol,
+                                                          double* __restrict__ cval) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t I = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
+  if (I >= nc) return;
+  const int beg = __builtin_amdgcn_readfirstlane(rptr[I]), len = __builtin_amdgcn_readfirstlane(rptr[I + 1]) - beg;
+  const int J = lane < len ? agg[rcol[beg + lane]] : INT_MAX;
+  const double v = lane < len ? rval[beg + lane] : 0.0;
+  double sum = 0.0;
+  bool first = lane < len;
+  for (int e = 0; e < len; ++e) {
+    const int Je = __builtin_amdgcn_readlane(J, e);
+    const double ve = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), e),
+                                       __builtin_amdgcn_readlane(__double2loint(v), e));
+    if (Je == J) {
+      sum += ve;
+      first = first && e >= lane;
+    }
+  }
+  const bool keep = first && fabs(sum) > 0.0;
+  const unsigned long long kept = __ballot(keep);
+  if constexpr (!FILL) {
+    if (lane == 0) cnt_or_ptr[I] = __popcll(kept);
+  } else {
+    int rank = 0;
+    for (unsigned long long m = kept; m; m &= m - 1)
+      rank += __builtin_amdgcn_readlane(J, __builtin_amdgcn_readfirstlane(__ffsll(m) - 1)) < J;
+    if (keep) {
+      const int q = cnt_or_ptr[I] + rank;
+      ccol[q] = J;
+      cval[q] = sum;
+    }
+  }
+}
+
 template <int CAP>
 void go_spgemm(bool fill, hipStream_t s, int64_t m, const Csr& X, const Csr& Y, int32_t* cnt, const int32_t* cptr,
                int32_t* ccol, double* cval, int* flag) {
@@ -360,42 +514,46 @@ int read_flag(hipStream_t s, const int* flag, int which) {
 
 }  // namespace
 
-// Host exclusive scan of cnt[0, m) into ptr[0, m]; returns the total or -1 beyond int32.
-int64_t scan_ptr(hipStream_t s, int64_t m, const int32_t* cnt, int32_t* ptr, int* rc) {
-  std::vector<int32_t> h(m);
-  *rc = AMG_OK;
-  if (m > 0 && hipMemcpyAsync(h.data(), cnt, sizeof(int32_t) * m, hipMemcpyDeviceToHost, s) != hipSuccess) {
-    *rc = AMG_EHIP;
-    return -1;
-  }
-  if (hipStreamSynchronize(s) != hipSuccess) {
-    *rc = AMG_EHIP;
-    return -1;
-  }
-  std::vector<int32_t> p(m + 1);
-  int64_t acc = 0;
-  for (int64_t i = 0; i < m; ++i) {
-    p[i] = (int32_t)acc;
-    acc += h[i];
-    if (acc >= (int64_t)INT32_MAX) {
-      *rc = AMG_ECAPACITY;
-      return -1;
-    }
-  }
-  p[m] = (int32_t)acc;
-  if (hipMemcpyAsync(ptr, p.data(), sizeof(int32_t) * (m + 1), hipMemcpyHostToDevice, s) != hipSuccess ||
+int64_t scan_ptr(hipStream_t s, int64_t m, const int32_t* cnt, int32_t* ptr, int* rc, int div, int scale) {
+  graph::DevBuf<int64_t> part;
+  const int64_t nb = (m + kScanChunk - 1) / kScanChunk;
+  *rc = part.alloc(nb + 1);
+  if (*rc != AMG_OK) return -1;
+  int64_t total = 0;
+  if (nb > 0)
+    hipLaunchKernelGGL(k_scan_part, dim3((unsigned)nb), dim3(kBlock), 0, s, m, cnt, div, scale, part.p);
+  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, nb, part.p);
+  hipLaunchKernelGGL(k_scan_write, dim3((unsigned)std::max<int64_t>(nb, 1)), dim3(kBlock), 0, s, m, nb, cnt, div, scale,
+                     (const int64_t*)part.p, ptr);
+  if (hipMemcpyAsync(&total, part.p + nb, sizeof(total), hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess) {
     *rc = AMG_EHIP;
     return -1;
   }
-  return acc;
+  if (total >= (int64_t)INT32_MAX) {
+    *rc = AMG_ECAPACITY;
+    return -1;
+  }
+  return total;
 }
 
 void free_csr(Csr& a) {
-  hipFree(a.ptr);
-  hipFree(a.col);
-  hipFree(a.val);
+  dev_free(a.ptr);
+  dev_free(a.col);
+  dev_free(a.val);
   a = Csr();
+}
+
+// largest of m counts; scratch: one device int
+int64_t max_count(hipStream_t s, int64_t m, const int32_t* cnt, int32_t* scratch, int* rc) {
+  int32_t most = 0;
+  *rc = AMG_OK;
+  if (hipMemsetAsync(scratch, 0, sizeof(int32_t), s) != hipSuccess) *rc = AMG_EHIP;
+  hipLaunchKernelGGL(k_max_count, dim3(std::min(1024u, grid_for(m))), dim3(kBlock), 0, s, m, cnt, scratch);
+  if (hipMemcpyAsync(&most, scratch, sizeof(most), hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess)
+    *rc = AMG_EHIP;
+  return most;
 }
 
 int spgemm(hipStream_t s, const Csr& X, const Csr& Y, Csr* C, int* flag) {
@@ -403,45 +561,43 @@ int spgemm(hipStream_t s, const Csr& X, const Csr& Y, Csr* C, int* flag) {
   *C = Csr();
   if (m <= 0 || m > (int64_t)UINT32_MAX) return AMG_EINVAL;
   int32_t* cnt = nullptr;
-  if (hipMalloc(&cnt, sizeof(int32_t) * (m + 1)) != hipSuccess) return AMG_ENOMEM;
+  if (temp_malloc(&cnt, sizeof(int32_t) * (m + 1)) != hipSuccess) return AMG_ENOMEM;
   // table size: the smallest power of two of at least twice the longest row bound
   hipLaunchKernelGGL(k_prod_bound, dim3(grid_for(m)), dim3(kBlock), 0, s, m, X.ptr, X.col, Y.ptr, cnt);
-  std::vector<int32_t> hb(m);
   int rc = AMG_OK;
-  if (hipMemcpyAsync(hb.data(), cnt, sizeof(int32_t) * m, hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess) {
-    hipFree(cnt);
-    return AMG_EHIP;
+  const int64_t bound = max_count(s, m, cnt, cnt + m, &rc);
+  if (rc != AMG_OK) {
+    dev_free(cnt);
+    return rc;
   }
-  const int64_t bound = *std::max_element(hb.begin(), hb.end());
   int cap = 64;
   while (cap < 2 * bound && cap < kMaxHash) cap <<= 1;
   rc = run_spgemm(cap, false, s, m, X, Y, cnt, nullptr, nullptr, nullptr, flag);
   if (rc != AMG_OK) {
-    hipFree(cnt);
+    dev_free(cnt);
     return rc;
   }
   const int full = read_flag(s, flag, F_CAPACITY);
   if (full != 0) {
-    hipFree(cnt);
+    dev_free(cnt);
     return full < 0 ? AMG_EHIP : AMG_ECAPACITY;
   }
   Csr c;
   c.m = m;
   c.ncols = Y.ncols;
-  if (hipMalloc(&c.ptr, sizeof(int32_t) * (m + 1)) != hipSuccess) {
-    hipFree(cnt);
+  if (temp_malloc(&c.ptr, sizeof(int32_t) * (m + 1)) != hipSuccess) {
+    dev_free(cnt);
     return AMG_ENOMEM;
   }
   const int64_t nnz = scan_ptr(s, m, cnt, c.ptr, &rc);
-  hipFree(cnt);
+  dev_free(cnt);
   if (rc != AMG_OK) {
     free_csr(c);
     return rc;
   }
   c.nnz = nnz;
-  if (hipMalloc(&c.col, sizeof(int32_t) * std::max<int64_t>(nnz, 1)) != hipSuccess ||
-      hipMalloc(&c.val, sizeof(double) * std::max<int64_t>(nnz, 1)) != hipSuccess) {
+  if (temp_malloc(&c.col, sizeof(int32_t) * std::max<int64_t>(nnz, 1)) != hipSuccess ||
+      temp_malloc(&c.val, sizeof(double) * std::max<int64_t>(nnz, 1)) != hipSuccess) {
     free_csr(c);
     return AMG_ENOMEM;
   }
@@ -460,21 +616,21 @@ int drop_small(hipStream_t s, Csr* a, double tau) {
   o.m = a->m;
   o.ncols = a->ncols;
   int32_t* kept = nullptr;
-  if (hipMalloc(&kept, sizeof(int32_t) * (a->m + 1)) != hipSuccess) return AMG_ENOMEM;
+  if (temp_malloc(&kept, sizeof(int32_t) * (a->m + 1)) != hipSuccess) return AMG_ENOMEM;
   hipLaunchKernelGGL(k_keep_count, dim3(grid_for(a->m)), dim3(kBlock), 0, s, a->m, a->ptr, a->val, tau, kept);
-  if (hipMalloc(&o.ptr, sizeof(int32_t) * (a->m + 1)) != hipSuccess) {
-    hipFree(kept);
+  if (temp_malloc(&o.ptr, sizeof(int32_t) * (a->m + 1)) != hipSuccess) {
+    dev_free(kept);
     return AMG_ENOMEM;
   }
   int rc = AMG_OK;
   o.nnz = scan_ptr(s, a->m, kept, o.ptr, &rc);
-  hipFree(kept);
+  dev_free(kept);
   if (rc != AMG_OK) {
     free_csr(o);
     return rc;
   }
-  if (hipMalloc(&o.col, sizeof(int32_t) * std::max<int64_t>(o.nnz, 1)) != hipSuccess ||
-      hipMalloc(&o.val, sizeof(double) * std::max<int64_t>(o.nnz, 1)) != hipSuccess) {
+  if (temp_malloc(&o.col, sizeof(int32_t) * std::max<int64_t>(o.nnz, 1)) != hipSuccess ||
+      temp_malloc(&o.val, sizeof(double) * std::max<int64_t>(o.nnz, 1)) != hipSuccess) {
     free_csr(o);
     return AMG_ENOMEM;
   }
@@ -495,16 +651,16 @@ int transpose(hipStream_t s, const Csr& a, Csr* t) {
   o.ncols = a.m;
   o.nnz = a.nnz;
   int32_t* cnt = nullptr;
-  if (hipMalloc(&cnt, sizeof(int32_t) * (o.m + 1)) != hipSuccess) return AMG_ENOMEM;
+  if (temp_malloc(&cnt, sizeof(int32_t) * (o.m + 1)) != hipSuccess) return AMG_ENOMEM;
   int rc = AMG_OK;
   if (hipMemsetAsync(cnt, 0, sizeof(int32_t) * (o.m + 1), s) != hipSuccess) rc = AMG_EHIP;
   if (rc == AMG_OK) {
     hipLaunchKernelGGL(k_col_count, dim3(grid_for(a.nnz)), dim3(kBlock), 0, s, a.nnz, a.col, cnt);
-    if (hipMalloc(&o.ptr, sizeof(int32_t) * (o.m + 1)) != hipSuccess) rc = AMG_ENOMEM;
+    if (temp_malloc(&o.ptr, sizeof(int32_t) * (o.m + 1)) != hipSuccess) rc = AMG_ENOMEM;
   }
   if (rc == AMG_OK) scan_ptr(s, o.m, cnt, o.ptr, &rc);
-  if (rc == AMG_OK && (hipMalloc(&o.col, sizeof(int32_t) * std::max<int64_t>(o.nnz, 1)) != hipSuccess ||
-                       hipMalloc(&o.val, sizeof(double) * std::max<int64_t>(o.nnz, 1)) != hipSuccess))
+  if (rc == AMG_OK && (temp_malloc(&o.col, sizeof(int32_t) * std::max<int64_t>(o.nnz, 1)) != hipSuccess ||
+                       temp_malloc(&o.val, sizeof(double) * std::max<int64_t>(o.nnz, 1)) != hipSuccess))
     rc = AMG_ENOMEM;
   if (rc == AMG_OK && hipMemsetAsync(cnt, 0, sizeof(int32_t) * (o.m + 1), s) != hipSuccess) rc = AMG_EHIP;
   if (rc == AMG_OK) {
@@ -514,33 +670,20 @@ int transpose(hipStream_t s, const Csr& a, Csr* t) {
     if (hipGetLastError() != hipSuccess) rc = AMG_EHIP;
   }
   if (rc == AMG_OK) {
-    // the rows longer than kShortRow, listed on the host from the row pointers
-    std::vector<int32_t> hp(o.m + 1);
-    std::vector<int32_t> longrows;
-    if (hipMemcpyAsync(hp.data(), o.ptr, sizeof(int32_t) * (o.m + 1), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) {
+    // the rows longer than kShortRow (the fill counters are done with: the list takes their place)
+    int32_t nlong = 0;
+    if (hipMemsetAsync(cnt + o.m, 0, sizeof(int32_t), s) != hipSuccess) rc = AMG_EHIP;
+    hipLaunchKernelGGL(k_long_rows, dim3(grid_for(o.m)), dim3(kBlock), 0, s, o.m, o.ptr, cnt, cnt + o.m);
+    if (hipMemcpyAsync(&nlong, cnt + o.m, sizeof(nlong), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
       rc = AMG_EHIP;
-    } else {
-      for (int64_t i = 0; i < o.m; ++i)
-        if (hp[i + 1] - hp[i] > kShortRow) longrows.push_back((int32_t)i);
-    }
-    if (rc == AMG_OK && !longrows.empty()) {
-      int32_t* drows = nullptr;
-      if (hipMalloc(&drows, sizeof(int32_t) * longrows.size()) != hipSuccess) {
-        rc = AMG_ENOMEM;
-      } else {
-        if (hipMemcpyAsync(drows, longrows.data(), sizeof(int32_t) * longrows.size(), hipMemcpyHostToDevice, s) !=
-            hipSuccess)
-          rc = AMG_EHIP;
-        if (rc == AMG_OK)
-          hipLaunchKernelGGL(k_row_sort_long, dim3((unsigned)longrows.size()), dim3(kWave), 0, s, drows, o.ptr, o.col,
-                             o.val);
-        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) rc = AMG_EHIP;
-        hipFree(drows);
-      }
+    if (rc == AMG_OK && nlong > 0) {
+      hipLaunchKernelGGL(k_row_sort_long, dim3((unsigned)nlong), dim3(kWave), 0, s, (const int32_t*)cnt, o.ptr, o.col,
+                         o.val);
+      if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) rc = AMG_EHIP;
     }
   }
-  hipFree(cnt);
+  dev_free(cnt);
   if (rc != AMG_OK) {
     free_csr(o);
     return rc;
@@ -549,13 +692,71 @@ int transpose(hipStream_t s, const Csr& a, Csr* t) {
   return AMG_OK;
 }
 
+int children_transpose(hipStream_t s, int64_t n, int64_t nc, const int32_t* children, Csr* PT) {
+  Csr o;
+  o.m = nc;
+  o.ncols = n;
+  o.nnz = n;
+  if (temp_malloc(&o.ptr, sizeof(int32_t) * (nc + 1)) != hipSuccess ||
+      temp_malloc(&o.col, sizeof(int32_t) * n) != hipSuccess || temp_malloc(&o.val, sizeof(double) * n) != hipSuccess) {
+    free_csr(o);
+    return AMG_ENOMEM;
+  }
+  hipLaunchKernelGGL(k_children_count, dim3(grid_for(nc)), dim3(kBlock), 0, s, nc, children, o.ptr);
+  int rc = AMG_OK;
+  scan_ptr(s, nc, o.ptr, o.ptr, &rc);
+  if (rc == AMG_OK) {
+    hipLaunchKernelGGL(k_children_rows, dim3(grid_for(nc * kMaxChildren)), dim3(kBlock), 0, s, nc, children, o.ptr,
+                       o.col, o.val);
+    if (hipGetLastError() != hipSuccess) rc = AMG_EHIP;
+  }
+  if (rc != AMG_OK) {
+    free_csr(o);
+    return rc;
+  }
+  *PT = o;
+  return AMG_OK;
+}
+
+int galerkin_from_restriction(hipStream_t s, const Csr& R, const int32_t* agg, Csr* Ac) {
+  const int64_t nc = R.m;
+  Csr o;
+  o.m = nc;
+  o.ncols = nc;
+  graph::DevBuf<int32_t> cnt;
+  AMGP_TRY(cnt.alloc(nc + 1));
+  int rc = AMG_OK;
+  hipLaunchKernelGGL(k_row_lengths, dim3(grid_for(nc)), dim3(kBlock), 0, s, nc, R.ptr, cnt.p);
+  const int64_t longest = max_count(s, nc, cnt.p, cnt.p + nc, &rc);
+  if (rc != AMG_OK) return rc;
+  if (longest > kWave) return AMG_EINVAL;
+  const dim3 grid(grid_for(nc * kWave)), block(kBlock);
+  if (temp_malloc(&o.ptr, sizeof(int32_t) * (nc + 1)) != hipSuccess) return AMG_ENOMEM;
+  hipLaunchKernelGGL(k_galerkin_rows<false>, grid, block, 0, s, nc, R.ptr, R.col, R.val, agg, o.ptr, nullptr, nullptr);
+  o.nnz = scan_ptr(s, nc, o.ptr, o.ptr, &rc);
+  if (rc == AMG_OK && (temp_malloc(&o.col, sizeof(int32_t) * std::max<int64_t>(o.nnz, 1)) != hipSuccess ||
+                       temp_malloc(&o.val, sizeof(double) * std::max<int64_t>(o.nnz, 1)) != hipSuccess))
+    rc = AMG_ENOMEM;
+  if (rc == AMG_OK) {
+    hipLaunchKernelGGL(k_galerkin_rows<true>, grid, block, 0, s, nc, R.ptr, R.col, R.val, agg, o.ptr, o.col, o.val);
+    if (hipGetLastError() != hipSuccess) rc = AMG_EHIP;
+  }
+  if (rc != AMG_OK) {
+    hipStreamSynchronize(s);
+    free_csr(o);
+    return rc;
+  }
+  *Ac = o;
+  return AMG_OK;
+}
+
 int tentative_prolongator(hipStream_t s, int64_t n, int64_t nc, const int32_t* agg, Csr* P) {
   Csr o;
   o.m = n;
   o.ncols = nc;
   o.nnz = n;
-  if (hipMalloc(&o.ptr, sizeof(int32_t) * (n + 1)) != hipSuccess ||
-      hipMalloc(&o.col, sizeof(int32_t) * n) != hipSuccess || hipMalloc(&o.val, sizeof(double) * n) != hipSuccess) {
+  if (temp_malloc(&o.ptr, sizeof(int32_t) * (n + 1)) != hipSuccess ||
+      temp_malloc(&o.col, sizeof(int32_t) * n) != hipSuccess || temp_malloc(&o.val, sizeof(double) * n) != hipSuccess) {
     free_csr(o);
     return AMG_ENOMEM;
   }
@@ -576,8 +777,8 @@ int smoothed_prolongator(hipStream_t s, const Csr& A, int nbatch, const Csr& Ph,
   double* diag = nullptr;
   unsigned long long* lam = nullptr;
   double* om = nullptr;
-  if (hipMalloc(&diag, sizeof(double) * n) != hipSuccess || hipMalloc(&lam, sizeof(unsigned long long) * nbatch) !=
-      hipSuccess || hipMalloc(&om, sizeof(double) * nbatch) != hipSuccess)
+  if (temp_malloc(&diag, sizeof(double) * n) != hipSuccess || temp_malloc(&lam, sizeof(unsigned long long) * nbatch) !=
+      hipSuccess || temp_malloc(&om, sizeof(double) * nbatch) != hipSuccess)
     rc = AMG_ENOMEM;
   std::vector<double> hl(nbatch), ho(nbatch);
   if (rc == AMG_OK && hipMemsetAsync(lam, 0, sizeof(unsigned long long) * nbatch, s) != hipSuccess) rc = AMG_EHIP;
@@ -598,9 +799,9 @@ int smoothed_prolongator(hipStream_t s, const Csr& A, int nbatch, const Csr& Ph,
                        Ph.val, diag, om);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) rc = AMG_EHIP;
   }
-  hipFree(diag);
-  hipFree(lam);
-  hipFree(om);
+  dev_free(diag);
+  dev_free(lam);
+  dev_free(om);
   if (rc == AMG_OK) rc = drop_small(s, &AP, kDropTau);
   if (rc != AMG_OK) {
     free_csr(AP);

@@ -180,18 +180,18 @@ int matching_step(hipStream_t s, const Csr& A, const double* w, Csr* P, double**
   o.ncols = nc;
   o.nnz = n;
   double* wcn = nullptr;
-  if (hipMalloc(&o.ptr, sizeof(int32_t) * (n + 1)) != hipSuccess || hipMalloc(&o.col, sizeof(int32_t) * n) !=
-      hipSuccess || hipMalloc(&o.val, sizeof(double) * n) != hipSuccess ||
-      hipMalloc(&wcn, sizeof(double) * std::max<int64_t>(nc, 1)) != hipSuccess) {
+  if (temp_malloc(&o.ptr, sizeof(int32_t) * (n + 1)) != hipSuccess || temp_malloc(&o.col, sizeof(int32_t) * n) !=
+      hipSuccess || temp_malloc(&o.val, sizeof(double) * n) != hipSuccess ||
+      temp_malloc(&wcn, sizeof(double) * std::max<int64_t>(nc, 1)) != hipSuccess) {
     free_csr(o);
-    hipFree(wcn);
+    dev_free(wcn);
     return AMG_ENOMEM;
   }
   hipLaunchKernelGGL(k_match_prol, dim3(grid_for(n + 1)), dim3(kBlock), 0, s, n, mate.p, rank.p, w, o.ptr, o.col,
                      o.val, wcn);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
     free_csr(o);
-    hipFree(wcn);
+    dev_free(wcn);
     return AMG_EHIP;
   }
   *P = o;
@@ -205,7 +205,7 @@ int matching_prolongator(hipStream_t s, const Csr& A, const double* w0, int step
                          int* flag) {
   const int64_t n = A.m;
   double* w = nullptr;
-  if (hipMalloc(&w, sizeof(double) * n) != hipSuccess) return AMG_ENOMEM;
+  if (temp_malloc(&w, sizeof(double) * n) != hipSuccess) return AMG_ENOMEM;
   if (w0)
     AMGP_HIP(hipMemcpyAsync(w, w0, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
   else
@@ -218,7 +218,7 @@ int matching_prolongator(hipStream_t s, const Csr& A, const double* w0, int step
     double* wc = nullptr;
     rc = matching_step(s, *Aview, w, &Ps.c, &wc, flag);
     if (rc != AMG_OK) break;
-    hipFree(w);
+    dev_free(w);
     w = wc;
     if (P.c.ptr == nullptr) {
       P.c = Ps.c;
@@ -240,7 +240,7 @@ int matching_prolongator(hipStream_t s, const Csr& A, const double* w0, int step
     if (Acur.c.m <= 1) break;
   }
   if (rc != AMG_OK) {
-    hipFree(w);
+    dev_free(w);
     return rc;
   }
   *Phat = P.c;

@@ -36,7 +36,7 @@ struct Prec<float> {
 template <typename T>
 int dalloc(T** p, int64_t count) {
   if (count < 1) count = 1;
-  if (hipMalloc((void**)p, sizeof(T) * (size_t)count) != hipSuccess) {
+  if (keep_malloc(p, sizeof(T) * (size_t)count) != hipSuccess) {
     *p = nullptr;
     return AMG_ENOMEM;
   }
@@ -46,13 +46,13 @@ int dalloc(T** p, int64_t count) {
 template <typename T>
 void free_vecs(Vecs<T>& v, bool own_bx) {
   if (own_bx) {
-    hipFree(v.b);
-    hipFree(v.x);
+    dev_free(v.b);
+    dev_free(v.x);
   }
-  hipFree(v.r);
-  hipFree(v.g0);
-  hipFree(v.g1);
-  hipFree(v.minv);
+  dev_free(v.r);
+  dev_free(v.g0);
+  dev_free(v.g1);
+  dev_free(v.minv);
   v = Vecs<T>();
 }
 
@@ -68,22 +68,23 @@ void drop_graphs(Handle* h) {
 
 // Free everything the handle owns (the Handle object itself stays).
 void release(Handle* h) {
+  MemoryScope scope(&h->arena);
   drop_graphs(h);
   if (h->cap) hipStreamDestroy(h->cap);
   for (size_t l = 0; l < h->lv.size(); ++l) {
     Level& L = h->lv[l];
     if (!L.csr_borrowed) {
-      hipFree(L.csr_ptr);
-      hipFree(L.csr_col);
-      hipFree(L.csr_val);
+      dev_free(L.csr_ptr);
+      dev_free(L.csr_col);
+      dev_free(L.csr_val);
     }
     free_ell(L.A64);
     free_ell(L.A32);
     free_vecs(L.v64, l > 0);
     free_vecs(L.v32, true);
-    hipFree(L.agg);
-    hipFree(L.children);
-    hipFree(L.wsmooth);
+    dev_free(L.agg);
+    dev_free(L.children);
+    dev_free(L.wsmooth);
     free_ell(L.P64);
     free_ell(L.PT64);
     free_ell(L.P32);
@@ -91,27 +92,28 @@ void release(Handle* h) {
     free_ell(L.R64);
     free_ell(L.R32);
   }
-  hipFree(h->ainv);
-  hipFree(h->cpart);
-  hipFree(h->partial);
-  hipFree(h->scal);
-  hipFree(h->dflag);
+  dev_free(h->ainv);
+  dev_free(h->cpart);
+  dev_free(h->partial);
+  dev_free(h->scal);
+  dev_free(h->dflag);
   if (h->hscal) hipHostFree(h->hscal);
   if (h->hpub) hipHostFree(h->hpub);
   if (h->ev) hipEventDestroy(h->ev);
-  hipFree(h->cg_r);
-  hipFree(h->cg_z);
-  hipFree(h->cg_p);
-  hipFree(h->cg_p2);
-  hipFree(h->cg_q);
-  hipFree(h->cg_rold);
-  hipFree(h->cg_u);
+  dev_free(h->cg_r);
+  dev_free(h->cg_z);
+  dev_free(h->cg_p);
+  dev_free(h->cg_p2);
+  dev_free(h->cg_q);
+  dev_free(h->cg_rold);
+  dev_free(h->cg_u);
   free_adj(h->adj64);
   free_adj(h->adj32);
-  hipFree(h->tr_buf);
-  hipFree(h->tr_sq);
-  hipFree(h->tr_loss);
-  hipFree(h->tr_partial);
+  dev_free(h->tr_buf);
+  dev_free(h->tr_sq);
+  dev_free(h->tr_loss);
+  dev_free(h->tr_partial);
+  h->arena.release();
   *h = Handle();
 }
 
@@ -443,12 +445,12 @@ int alloc_adj(Handle* h, std::vector<AdjVecs<T>>& adj) {
 template <typename T>
 void free_adj(std::vector<AdjVecs<T>>& adj) {
   for (auto& a : adj) {
-    hipFree(a.u);
-    hipFree(a.xmid);
-    hipFree(a.xpre);
-    hipFree(a.res);
-    hipFree(a.xin);
-    hipFree(a.bout);
+    dev_free(a.u);
+    dev_free(a.xmid);
+    dev_free(a.xpre);
+    dev_free(a.res);
+    dev_free(a.xin);
+    dev_free(a.bout);
   }
   adj.clear();
 }
@@ -456,10 +458,10 @@ void free_adj(std::vector<AdjVecs<T>>& adj) {
 void train_release(Handle* h) {
   free_adj(h->adj64);
   free_adj(h->adj32);
-  hipFree(h->tr_buf);
-  hipFree(h->tr_sq);
-  hipFree(h->tr_loss);
-  hipFree(h->tr_partial);
+  dev_free(h->tr_buf);
+  dev_free(h->tr_sq);
+  dev_free(h->tr_loss);
+  dev_free(h->tr_partial);
   h->tr_buf = nullptr;
   h->tr_sq = nullptr;
   h->tr_loss = nullptr;
@@ -682,23 +684,39 @@ int general_level(Handle* h, hipStream_t s, Level& L, Level* C, Csr* Phat) {
   return AMG_OK;
 }
 
-// R = P^T A for the 2x2x2 box P of level L (the restriction of k_restrict_product), in slices
-// aligned on each aggregate's first row, whatever their padding (small ragged levels pad more
-// than 10%, but one pass over R still costs less than the residual's pass over A).  Left empty
-// (the residual and the sum over children are used instead) when a slice has more than 64
-// offsets.
-int restriction_product(Handle* h, hipStream_t s, Level& L) {
-  CsrHold Ph, PhT, R;
-  AMGP_TRY(tentative_prolongator(s, L.n, L.nc, L.agg, &Ph.c));
-  AMGP_TRY(transpose(s, Ph.c, &PhT.c));
-  AMGP_TRY(spgemm(s, PhT.c, level_csr(L), &R.c, h->dflag));
-  const int rc =
-      build_ell_aligned(s, L.nc, R.c.ptr, R.c.col, R.c.val, &L.R64, L.children, kMaxChildren, L.n, true);
+// Level L -> C for the 2x2x2 box P: R = P^T A, A_c = R P, and R in slices aligned on each
+// aggregate's first row (the restriction of k_restrict_product), whatever their padding (small
+// ragged levels pad more than 10%, but one pass over R still costs less than the residual's pass
+// over A).  R is left empty (the residual and the sum over children are used instead) when a slice
+// has more than 64 offsets.
+int box_level(Handle* h, hipStream_t s, Level& L, Level* C) {
+  CsrHold PT, R, Ac;
+  AMGP_TRY(children_transpose(s, L.n, L.nc, L.children, &PT.c));
+  AMGP_TRY(spgemm(s, PT.c, level_csr(L), &R.c, h->dflag));
+  int rc = galerkin_from_restriction(s, R.c, L.agg, &Ac.c);
+  if (rc == AMG_EINVAL) {
+    // rows of R beyond a wavefront: the product from the fine rows (at most 64 distinct columns)
+    Ac.c.m = Ac.c.ncols = L.nc;
+    AMGP_TRY(galerkin(s, L.n, L.csr_ptr, L.csr_col, L.csr_val, L.agg, L.nc, L.children, &Ac.c.ptr, &Ac.c.col, &Ac.c.val,
+                      &Ac.c.nnz, h->dflag));
+    // entries of the product that are exactly zero are not stored, as in a general sparse
+    // product: couplings carried only by zero stencil entries (the Q1 face entries between
+    // aggregates one cell wide in two directions)
+    rc = drop_small(s, &Ac.c, 0.0);
+  }
+  AMGP_TRY(rc);
+  C->csr_ptr = Ac.c.ptr;
+  C->csr_col = Ac.c.col;
+  C->csr_val = Ac.c.val;
+  C->nnz = Ac.c.nnz;
+  Ac.c = Csr();  // now owned by the level
+  rc = build_ell_aligned(s, L.nc, R.c.ptr, R.c.col, R.c.val, &L.R64, L.children, kMaxChildren, L.n, true);
   return rc == AMG_EINVAL ? AMG_OK : rc;
 }
 
 int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col, const double* val,
           const amg_opts* o, hipStream_t s) {
+  MemoryScope scope(&h->arena);
   h->nbatch = o->nbatch > 0 ? o->nbatch : 1;
   h->max_coarse = o->max_coarse > 0 ? o->max_coarse : 4096;
   h->precision = o->precision;
@@ -757,7 +775,7 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
       AMGP_TRY(matching_prolongator(s, level_csr(L), L.wsmooth, h->match_steps, &Ph.c, &wnext, h->dflag));
       const int64_t nc = Ph.c.ncols;
       if (nc >= L.n) {
-        hipFree(wnext);
+        dev_free(wnext);
         break;
       }
       // the composite tentative prolongator has one entry per row: its column is the row's aggregate
@@ -809,24 +827,7 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
     C.ny = cy;
     C.nz = cz;
     if (!L.general) {
-      int rc = galerkin(s, L.n, L.csr_ptr, L.csr_col, L.csr_val, L.agg, nc, L.children, &C.csr_ptr, &C.csr_col,
-                        &C.csr_val, &C.nnz, h->dflag);
-      // entries of the product that are exactly zero are not stored, as in a general sparse
-      // product: couplings carried only by zero stencil entries (the Q1 face entries between
-      // aggregates one cell wide in two directions)
-      Csr cc;
-      cc.m = nc;
-      cc.ncols = nc;
-      cc.nnz = C.nnz;
-      cc.ptr = C.csr_ptr;
-      cc.col = C.csr_col;
-      cc.val = C.csr_val;
-      if (rc == AMG_OK) rc = drop_small(s, &cc, 0.0);
-      C.csr_ptr = cc.ptr;
-      C.csr_col = cc.col;
-      C.csr_val = cc.val;
-      C.nnz = cc.nnz;
-      if (rc == AMG_OK) rc = restriction_product(h, s, L);
+      const int rc = box_level(h, s, L, &C);
       if (rc != AMG_OK) {
         h->lv.push_back(C);  // owned by the handle from here on, also on error
         return rc;
@@ -844,11 +845,11 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
     h->ncp = (h->ncl + kDenseTile - 1) / kDenseTile * kDenseTile;
     AMGP_TRY(dalloc(&h->cpart, (int64_t)h->nbatch * (h->ncp / kDenseTile) * (h->ncp / kDenseTile) * kDenseTile));
     double* dense = nullptr;
-    AMGP_TRY(dalloc(&dense, (int64_t)h->nbatch * h->ncp * h->ncp));
+    if (temp_malloc(&dense, sizeof(double) * h->nbatch * h->ncp * h->ncp) != hipSuccess) return AMG_ENOMEM;
     int rc = launch_to_dense(s, h->nbatch, h->ncl, h->ncp, L.csr_ptr, L.csr_col, L.csr_val, dense, h->dflag);
     if (rc == AMG_OK) rc = dense_spd_inverse(s, h->nbatch, h->ncp, dense, &h->ainv, h->dflag);
     if (rc == AMG_OK && hipStreamSynchronize(s) != hipSuccess) rc = AMG_EHIP;
-    hipFree(dense);
+    dev_free(dense);
     if (rc != AMG_OK) return rc;
     int fl[F_NFLAG];
     AMGP_TRY(read_flags(h, s, fl));

@@ -56,6 +56,20 @@ enum SliceKind {
   SLICE_FULL = 2,    // every lane holds every step
   SLICE_TRIPLES = 4  // (with one of the two) the steps are triples of consecutive offsets, the rows consecutive
 };
+// Mirrored diagonals (large symmetric stencil matrices of varying coefficients): when the whole
+// matrix uses few offsets (7 or 27 of a stencil) and a_ij and a_ji are the same bits, only the entries of
+// offset >= 0 are stored, one array of `stride` values per offset behind `pad` zeros, and the entry
+// of row i at offset -o is read from row i - o of the array of o, which the same pass has read or
+// is about to read.  `mir` lists the steps in ascending offset: the offset and where its values lie
+// (row i's at val[voff + i]).  A 7-point row costs 4 values of memory traffic instead of 7; the
+// values and their order are those of the dense slices, so results are the same bits.  `doff` holds,
+// per 64-row slice, a bit for every step that its rows use (the steps of its dense form).
+struct MirrorStep {
+  int64_t voff;
+  int32_t off, unused;
+};
+constexpr int kMirrorMaxSteps = 27;
+
 template <typename T>
 struct Ell {
   int64_t n = 0;
@@ -78,6 +92,8 @@ struct Ell {
   int64_t npat = 0;
   int64_t dense = 0;             // stored values (dense slices); padded counts all slices' steps
   int64_t patterned = 0;         // slices kept as patterns
+  MirrorStep* mir = nullptr;     // [nmir] steps of mirrored diagonals (null: none)
+  int nmir = 0;
 };
 
 // Per-problem smoother weights for stacked problems: the weight of row i is
@@ -98,7 +114,8 @@ struct Prol {
 };
 
 // What the kernels are given (small: the small levels' kernels are bound by their launches).  A
-// matrix with uniform slices has desc and the patterns in the places of sptr and col.
+// matrix with uniform slices has desc and the patterns in the places of sptr and col, one of
+// mirrored diagonals its steps in the place of sptr and their number in that of npat.
 template <typename T>
 struct EllView {
   const int32_t* __restrict__ sptr;
@@ -107,6 +124,7 @@ struct EllView {
   const int32_t* __restrict__ doff;
   int32_t last;  // columns - 1, the clamp of offset-aligned columns
   int32_t npat;
+  __host__ __device__ const MirrorStep* mir() const { return reinterpret_cast<const MirrorStep*>(sptr); }
   __host__ __device__ const int2* desc() const { return reinterpret_cast<const int2*>(sptr); }
   __host__ __device__ const unsigned long long* pmask() const {
     return reinterpret_cast<const unsigned long long*>(col);
@@ -121,6 +139,7 @@ inline EllView<T> view(const Ell<T>& e) {
   if (e.desc)
     return EllView<T>{reinterpret_cast<const int32_t*>(e.desc), reinterpret_cast<const int32_t*>(e.pat), e.val, e.doff,
                       last, (int32_t)e.npat};
+  if (e.mir) return EllView<T>{reinterpret_cast<const int32_t*>(e.mir), nullptr, e.val, e.doff, last, e.nmir};
   return EllView<T>{e.sptr, e.col, e.val, e.doff, last, 0};
 }
 

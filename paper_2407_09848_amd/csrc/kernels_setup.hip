@@ -1,6 +1,7 @@
 // Setup kernels: l1-Jacobi diagonal, CSR -> sliced ELL, box aggregation and the
 // Galerkin product A_c = P^T A P for a piecewise-constant P.
 #include <algorithm>
+#include <vector>
 
 #include <climits>
 
@@ -442,6 +443,105 @@ __global__ void k_ell_fill_aligned(int64_t n, int64_t nslices, const int32_t* __
   }
 }
 
+// Distinct offsets of all slices into table[kOffHash] (empty slots kOffEmpty), their number in *count.
+__global__ void k_union_offsets(int64_t nslices, const int32_t* __restrict__ offs, const int32_t* __restrict__ width,
+                                int32_t* __restrict__ table, int32_t* __restrict__ count) {
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t s = g / kSlice;
+  const int t = (int)(g % kSlice);
+  if (s >= nslices || t >= width[s]) return;
+  const int o = offs[s * kSlice + t];
+  unsigned h = off_slot(o);
+  for (int probe = 0; probe < kOffHash; ++probe) {
+    int old = __hip_atomic_load(&table[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (old == o) return;
+    if (old == kOffEmpty) {
+      if (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > kMirrorMaxSteps) return;
+      old = atomicCAS(&table[h], kOffEmpty, o);
+      if (old == kOffEmpty) {
+        atomicAdd(count, 1);
+        return;
+      }
+      if (old == o) return;
+    }
+    h = (h + 1) & (kOffHash - 1);
+  }
+}
+
+// bit t of present[s]: slice s has entries of offset sorted[t]
+__global__ void k_mirror_present(int64_t nslices, const int32_t* __restrict__ offs, const int32_t* __restrict__ width,
+                                 int w, const MirrorStep* __restrict__ steps, int32_t* __restrict__ present) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= nslices) return;
+  unsigned m = 0;
+  for (int k = 0, t = 0; k < width[s]; ++k) {  // both lists ascend
+    while (t < w && steps[t].off != offs[s * kSlice + k]) ++t;
+    if (t < w) m |= 1u << t;
+  }
+  present[s] = (int32_t)m;
+}
+
+__global__ void k_fill_int(int n, int32_t v, int32_t* __restrict__ x) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) x[i] = v;
+}
+
+// Mirrored diagonals: CHECK = false stores every entry of offset >= 0 (row i of array k at
+// val[k stride + pad + i], zeroed beforehand); CHECK = true compares every entry of negative offset
+// with the one it mirrors (differ[0] set on other bits) and counts the entries that are not +0 on
+// each side (differ[1], differ[2]), which agree when no entry lacks its mirror image.
+// Rows pass through LDS as in k_l1_diag.
+template <bool CHECK>
+__global__ __launch_bounds__(kBlock) void k_mirror(int64_t n, const int32_t* __restrict__ ptr,
+                                                   const int32_t* __restrict__ col, const double* __restrict__ cval,
+                                                   int nup, const int32_t* __restrict__ up, int64_t stride,
+                                                   int64_t pad, double* __restrict__ val,
+                                                   unsigned long long* __restrict__ differ) {
+  __shared__ int32_t scol[kRowChunk];
+  __shared__ double sval[kRowChunk];
+  __shared__ int32_t sup[kMirrorMaxSteps];
+  const int64_t i0 = (int64_t)blockIdx.x * kBlock, i = i0 + threadIdx.x;
+  const int64_t i1 = i0 + kBlock < n ? i0 + kBlock : n;
+  const int beg = ptr[i0], end = ptr[i1];
+  const int p = i < n ? ptr[i] : end, pe = i < n ? ptr[i + 1] : end;
+  if ((int)threadIdx.x < nup) sup[threadIdx.x] = up[threadIdx.x];
+  unsigned long long bad = 0, above = 0, below = 0;
+  for (int b = beg; b < end; b += kRowChunk) {
+    const int m = min(kRowChunk, end - b);
+    __syncthreads();
+    for (int e = threadIdx.x; e < m; e += kBlock) {
+      scol[e] = col[b + e];
+      sval[e] = cval[b + e];
+    }
+    __syncthreads();
+    for (int q = max(p, b); q < min(pe, b + m); ++q) {
+      const int c = scol[q - b], o = c - (int)i;
+      const unsigned long long bits = (unsigned long long)__double_as_longlong(sval[q - b]);
+      int k = 0;
+      while (k < nup && sup[k] != abs(o)) ++k;
+      if (k == nup) continue;  // cannot be: up lists every offset of the matrix
+      if (!CHECK && o >= 0) val[k * stride + pad + i] = sval[q - b];
+      if (CHECK && o > 0) above += bits != 0;
+      if (CHECK && o < 0) {
+        below += bits != 0;
+        bad |= bits != (unsigned long long)__double_as_longlong(val[k * stride + pad + c]);
+      }
+    }
+  }
+  if constexpr (CHECK) {
+    for (int off = 32; off > 0; off >>= 1) {
+      bad |= __shfl_xor(bad, off, kWave);
+      above += __shfl_xor(above, off, kWave);
+      below += __shfl_xor(below, off, kWave);
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+      if (bad) differ[0] = 1;
+      atomicAdd(&differ[1], above);
+      atomicAdd(&differ[2], below);
+    }
+  }
+}
+
 __global__ void k_round_f32(int64_t m, const double* __restrict__ a, float* __restrict__ b) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < m) b[i] = (float)a[i];
@@ -615,6 +715,80 @@ int launch_l1_diag(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* 
 // stay dense and the plain kernels, which have no pattern path, serve them faster.
 constexpr int64_t kUniformMaxRows = int64_t(1) << 28;  // 32-bit byte offsets of the full slices' gathers
 
+// Mirrored diagonals for the matrix of the given slices when it is large enough to be bound by its
+// bytes, its offsets are few and come in pairs, storing half of them takes at most 65% of the dense
+// slices' room (a wide pad or many rows at a boundary take more), and it is symmetric in every
+// bit; out->mir stays null otherwise.  Smaller levels are bound by latency, where the dense slices'
+// two steps per load win: with the 262144 rows of a 64^3 level mirrored its solve took 2.22 instead of
+// 2.13 ms.
+constexpr int64_t kMirrorMinRows = int64_t(1) << 19;
+
+static int build_mirror(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
+                        int64_t nslices, const int32_t* offs, const int32_t* width, int64_t aligned,
+                        Ell<double>* out) {
+  using graph::DevBuf;
+  DevBuf<int32_t> buf;  // table, count, upper offsets
+  DevBuf<unsigned long long> differ;
+  AMGP_TRY(buf.alloc(kOffHash + 1 + kMirrorMaxSteps));
+  AMGP_TRY(differ.alloc(3));
+  int32_t *table = buf.p, *count = table + kOffHash, *dup = count + 1;
+  hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(kOffHash), 0, s, kOffHash, kOffEmpty, table);
+  AMGP_HIP(hipMemsetAsync(count, 0, sizeof(int32_t), s));
+  hipLaunchKernelGGL(k_union_offsets, dim3(grid_for(nslices * kSlice)), dim3(kBlock), 0, s, nslices, offs, width, table,
+                     count);
+  int32_t h[kOffHash + 1];
+  AMGP_HIP(hipMemcpyAsync(h, table, sizeof(h), hipMemcpyDeviceToHost, s));
+  AMGP_HIP(hipStreamSynchronize(s));
+  const int w = h[kOffHash];
+  if (w > kMirrorMaxSteps || w % 2 == 0) return AMG_OK;
+  std::vector<int32_t> o;
+  for (int t = 0; t < kOffHash; ++t)
+    if (h[t] != kOffEmpty) o.push_back(h[t]);
+  std::sort(o.begin(), o.end());
+  if ((int)o.size() != w) return AMG_OK;
+  for (int t = 0; t < w; ++t)
+    if (o[t] != -o[w - 1 - t]) return AMG_OK;
+  const int nup = w / 2 + 1;
+  const int64_t pad = (o[w - 1] + 31) / 32 * 32, stride = (pad + n + 31) / 32 * 32;
+  if (nup * stride > aligned / 100 * 65) return AMG_OK;
+  std::vector<MirrorStep> st(w);
+  for (int t = 0; t < w; ++t) {
+    const int k = std::abs(t - w / 2);
+    st[t] = MirrorStep{k * stride + pad + std::min(o[t], 0), o[t], 0};
+  }
+  double* v = nullptr;
+  if (temp_malloc(&v, sizeof(double) * nup * stride) != hipSuccess) return AMG_ENOMEM;
+  unsigned long long d[3] = {1, 0, 0};
+  const int rc = [&]() -> int {
+    AMGP_HIP(hipMemsetAsync(v, 0, sizeof(double) * nup * stride, s));
+    AMGP_HIP(hipMemsetAsync(differ.p, 0, sizeof(d), s));
+    AMGP_HIP(hipMemcpyAsync(dup, o.data() + w / 2, sizeof(int32_t) * nup, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_mirror<false>, dim3(grid_for(n)), dim3(kBlock), 0, s, n, ptr, col, val, nup, dup, stride, pad,
+                       v, differ.p);
+    hipLaunchKernelGGL(k_mirror<true>, dim3(grid_for(n)), dim3(kBlock), 0, s, n, ptr, col, val, nup, dup, stride, pad,
+                       v, differ.p);
+    AMGP_HIP(hipMemcpyAsync(d, differ.p, sizeof(d), hipMemcpyDeviceToHost, s));
+    AMGP_HIP(hipStreamSynchronize(s));
+    if (d[0] || d[1] != d[2]) return AMG_OK;
+    MirrorStep* m = nullptr;
+    if (keep_malloc(&m, sizeof(MirrorStep) * w) != hipSuccess ||
+        keep_malloc(&out->doff, sizeof(int32_t) * nslices) != hipSuccess)
+      return AMG_ENOMEM;
+    AMGP_HIP(hipMemcpyAsync(m, st.data(), sizeof(MirrorStep) * w, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_mirror_present, dim3(grid_for(nslices)), dim3(kBlock), 0, s, nslices, offs, width, w,
+                       (const MirrorStep*)m, out->doff);
+    AMGP_HIP(hipGetLastError());
+    AMGP_HIP(hipStreamSynchronize(s));
+    out->mir = m;
+    out->nmir = w;
+    out->val = v;
+    out->dense = nup * stride;
+    return AMG_OK;
+  }();
+  if (!out->mir) dev_free(v);
+  return rc;
+}
+
 // Offset-aligned sliced ELL (one row per lane) when every slice has at most 64 distinct column
 // offsets and the layout is at most 10% larger than the packed one; AMG_EINVAL otherwise.
 int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
@@ -688,6 +862,10 @@ int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_
       AMGP_HIP(hipGetLastError());
       AMGP_HIP(hipStreamSynchronize(s));  // tab leaves scope
     } else {
+      if (!anchor && e.ncols == n && n >= kMirrorMinRows && n < kUniformMaxRows) {
+        AMGP_TRY(build_mirror(s, n, ptr, col, val, nslices, offs, wd, aligned, &e));
+        if (e.mir) return AMG_OK;
+      }
       e.dense = aligned;
       if (keep_malloc(&e.sptr, sizeof(int32_t) * (nslices + 1)) != hipSuccess) return AMG_ENOMEM;
       int rc2 = AMG_OK;
@@ -777,6 +955,7 @@ int build_ell32(hipStream_t s, const Ell<double>& a, Ell<float>* out) {
   e.npat = a.npat;
   e.dense = a.dense;
   e.patterned = a.patterned;
+  e.nmir = a.nmir;
   const int64_t stored = a.doff ? a.dense : a.padded;
   auto copy = [&](auto** to, const auto* from, int64_t count) -> int {
     if (!from) return AMG_OK;
@@ -787,7 +966,8 @@ int build_ell32(hipStream_t s, const Ell<double>& a, Ell<float>* out) {
   const int rc = [&]() -> int {
     AMGP_TRY(copy(&e.sptr, a.sptr, e.nslices + 1));
     AMGP_TRY(copy(&e.col, a.col, stored));
-    AMGP_TRY(copy(&e.doff, a.doff, stored / kSlice));
+    AMGP_TRY(copy(&e.doff, a.doff, a.mir ? a.nslices : stored / kSlice));
+    AMGP_TRY(copy(&e.mir, a.mir, a.nmir));
     AMGP_TRY(copy(&e.desc, a.desc, e.nslices));
     AMGP_TRY(copy(&e.pat, a.pat, (20 * e.npat + 7) / 8));
     if (keep_malloc(&e.val, sizeof(float) * std::max<int64_t>(stored, 1)) != hipSuccess) return AMG_ENOMEM;
@@ -797,10 +977,10 @@ int build_ell32(hipStream_t s, const Ell<double>& a, Ell<float>* out) {
       hipLaunchKernelGGL(k_round_f32, dim3(grid_for(e.npat)), dim3(kBlock), 0, s, e.npat, av.pval(),
                          const_cast<float*>(ev.pval()));
     }
-    if (a.doff && stored > 0)
+    if (a.doff && !a.mir && stored > 0)
       hipLaunchKernelGGL(k_round_f32_aligned, dim3(grid_for(e.nslices * kSlice)), dim3(kBlock), 0, s, e.nslices,
                          e.sptr, e.desc, a.val, e.val);
-    else if (!a.doff)
+    else if (!a.doff || a.mir)
       hipLaunchKernelGGL(k_round_f32, dim3(grid_for(stored)), dim3(kBlock), 0, s, stored, a.val, e.val);
     AMGP_HIP(hipGetLastError());
     return AMG_OK;
@@ -822,6 +1002,7 @@ static void free_ell_of(Ell<T>& e) {
   dev_free(e.doff);
   dev_free(e.desc);
   dev_free(e.pat);
+  dev_free(e.mir);
   e = Ell<T>();
 }
 void free_ell(Ell<double>& e) { free_ell_of(e); }

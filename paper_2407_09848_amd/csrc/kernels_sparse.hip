@@ -83,10 +83,11 @@ __device__ __forceinline__ void st(T* p, T v) {
 // The row's l1 inverse diagonal, read by every step of a level: an ordinary load on wide
 // (27-point) FP64 levels and on FP32 levels, a nontemporal one on the other streaming FP64
 // levels.  Measured: 320^3 27-point solve 482.5 -> 480.5 ms, the 256^3 diffusion solve with the
-// FP32 hierarchy 61.2 -> 60.7 ms; on the 7-point FP64 level ordinary loads cost 5% (294 -> 310 us).
+// FP32 hierarchy 61.2 -> 60.7 ms; on the 7-point FP64 level ordinary loads cost 5% (294 -> 310 us;
+// with mirrored diagonals 3% of five steps on 6.5M rows, 515 -> 530 us).
 template <bool NT, int V, typename T>
 __device__ __forceinline__ T ld_minv(const T* p) {
-  if constexpr (V != 0 || std::is_same_v<T, float>) return *p; else return ld<NT>(p);
+  if constexpr ((V != 0 && V != 3) || std::is_same_v<T, float>) return *p; else return ld<NT>(p);
 }
 
 // Offset-aligned slices keep each lane's steps in pairs: steps 2q and 2q + 1 of lane l sit at
@@ -282,7 +283,7 @@ struct GatherVec {
 };
 // Kernel variants of the one-row-per-lane levels: narrow and wide dense slices (kWideBatch), and
 // levels with uniform slices, whose kernels also request the row's own vectors first.
-enum Variant { V_NARROW = 0, V_WIDE = 1, V_UNIFORM = 2 };
+enum Variant { V_NARROW = 0, V_WIDE = 1, V_UNIFORM = 2, V_MIRROR = 3 };
 
 // The value of the lane below (DPP wave_shr) or above (wave_shl); the lane at the end, which has no
 // such neighbour, keeps `end`.
@@ -373,9 +374,50 @@ __device__ __forceinline__ T pattern_triples_sum(EllView<T> A, int beg, int w, i
   return acc;
 }
 
+// The sum over mirrored diagonals: per step a coalesced load of the values at the row (or at the row
+// the entry mirrors) and a gather, in ascending offset order.  `present` has a bit for each step that
+// the slice's rows use at all; the others are left out as in the dense slices, where a stacked
+// problem's rows never meet the entries of its neighbour.  WHOLE: all steps, every column in range.
+// The values take ordinary loads: the rows that mirror them read them again from the caches (with
+// nontemporal ones the 256^3 FP64 solve went from 87.8 back to 90.1 ms).  Against dense slices:
+// 32 x 64^3 FP32 training step 7.33 -> 6.19 ms, 256^3 solve with the FP32 hierarchy 58.9 -> 52.7 ms, FP64
+// 90.4 -> 87.8 ms, degree-5 application on 203x187x171 rows 544 -> 515 us.
+constexpr int kMirrorBatch = 7;
+template <bool WHOLE, typename T, typename Gf>
+__device__ __forceinline__ T mirror_steps(EllView<T> A, unsigned present, int r, Gf g) {
+  constexpr int B = kMirrorBatch;
+  const MirrorStep* st = A.mir();
+  const int w = A.npat;
+  T acc = T(0);
+  for (int t = 0; t < w; t += B) {
+    T gv[B], v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int q = min(t + u, w - 1);
+      v[u] = GatherVec<T>::at_row(A.val + st[q].voff, r);
+      gv[u] = WHOLE ? g.at(st[q].off, r) : g(min(max(r + st[q].off, 0), A.last));
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u)
+      if (t + u < w && (WHOLE || (present >> (t + u)) & 1)) acc += v[u] * gv[u];
+  }
+  return acc;
+}
+
+template <typename T, typename Gf>
+__device__ __forceinline__ T mirror_sum(EllView<T> A, int s, int lane, int r, Gf g) {
+  const int r0 = __builtin_amdgcn_readfirstlane(r - lane);  // the wavefront's first row
+  const unsigned present = __builtin_amdgcn_readfirstlane(A.doff[s]);
+  const MirrorStep* st = A.mir();
+  if (present == (1u << A.npat) - 1 && r0 + st[0].off >= 0 && r0 + kWave - 1 <= A.last - st[A.npat - 1].off)
+    return mirror_steps<true>(A, present, r, g);
+  return mirror_steps<false>(A, present, r, g);
+}
+
 // The aligned sum of slice s for the row r (its anchor) on this lane; s is wave-uniform.
 template <bool NT, int V, typename T, typename Gf>
 __device__ __forceinline__ T slice_sum(EllView<T> A, int s, int lane, int r, Gf g) {
+  if constexpr (V == V_MIRROR) return mirror_sum(A, s, lane, r, g);
   int beg, end;
   const int32_t* off;
   if constexpr (V == V_UNIFORM) {
@@ -426,7 +468,7 @@ __device__ __forceinline__ T ell_dot(EllView<T> A, int64_t row, const T* __restr
   // every lane of the wavefront is in the same slice: read its bounds once, as scalars
   const int s = __builtin_amdgcn_readfirstlane((int)(row / R));
   // offset-aligned slice: the column is the row plus the step's (uniform) offset
-  if constexpr (V == V_UNIFORM) return slice_sum<NT, V>(A, s, (int)(row & 63), (int)row, GatherVec<T>{x});
+  if constexpr (V >= V_UNIFORM) return slice_sum<NT, V>(A, s, (int)(row & 63), (int)row, GatherVec<T>{x});
   if (G == 1 && A.doff) return slice_sum<NT, V>(A, s, (int)(row & 63), (int)row, GatherVec<T>{x});
   const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
   const int end = __builtin_amdgcn_readfirstlane(A.sptr[s + 1]);
@@ -654,7 +696,7 @@ __global__ __launch_bounds__(kBlock) void k_first2_zero(int64_t n, EllView<T> A,
   }
   T ag = T(0);
   const FirstDir<T, MODE, U> g1of{minv, b, u, c1};
-  if (V == V_UNIFORM || (G == 1 && A.doff)) {
+  if (V >= V_UNIFORM || (G == 1 && A.doff)) {
     ag = slice_sum<NT, V>(A, s, (int)(i & 63), (int)i, g1of);
   } else {
     const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
@@ -745,7 +787,7 @@ __device__ __forceinline__ T ell_dot_prol(EllView<T> A, int64_t row, const T* __
   const int s = __builtin_amdgcn_readfirstlane((int)(row / kSlice));
   const int lane = (int)(row & 63);
   const GatherProl<T> g{x, pr.agg, pr.xc};
-  if (V == V_UNIFORM || A.doff) return slice_sum<NT, V>(A, s, lane, (int)row, g);
+  if (V >= V_UNIFORM || A.doff) return slice_sum<NT, V>(A, s, lane, (int)row, g);
   const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
   const int end = __builtin_amdgcn_readfirstlane(A.sptr[s + 1]);
   T acc = T(0);
@@ -848,6 +890,12 @@ __device__ __forceinline__ T ell_dot_any(EllView<T> A, int row, const T* __restr
   int beg, end;
   const int32_t* off;
   T acc = T(0);
+  if constexpr (V == V_MIRROR) {
+    const MirrorStep* st = A.mir();
+    for (int t = 0; t < A.npat; ++t)
+      if ((A.doff[s] >> t) & 1) acc += A.val[st[t].voff + row] * x[min(max(row + st[t].off, 0), A.last)];
+    return acc;
+  }
   if constexpr (V == V_UNIFORM) {
     const int2 d = A.desc()[s];
     const int w = d.y >> 4;
@@ -866,7 +914,7 @@ __device__ __forceinline__ T ell_dot_any(EllView<T> A, int row, const T* __restr
     end = A.sptr[s + 1];
     off = A.doff + (beg >> 6);
   }
-  if (V == V_UNIFORM || A.doff) {
+  if (V >= V_UNIFORM || A.doff) {
     auto g = [&](int c) { return x[c]; };
     if constexpr (std::is_same_v<T, float>)
       return aligned_sum_f32<NT, decltype(g), false>(A.val, beg, end, row & 63, off, row, A.last, g);
@@ -1038,7 +1086,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_dot_p(int64_t n, EllView<double
     double pw = 0.0;
     if constexpr (PRE && V != V_NARROW) pw = pnew[i];  // the row's own entry first (see kWideBatch)
     double acc = 0.0;
-    if (V == V_UNIFORM || A.doff) {
+    if (V >= V_UNIFORM || A.doff) {
       acc = slice_sum<kStreamVal, V>(A, s, (int)(i & 63), (int)i, pj);
     } else {
       const int beg = __builtin_amdgcn_readfirstlane(A.sptr[s]);
@@ -1234,6 +1282,14 @@ void with_variant(const Ell<T>& A, bool nt, F&& f) {
   using Narrow = std::integral_constant<int, V_NARROW>;
   using Wide = std::integral_constant<int, V_WIDE>;
   using Uniform = std::integral_constant<int, V_UNIFORM>;
+  using Mirror = std::integral_constant<int, V_MIRROR>;
+  if (A.mir) {
+    if (nt)
+      f(std::true_type(), Mirror());
+    else
+      f(std::false_type(), Mirror());
+    return;
+  }
   if (A.desc) {
     if (nt)
       f(std::true_type(), Uniform());

@@ -1117,7 +1117,7 @@ int amg_level_patterns(const amg_handle* h, int level, int restriction, int64_t*
   const amgp::Level& L = h->impl.lv[level];
   if (restriction && (L.general || !L.R64.val)) return AMG_EINVAL;
   const amgp::Ell<double>& A = restriction ? L.R64 : L.A64;
-  if (h_values) *h_values = A.desc ? A.dense : A.padded;
+  if (h_values) *h_values = A.desc || A.mir ? A.dense : A.padded;
   if (h_slices) *h_slices = A.patterned;
   if (h_steps) *h_steps = A.npat;
   return AMG_OK;

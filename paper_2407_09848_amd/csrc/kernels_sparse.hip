@@ -46,13 +46,19 @@ inline unsigned xcd_grid(int64_t n) {
 // 1.1 GB per step: streaming it took the solve from 0.496 to 0.493 s).
 constexpr unsigned kRemapMaxBlocks = 12288;
 constexpr unsigned kXcdChunk = 128;
+// the kernels of two rows per lane (mirrored diagonals): 256^3 solve 79.1 ms with runs of 16 blocks (8192
+// rows), 80.1 with 32, 80.9 with 64
+constexpr unsigned kPairXcdChunk = 16;
 
+// RPL: rows per lane of the kernel (a block of two rows per lane covers 512 rows).
+template <int RPL = 1>
 __device__ __forceinline__ int64_t logical_block() {
-  if (gridDim.x > kRemapMaxBlocks) {
-    constexpr unsigned span = kXcd * kXcdChunk;
+  constexpr unsigned kChunk = RPL == 1 ? kXcdChunk : kPairXcdChunk;
+  if (gridDim.x > kRemapMaxBlocks / RPL) {
+    constexpr unsigned span = kXcd * kChunk;
     if (blockIdx.x >= gridDim.x - gridDim.x % span) return blockIdx.x;
     const unsigned x = blockIdx.x % kXcd, q = blockIdx.x / kXcd;
-    return (int64_t)(q / kXcdChunk) * span + x * kXcdChunk + q % kXcdChunk;
+    return (int64_t)(q / kChunk) * span + x * kChunk + q % kChunk;
   }
   const unsigned per = gridDim.x / kXcd;
   return (int64_t)(blockIdx.x % kXcd) * per + blockIdx.x / kXcd;
@@ -269,6 +275,22 @@ __device__ __forceinline__ double aligned_sum_f64(const double* __restrict__ val
   return acc;
 }
 
+// Two consecutive entries from row r of p on; the pair needs no wider alignment than one entry.
+template <typename T>
+struct V2 {
+  T x, y;
+};
+template <typename T>
+struct PairOf {
+  typedef T type __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+};
+template <typename T>
+__device__ __forceinline__ V2<T> at_row2(const T* p, int r) {
+  typedef typename PairOf<T>::type P;
+  const P v = *reinterpret_cast<const P*>(reinterpret_cast<const char*>(p) + (uint32_t)r * (uint32_t)sizeof(T));
+  return V2<T>{v.x, v.y};
+}
+
 // Gathers of the products: g(c) by column, g.at(off, r) at column r + off with a wave-uniform
 // offset known to be in range (the offset then goes into the scalar base address and the row into
 // a 32-bit byte offset, n < 2^28).
@@ -277,6 +299,7 @@ struct GatherVec {
   const T* __restrict__ x;
   __device__ __forceinline__ T operator()(int c) const { return x[c]; }
   __device__ __forceinline__ T at(int off, int r) const { return at_row(x + off, r); }
+  __device__ __forceinline__ auto at2(int off, int r) const { return at_row2(x + off, r); }
   static __device__ __forceinline__ T at_row(const T* p, int r) {
     return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (uint32_t)r * (uint32_t)sizeof(T));
   }
@@ -678,6 +701,15 @@ struct FirstDir {
     return dir(U ? GatherVec<T>::at_row(u + off, r)
                  : GatherVec<T>::at_row(minv + off, r) * GatherVec<T>::at_row(b + off, r));
   }
+  __device__ __forceinline__ V2<T> at2(int off, int r) const {
+    if constexpr (U) {
+      const V2<T> a = at_row2(u + off, r);
+      return V2<T>{dir(a.x), dir(a.y)};
+    } else {
+      const V2<T> m = at_row2(minv + off, r), v = at_row2(b + off, r);
+      return V2<T>{dir(m.x * v.x), dir(m.y * v.y)};
+    }
+  }
 };
 
 template <typename T, int MODE, bool STORE, bool NT, int G, int V = V_NARROW, bool U = false>
@@ -777,6 +809,11 @@ struct GatherProl {
   __device__ __forceinline__ T operator()(int c) const { return x[c] + xc[agg[c]]; }
   __device__ __forceinline__ T at(int off, int r) const {
     return GatherVec<T>::at_row(x + off, r) + xc[GatherVec<int32_t>::at_row(agg + off, r)];
+  }
+  __device__ __forceinline__ V2<T> at2(int off, int r) const {
+    const V2<T> v = at_row2(x + off, r);
+    const V2<int32_t> a = at_row2(agg + off, r);
+    return V2<T>{v.x + xc[a.x], v.y + xc[a.y]};
   }
 };
 
@@ -1056,6 +1093,12 @@ struct Direction {
     const double pr = GatherVec<double>::at_row(p + off, r);
     if constexpr (PRE) return pr; else return (double)GatherVec<TZ>::at_row(z + off, r) + beta * pr;
   }
+  __device__ __forceinline__ V2<double> at2(int off, int r) const {
+    const V2<double> v = at_row2(p + off, r);
+    if constexpr (PRE) return v;
+    const V2<TZ> a = at_row2(z + off, r);
+    return V2<double>{(double)a.x + beta * v.x, (double)a.y + beta * v.y};
+  }
 };
 
 // The CG direction update fused into the next SpMV: p_new = z + beta p_old and
@@ -1157,6 +1200,298 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t n, const double* _
   }
   const double s = block_sum(v);
   if (threadIdx.x == 0) partial[logical_block()] = s;
+}
+
+// ---------------------------------------------------------------------------
+// Two rows per lane, for the levels of mirrored diagonals: a wavefront serves 128 consecutive rows,
+// lane l the rows 2 l and 2 l + 1 of them, so that values, row vectors and gathers of a pair come with
+// one load of twice the width.  Every row's products keep their order; partial sums of dot
+// products cover 512 rows a block.
+// ---------------------------------------------------------------------------
+constexpr int kPair = 2;
+
+// rows r, r + 1 of p; WHOLE: both below n, else those that are not read as 0
+template <bool NT, bool WHOLE, typename T>
+__device__ __forceinline__ V2<T> ld_pair(const T* p, int64_t r, int64_t n) {
+  if constexpr (WHOLE) {
+    typedef typename PairOf<T>::type P;
+    const P* q = reinterpret_cast<const P*>(p + r);
+    const P v = NT ? __builtin_nontemporal_load(q) : *q;
+    return V2<T>{v.x, v.y};
+  }
+  return V2<T>{r < n ? p[r] : T(0), r + 1 < n ? p[r + 1] : T(0)};
+}
+template <bool NT, bool WHOLE, typename T>
+__device__ __forceinline__ void st_pair(T* p, int64_t r, int64_t n, V2<T> v) {
+  if constexpr (WHOLE) {
+    typedef typename PairOf<T>::type P;
+    const P w = {v.x, v.y};
+    P* q = reinterpret_cast<P*>(p + r);
+    if constexpr (NT) __builtin_nontemporal_store(w, q); else *q = w;
+    return;
+  }
+  if (r < n) p[r] = v.x;
+  if (r + 1 < n) p[r + 1] = v.y;
+}
+__device__ __forceinline__ int64_t pair_row() { return (logical_block<kPair>() * kBlock + threadIdx.x) * kPair; }
+
+// The pair (column c, c + 1) of a gather: at2 with a wave-uniform offset known to be in range, clamped
+// column by column otherwise.
+template <typename T, typename Gf>
+__device__ __forceinline__ V2<T> clamp2(const Gf& g, int c, int last) {
+  return V2<T>{g(min(max(c, 0), last)), g(min(max(c + 1, 0), last))};
+}
+
+template <bool WHOLE, typename T, typename Gf>
+__device__ __forceinline__ V2<T> mirror_pair_steps(EllView<T> A, unsigned present, int r, Gf g) {
+  constexpr int B = kMirrorBatch;
+  const MirrorStep* st = A.mir();
+  const int w = A.npat;
+  V2<T> acc{T(0), T(0)};
+  for (int t = 0; t < w; t += B) {
+    V2<T> gv[B], v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int q = min(t + u, w - 1);
+      v[u] = at_row2(A.val + st[q].voff, r);
+      gv[u] = WHOLE ? g.at2(st[q].off, r) : clamp2<T>(g, r + st[q].off, A.last);
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      if (t + u >= w) continue;
+      if (WHOLE || (present >> (t + u)) & 1) {
+        acc.x += v[u].x * gv[u].x;
+        acc.y += v[u].y * gv[u].y;
+      }
+    }
+  }
+  return acc;
+}
+
+// (A g)_r and (A g)_{r + 1} for the even row r of this lane
+template <typename T, typename Gf>
+__device__ __forceinline__ V2<T> pair_sum(EllView<T> A, int r, Gf g) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int r0 = __builtin_amdgcn_readfirstlane(r - kPair * lane);  // the wavefront's first row
+  const MirrorStep* st = A.mir();
+  const int s = r0 >> 6, s1 = min(s + 1, A.last >> 6);  // its two slices
+  const unsigned p0 = __builtin_amdgcn_readfirstlane(A.doff[s]), p1 = __builtin_amdgcn_readfirstlane(A.doff[s1]);
+  const unsigned all = (1u << A.npat) - 1;
+  if ((p0 & p1) == all && r0 + st[0].off >= 0 && r0 + kPair * kWave - 1 <= A.last - st[A.npat - 1].off)
+    return mirror_pair_steps<true>(A, all, r, g);
+  return mirror_pair_steps<false>(A, lane < kWave / 2 ? p0 : p1, r, g);
+}
+
+// f(WHOLE, row) for the lane's pair: WHOLE when all 128 rows of the wavefront are below n; wavefronts past
+// n do nothing.
+template <typename F>
+__device__ __forceinline__ void for_pair(int64_t n, F&& f) {
+  const int64_t r = pair_row();
+  const int64_t r0 = r - kPair * (int64_t)(threadIdx.x & (kWave - 1));
+  if (r0 + kPair * kWave <= n)
+    f(std::true_type(), r);
+  else if (r < n)
+    f(std::false_type(), r);
+}
+
+template <typename T, int MODE, bool STORE, bool NT, bool XUPD, bool WHOLE>
+__device__ __forceinline__ V2<T> pair_step(int64_t i, int64_t n, EllView<T> A, const T* __restrict__ minv,
+                                           const T* __restrict__ gold, T* __restrict__ gnew, const T* rin, T* rout,
+                                           T* __restrict__ x, T alpha, T c, T w, T wprev, Wt wv, Wt wpv, Prol<T> pr) {
+  const V2<T> mi = ld_pair<NT, WHOLE>(minv, i, n), go = ld_pair<false, WHOLE>(gold, i, n),
+              ri = ld_pair<NT, WHOLE>(rin, i, n);
+  V2<T> xi{T(0), T(0)};
+  if constexpr (XUPD) xi = ld_pair<NT, WHOLE>((const T*)x, i, n);
+  const V2<T> ag = pair_sum(A, (int)i, GatherVec<T>{gold});
+  V2<T> rn, gn, xn{T(0), T(0)};
+  rn.x = (MODE == 0) ? ri.x - ag.x : ri.x - mi.x * ag.x;
+  rn.y = (MODE == 0) ? ri.y - ag.y : ri.y - mi.y * ag.y;
+  gn.x = (MODE == 0) ? alpha * go.x + c * (mi.x * rn.x) : alpha * go.x + c * rn.x;
+  gn.y = (MODE == 0) ? alpha * go.y + c * (mi.y * rn.y) : alpha * go.y + c * rn.y;
+  if constexpr (XUPD) {
+    const T w0 = wsel(wv, w, i), w1 = wsel(wv, w, (i + 1 < n ? i + 1 : i));
+    const T p0 = wsel(wpv, wprev, i), p1 = wsel(wpv, wprev, (i + 1 < n ? i + 1 : i));
+    if (pr.agg) {
+      xi.x = xi.x + pr.xc[pr.agg[i]];
+      if (WHOLE || i + 1 < n) xi.y = xi.y + pr.xc[pr.agg[i + 1]];
+    }
+    xn.x = xi.x + p0 * go.x + w0 * gn.x;
+    xn.y = xi.y + p1 * go.y + w1 * gn.y;
+    st_pair<NT, WHOLE>(x, i, n, xn);
+  }
+  if constexpr (STORE) {
+    st_pair<NT, WHOLE>(rout, i, n, rn);
+    st_pair<false, WHOLE>(gnew, i, n, gn);
+  }
+  return xn;
+}
+
+template <typename T, int MODE, bool STORE, bool NT>
+__global__ __launch_bounds__(kBlock) void k_pair_fused(int64_t n, EllView<T> A, const T* __restrict__ minv,
+                                                       const T* __restrict__ gold, T* __restrict__ gnew, const T* rin,
+                                                       T* rout, T* __restrict__ x, T alpha, T c, T w, T wprev, Wt wv,
+                                                       Wt wpv, Prol<T> pr) {
+  for_pair(n, [&](auto whole, int64_t i) {
+    pair_step<T, MODE, STORE, NT, true, decltype(whole)::value>(i, n, A, minv, gold, gnew, rin, rout, x, alpha, c, w,
+                                                                wprev, wv, wpv, pr);
+  });
+}
+
+template <typename T, int MODE, bool NT>
+__global__ __launch_bounds__(kBlock) void k_pair_fused_keep_x(int64_t n, EllView<T> A, const T* __restrict__ minv,
+                                                              const T* __restrict__ gold, T* __restrict__ gnew,
+                                                              const T* rin, T* rout, T alpha, T c) {
+  for_pair(n, [&](auto whole, int64_t i) {
+    pair_step<T, MODE, true, NT, false, decltype(whole)::value>(i, n, A, minv, gold, gnew, rin, rout, nullptr, alpha, c,
+                                                                T(0), T(0), Wt(), Wt(), Prol<T>());
+  });
+}
+
+template <typename T, int MODE, bool NT>
+__global__ __launch_bounds__(kBlock) void k_pair_fused_dot(int64_t n, EllView<T> A, const T* __restrict__ minv,
+                                                           const T* __restrict__ gold, const T* rin,
+                                                           T* __restrict__ x, T alpha, T c, T w, T wprev, Wt wv,
+                                                           Wt wpv, Prol<T> pr, const double* __restrict__ dr,
+                                                           const double* __restrict__ drold,
+                                                           double* __restrict__ partial) {
+  double v = 0.0, u = 0.0;
+  for_pair(n, [&](auto whole, int64_t i) {
+    constexpr bool WHOLE = decltype(whole)::value;
+    const V2<T> xn = pair_step<T, MODE, false, NT, true, WHOLE>(i, n, A, minv, gold, nullptr, rin, nullptr, x, alpha, c,
+                                                                w, wprev, wv, wpv, pr);
+    const V2<double> d = ld_pair<NT, WHOLE>(dr, i, n);  // 0 past n
+    v = d.x * (double)xn.x + d.y * (double)xn.y;
+    if (drold) {
+      const V2<double> e = ld_pair<NT, WHOLE>(drold, i, n);
+      u = e.x * (double)xn.x + e.y * (double)xn.y;
+    }
+  });
+  const double sv = block_sum(v);
+  __syncthreads();
+  const double su = drold ? block_sum(u) : 0.0;
+  if (threadIdx.x == 0) {
+    partial[logical_block<kPair>()] = sv;
+    partial[gridDim.x + logical_block<kPair>()] = su;
+  }
+}
+
+template <typename T, int MODE, bool STORE, bool NT, bool U>
+__global__ __launch_bounds__(kBlock) void k_pair_first2_zero(int64_t n, EllView<T> A, const T* __restrict__ minv,
+                                                             const T* __restrict__ b, T* __restrict__ gnew,
+                                                             T* __restrict__ r, T* __restrict__ x, T c1, T alpha, T c,
+                                                             T w1, T w2, Wt w1v, Wt w2v, const T* __restrict__ u) {
+  for_pair(n, [&](auto whole, int64_t i) {
+    constexpr bool WHOLE = decltype(whole)::value;
+    const V2<T> mi = ld_pair<false, WHOLE>(minv, i, n), bi = ld_pair<false, WHOLE>(b, i, n);
+    const V2<T> ag = pair_sum(A, (int)i, FirstDir<T, MODE, U>{minv, b, u, c1});
+    auto row = [&](T m, T bb, T a, T u1, T u2, T& xo, T& ro, T& go) {
+      if (MODE == 0) {
+        const T g1 = c1 * (m * bb);
+        ro = bb - a;
+        go = alpha * g1 + c * (m * ro);
+        xo = u1 * g1 + u2 * go;
+      } else {
+        const T r0 = m * bb, g1 = r0 / c1;
+        ro = r0 - m * a;
+        go = alpha * g1 + c * ro;
+        xo = g1 + go;
+      }
+    };
+    const int64_t j = (i + 1 < n ? i + 1 : i);
+    V2<T> xn, rn, gn;
+    row(mi.x, bi.x, ag.x, wsel(w1v, w1, i), wsel(w2v, w2, i), xn.x, rn.x, gn.x);
+    row(mi.y, bi.y, ag.y, wsel(w1v, w1, j), wsel(w2v, w2, j), xn.y, rn.y, gn.y);
+    st_pair<NT, WHOLE>(x, i, n, xn);
+    if constexpr (STORE) {
+      st_pair<NT, WHOLE>(r, i, n, rn);
+      st_pair<false, WHOLE>(gnew, i, n, gn);
+    }
+  });
+}
+
+// PROL: on x + P x_c
+template <typename T, int MODE, bool NT, bool PROL>
+__global__ __launch_bounds__(kBlock) void k_pair_first_res(int64_t n, EllView<T> A, const T* __restrict__ minv,
+                                                           const T* __restrict__ b, const T* __restrict__ x,
+                                                           Prol<T> pr, T* __restrict__ r, T* __restrict__ g, T c) {
+  for_pair(n, [&](auto whole, int64_t i) {
+    constexpr bool WHOLE = decltype(whole)::value;
+    const V2<T> bi = ld_pair<NT, WHOLE>(b, i, n), mi = ld_pair<NT, WHOLE>(minv, i, n);
+    V2<T> ax;
+    if constexpr (PROL)
+      ax = pair_sum(A, (int)i, GatherProl<T>{x, pr.agg, pr.xc});
+    else
+      ax = pair_sum(A, (int)i, GatherVec<T>{x});
+    V2<T> rn{bi.x - ax.x, bi.y - ax.y}, gn;
+    if (MODE == 0) {
+      gn = V2<T>{c * (mi.x * rn.x), c * (mi.y * rn.y)};
+    } else {
+      rn = V2<T>{mi.x * rn.x, mi.y * rn.y};
+      gn = V2<T>{rn.x / c, rn.y / c};
+    }
+    st_pair<NT, WHOLE>(r, i, n, rn);
+    st_pair<false, WHOLE>(g, i, n, gn);
+  });
+}
+
+// y = A x, or y = b - A x (b given)
+template <typename T, bool NT, bool RES>
+__global__ __launch_bounds__(kBlock) void k_pair_spmv(int64_t n, EllView<T> A, const T* __restrict__ b,
+                                                      const T* __restrict__ x, T* __restrict__ y) {
+  for_pair(n, [&](auto whole, int64_t i) {
+    constexpr bool WHOLE = decltype(whole)::value;
+    const V2<T> v = pair_sum(A, (int)i, GatherVec<T>{x});
+    if constexpr (RES) {
+      const V2<T> bi = ld_pair<NT, WHOLE>(b, i, n);
+      st_pair<false, WHOLE>(y, i, n, V2<T>{bi.x - v.x, bi.y - v.y});
+    } else {
+      st_pair<NT, WHOLE>(y, i, n, v);
+    }
+  });
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_pair_jacobi(int64_t n, EllView<T> A, const T* __restrict__ minv,
+                                                        const T* __restrict__ b, const T* __restrict__ xold,
+                                                        T* __restrict__ xnew) {
+  for_pair(n, [&](auto whole, int64_t i) {
+    constexpr bool WHOLE = decltype(whole)::value;
+    const V2<T> ax = pair_sum(A, (int)i, GatherVec<T>{xold});
+    const V2<T> xo = ld_pair<false, WHOLE>(xold, i, n), mi = ld_pair<false, WHOLE>(minv, i, n),
+                bi = ld_pair<false, WHOLE>(b, i, n);
+    st_pair<false, WHOLE>(xnew, i, n, V2<T>{xo.x + mi.x * (bi.x - ax.x), xo.y + mi.y * (bi.y - ax.y)});
+  });
+}
+
+template <bool NT, typename TZ, bool PRE>
+__global__ __launch_bounds__(kBlock) void k_pair_spmv_dot_p(int64_t n, EllView<double> A,
+                                                            const double* __restrict__ scal, const TZ* __restrict__ z,
+                                                            const double* __restrict__ pold, double* pnew,
+                                                            double* __restrict__ q, double* __restrict__ partial,
+                                                            double* __restrict__ x) {
+  const double beta = scal[S_BETA];
+  double v = 0.0;
+  for_pair(n, [&](auto whole, int64_t i) {
+    constexpr bool WHOLE = decltype(whole)::value;
+    V2<double> pi;
+    if constexpr (PRE) pi = ld_pair<false, WHOLE>((const double*)pnew, i, n);
+    const V2<double> a = pair_sum(A, (int)i, Direction<TZ, PRE>{z, PRE ? pnew : pold, beta});
+    if constexpr (!PRE) {
+      const V2<double> po = ld_pair<false, WHOLE>(pold, i, n);
+      const V2<TZ> zi = ld_pair<false, WHOLE>(z, i, n);
+      pi = V2<double>{(double)zi.x + beta * po.x, (double)zi.y + beta * po.y};
+      st_pair<NT, WHOLE>(pnew, i, n, pi);
+      if (x) {
+        const double alpha = scal[S_ALPHA];
+        const V2<double> xi = ld_pair<NT, WHOLE>((const double*)x, i, n);
+        st_pair<NT, WHOLE>(x, i, n, V2<double>{xi.x + alpha * po.x, xi.y + alpha * po.y});
+      }
+    }
+    st_pair<NT, WHOLE>(q, i, n, a);
+    v = WHOLE || i + 1 < n ? pi.x * a.x + pi.y * a.y : pi.x * a.x;
+  });
+  const double sum = block_sum(v);
+  if (threadIdx.x == 0) partial[logical_block<kPair>()] = sum;
 }
 
 // Optional middle stage for long partial lists: block b sums the contiguous chunk b of both
@@ -1277,18 +1612,20 @@ inline bool wide(const Ell<float>&) { return false; }
 
 // Runs f(NT, V) for a level of one row per lane: the streaming hints of `nt`, and the variant of
 // its slices.  kHasWide: the kernel has a wide form (streaming levels only).
-template <bool kHasWide, typename T, typename F>
+template <bool kHasWide, bool kHasMirror = false, typename T, typename F>
 void with_variant(const Ell<T>& A, bool nt, F&& f) {
   using Narrow = std::integral_constant<int, V_NARROW>;
   using Wide = std::integral_constant<int, V_WIDE>;
   using Uniform = std::integral_constant<int, V_UNIFORM>;
   using Mirror = std::integral_constant<int, V_MIRROR>;
-  if (A.mir) {
-    if (nt)
-      f(std::true_type(), Mirror());
-    else
-      f(std::false_type(), Mirror());
-    return;
+  if constexpr (kHasMirror || std::is_same_v<T, float>) {
+    if (A.mir) {
+      if (nt)
+        f(std::true_type(), Mirror());
+      else
+        f(std::false_type(), Mirror());
+      return;
+    }
   }
   if (A.desc) {
     if (nt)
@@ -1308,6 +1645,37 @@ void with_variant(const Ell<T>& A, bool nt, F&& f) {
   else
     f(std::false_type(), Narrow());
 }
+
+// f(mode, store) as constants
+template <typename F>
+void with_mode_store(int mode, bool store, F&& f) {
+  using M0 = std::integral_constant<int, 0>;
+  using M1 = std::integral_constant<int, 1>;
+  if (mode == 0 && store)
+    f(M0(), std::true_type());
+  else if (mode == 0)
+    f(M0(), std::false_type());
+  else if (store)
+    f(M1(), std::true_type());
+  else
+    f(M1(), std::false_type());
+}
+
+// Levels served by two rows per lane: f(NT) with the launch shape.
+template <typename T, typename F>
+int with_pairs(const Ell<T>& A, F&& f) {
+  const dim3 gr((grid_for((A.n + 1) / 2) + kXcd - 1) / kXcd * kXcd);
+  if (streamed(xcd_grid(A.n)))
+    f(std::true_type(), gr);
+  else
+    f(std::false_type(), gr);
+  return hipGetLastError() == hipSuccess ? AMG_OK : AMG_EHIP;
+}
+// FP64 levels of mirrored diagonals: loads of 16 bytes instead of 8 for every stream of a row (256^3
+// solve 87.6 -> 79.1 ms, degree-5 application on 203x187x171 rows 515 -> 471 us).  With the FP32
+// hierarchy, whose pairs take 8 bytes, one row per lane is the faster (52.5 against 54.4 ms; 32 x 64^3
+// training step 6.15 against 6.65 ms).
+inline bool paired(const Ell<double>& A) { return A.mir != nullptr; }
 
 // The levels whose merged first two steps can read u = M^{-1} b instead of gathering M^{-1} and b
 bool first2_takes_u(const Ell<double>& A) { return streamed(xcd_grid(A.n)) && wide(A); }
@@ -1330,6 +1698,11 @@ int with_group(int group, F&& f) {
 
 template <typename T>
 int launch_spmv(hipStream_t s, const Ell<T>& A, const T* x, T* y) {
+    if constexpr (std::is_same_v<T, double>)
+    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+      hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, false>), gr, dim3(kBlock), 0, s, A.n, view(A),
+                         (const T*)nullptr, x, y);
+    });
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const unsigned g = xcd_grid(A.n * G);
@@ -1345,6 +1718,10 @@ int launch_spmv(hipStream_t s, const Ell<T>& A, const T* x, T* y) {
 
 template <typename T>
 int launch_residual(hipStream_t s, const Ell<T>& A, const T* b, const T* x, T* r) {
+    if constexpr (std::is_same_v<T, double>)
+    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+      hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, true>), gr, dim3(kBlock), 0, s, A.n, view(A), b, x, r);
+    });
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const unsigned g = xcd_grid(A.n * G);
@@ -1406,6 +1783,21 @@ template <typename T>
 int launch_first2_zero(hipStream_t s, int mode, bool store, const Ell<T>& A, const T* minv, const T* b, T* gnew,
                        T* r, T* x, double c1, double alpha, double c, double w1, double w2, Wt w1v, Wt w2v,
                        const T* u) {
+    if constexpr (std::is_same_v<T, double>)
+    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+      auto go = [&](auto m, auto st, auto hu) {
+        hipLaunchKernelGGL((k_pair_first2_zero<T, decltype(m)::value, decltype(st)::value, decltype(nt)::value,
+                                               decltype(hu)::value>),
+                           gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, gnew, r, x, (T)c1, (T)alpha, (T)c, (T)w1,
+                           (T)w2, w1v, w2v, u);
+      };
+      with_mode_store(mode, store, [&](auto m, auto st) {
+        if (u)
+          go(m, st, std::true_type());
+        else
+          go(m, st, std::false_type());
+      });
+    });
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const dim3 gr(xcd_grid(A.n * G));
@@ -1443,6 +1835,14 @@ void go_first_res(dim3 gr, hipStream_t s, int mode, EllView<T> A, int64_t n, con
 template <typename T>
 int launch_first_res(hipStream_t s, int mode, const Ell<T>& A, const T* minv, const T* b, const T* x, T* r,
                      T* g, double c, Prol<T> pr) {
+    if constexpr (std::is_same_v<T, double>)
+    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+      auto go = [&](auto m, auto prol) {
+        hipLaunchKernelGGL((k_pair_first_res<T, decltype(m)::value, decltype(nt)::value, decltype(prol)::value>), gr,
+                           dim3(kBlock), 0, s, A.n, view(A), minv, b, x, pr, r, g, (T)c);
+      };
+      with_mode_store(mode, pr.agg != nullptr, go);
+    });
   if (pr.agg) {
     if (A.group != 1) return AMG_EINVAL;
     const dim3 gr(xcd_grid(A.n)), bl(kBlock);
@@ -1498,6 +1898,18 @@ template <typename T>
 int launch_fused(hipStream_t s, int mode, bool store, const Ell<T>& A, const T* minv, const T* gold, T* gnew,
                  const T* rin, T* rout, T* x, double alpha, double c, double w, double wprev, Wt wv, Wt wpv,
                  Prol<T> pr) {
+    if constexpr (std::is_same_v<T, double>)
+    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+      with_mode_store(mode, store, [&](auto m, auto st) {
+        constexpr int MODE = decltype(m)::value;
+        if (!x)  // a stored step that leaves x alone
+          hipLaunchKernelGGL((k_pair_fused_keep_x<T, MODE, decltype(nt)::value>), gr, dim3(kBlock), 0, s, A.n, view(A),
+                             minv, gold, gnew, rin, rout, (T)alpha, (T)c);
+        else
+          hipLaunchKernelGGL((k_pair_fused<T, MODE, decltype(st)::value, decltype(nt)::value>), gr, dim3(kBlock), 0, s,
+                             A.n, view(A), minv, gold, gnew, rin, rout, x, (T)alpha, (T)c, (T)w, (T)wprev, wv, wpv, pr);
+      });
+    });
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const dim3 gr(xcd_grid(A.n * G));
@@ -1517,6 +1929,15 @@ template <typename T>
 int launch_fused_dot(hipStream_t s, int mode, const Ell<T>& A, const T* minv, const T* gold, const T* rin, T* x,
                      double alpha, double c, double w, double wprev, Wt wv, Wt wpv, Prol<T> pr, const double* dr,
                      const double* drold, double* partial, unsigned* nblocks) {
+    if constexpr (std::is_same_v<T, double>)
+    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+      with_mode_store(mode, false, [&](auto m, auto) {
+        hipLaunchKernelGGL((k_pair_fused_dot<T, decltype(m)::value, decltype(nt)::value>), gr, dim3(kBlock), 0, s, A.n,
+                           view(A), minv, gold, rin, x, (T)alpha, (T)c, (T)w, (T)wprev, wv, wpv, pr, dr, drold,
+                           partial);
+      });
+      *nblocks = gr.x;
+    });
   if (A.group != 1) return AMG_EINVAL;
   const dim3 gr(xcd_grid(A.n)), bl(kBlock);
   with_variant<true>(A, streamed(gr.x), [&](auto nt, auto v) {
@@ -1541,6 +1962,10 @@ template int launch_fused_dot<float>(hipStream_t, int, const Ell<float>&, const 
 
 template <typename T>
 int launch_jacobi(hipStream_t s, const Ell<T>& A, const T* minv, const T* b, const T* xold, T* xnew) {
+    if constexpr (std::is_same_v<T, double>)
+    if (paired(A)) return with_pairs(A, [&](auto, dim3 gr) {
+      hipLaunchKernelGGL(k_pair_jacobi<T>, gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, xold, xnew);
+    });
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const dim3 gr(xcd_grid(A.n * G)), bl(kBlock);
@@ -1565,7 +1990,7 @@ int launch_restrict(hipStream_t s, const Ell<T>& A, int64_t nc, const int32_t* c
   static_assert(kMaxChildren == 8 && kWave % kMaxChildren == 0, "eight lanes per aggregate");
   if (A.group == 1 && A.n <= kFusedRestrictMaxRows) {
     const unsigned g = xcd_grid(nc * kMaxChildren);
-    with_variant<false>(A, streamed(g), [&](auto nt, auto v) {
+    with_variant<false, true>(A, streamed(g), [&](auto nt, auto v) {
       hipLaunchKernelGGL((k_res_restrict<T, decltype(nt)::value, decltype(v)::value>), dim3(g), dim3(kBlock), 0, s,
                          nc, view(A), children, b, x, bc);
     });
@@ -1665,6 +2090,17 @@ template int launch_dot2<float>(hipStream_t, int64_t, const double*, const float
 template <typename TZ>
 int launch_spmv_dot_p(hipStream_t s, const Ell<double>& A, const double* scal, const TZ* z, const double* pold,
                       double* pnew, double* q, double* partial, double* x, unsigned* nblocks) {
+    if (paired(A))
+    return with_pairs(A, [&](auto nt, dim3 gr) {
+      constexpr bool NT = decltype(nt)::value;
+      if constexpr (NT) {
+        const unsigned g = xcd_grid(A.n);
+        hipLaunchKernelGGL((k_form_p<true, TZ>), dim3(g), dim3(kBlock), 0, s, A.n, scal, z, pold, pnew, x);
+      }
+      hipLaunchKernelGGL((k_pair_spmv_dot_p<NT, TZ, NT>), gr, dim3(kBlock), 0, s, A.n, view(A), scal, z, pold, pnew, q,
+                         partial, NT ? nullptr : x);
+      *nblocks = gr.x;
+    });
   const unsigned g = xcd_grid(A.n);
   if (streamed(g)) {
     hipLaunchKernelGGL((k_form_p<true, TZ>), dim3(g), dim3(kBlock), 0, s, A.n, scal, z, pold, pnew, x);

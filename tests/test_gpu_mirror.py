@@ -124,3 +124,20 @@ def test_infinity_and_nan_reach_the_rows_of_a_dense_layout(amg):
             got.append(host(y))
     assert np.array_equal(np.isnan(got[0]), np.isnan(got[1]))
     assert np.array_equal(np.isinf(got[0]), np.isinf(got[1]))
+
+
+def test_vectors_at_any_row(amg):
+    # vectors that begin 8 bytes past a 16-byte boundary (views into a larger array)
+    torch = torch_cuda()
+    A = MATRICES["ragged"][0]()
+    As = A.to_scipy()
+    rng = np.random.default_rng(16)
+    b = rng.uniform(-1, 1, A.n)
+    with hierarchy(A) as h:
+        bv = torch.empty(A.n + 1, dtype=torch.float64, device="cuda")[1:]
+        xv = torch.full((A.n + 3,), float("nan"), dtype=torch.float64, device="cuda")[3:]
+        bv.copy_(dev(b))
+        assert bv.data_ptr() % 16 == 8 and xv.data_ptr() % 16 == 8
+        amg.smoother_apply(h, 0, 2, 4, bv, xv, True)
+        beta, a = oracle_params(2, 4)
+        assert relerr(host(xv), S.smooth(As, S.l1_diagonal(As), b, None, 2, 4, beta, a)) <= 1e-12

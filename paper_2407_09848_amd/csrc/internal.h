@@ -477,6 +477,10 @@ void free_ell(Ell<float>& e);
 // dense[nbatch][np][np] (SPD, lower tiles read, overwritten) -> *packed: the lower 64x64 blocks of
 // each A^{-1} in contiguous tiles (tile J(J+1)/2 + I = block (J, I)); the caller's, also on error
 int dense_spd_inverse(hipStream_t s, int nbatch, int64_t np, double* dense, double** packed, int* flag);
+// The operator of `sweeps` l1-Jacobi sweeps from zero, sum_j (I - M^{-1} A)^j M^{-1} (symmetric), as such
+// tiles; np is n rounded up to whole tiles
+int sweep_operator(hipStream_t s, int64_t n, int64_t np, const int32_t* ptr, const int32_t* col, const double* val,
+                   const double* minv, int sweeps, double** packed);
 // x = A^{-1} b from the lower blocks of the symmetric inverse; part holds nbatch * (np/64)^2 * 64 doubles
 template <typename T>
 int launch_coarse_symv(hipStream_t s, int nbatch, int64_t nl, int64_t np, const double* ainv, const T* b, T* x,

@@ -277,6 +277,37 @@ __global__ __launch_bounds__(256) void k_inverse_tiles(int np, int ntiles, const
   for_tile(acc, [&](int i, int j, double v) { dst[i * TM + j] = v; });
 }
 
+// One l1-Jacobi sweep on the columns of X (np x np, row-major): X_new = X + M^{-1} (I - A X), the sweep of
+// k_jacobi for the right-hand sides e_c; a block serves 256 columns of one row.
+__global__ __launch_bounds__(256) void k_sweep_columns(int n, int np, const int32_t* __restrict__ ptr,
+                                                       const int32_t* __restrict__ col,
+                                                       const double* __restrict__ val,
+                                                       const double* __restrict__ minv, const double* __restrict__ X,
+                                                       double* __restrict__ Xnew) {
+  const int i = blockIdx.x, c = blockIdx.y * 256 + threadIdx.x;
+  if (c >= n) return;
+  double ax = 0.0;
+#pragma unroll 4
+  for (int p = ptr[i]; p < ptr[i + 1]; ++p) ax += val[p] * X[(long long)col[p] * np + c];
+  const double b = i == c ? 1.0 : 0.0;
+  Xnew[(long long)i * np + c] = X[(long long)i * np + c] + minv[i] * (b - ax);
+}
+
+__global__ void k_diagonal(int n, int np, const double* __restrict__ d, double* __restrict__ X) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) X[(long long)i * np + i] = d[i];
+}
+
+// Copy the lower 64x64 blocks of an np x np matrix into contiguous 32 KB tiles.
+__global__ __launch_bounds__(256) void k_pack_tiles(int np, const double* __restrict__ dense,
+                                                    double* __restrict__ packed) {
+  int J, I;
+  tile_of(blockIdx.x, J, I);
+  const double* src = dense + (long long)J * TM * np + (long long)I * TM;
+  double* dst = packed + (long long)blockIdx.x * TM * TM;
+  for (int e = threadIdx.x; e < TM * TM; e += 256) dst[e] = src[(long long)(e / TM) * np + e % TM];
+}
+
 // x = A^{-1} b for the symmetric dense inverse, reading only its lower 64x64
 // blocks, each exactly once, from the packed contiguous tiles.  Tile (J, I) of
 // problem p is handled by one wavefront that streams its 64 rows (one 512 B
@@ -395,6 +426,36 @@ int dense_spd_inverse(hipStream_t s, int nbatch, int64_t np64, double* dense, do
   if (rc != AMG_OK) hipStreamSynchronize(s);
   dev_free(dinv);
   dev_free(X);
+  return rc;
+}
+
+int sweep_operator(hipStream_t s, int64_t n, int64_t np, const int32_t* ptr, const int32_t* col, const double* val,
+                   const double* minv, int sweeps, double** packed) {
+  const int nb = (int)(np / TM), ntiles = nb * (nb + 1) / 2;
+  const size_t bytes = sizeof(double) * (size_t)np * np;
+  double* X[2] = {nullptr, nullptr};
+  *packed = nullptr;
+  const int rc = [&]() -> int {
+    if (temp_malloc(&X[0], bytes) != hipSuccess || temp_malloc(&X[1], bytes) != hipSuccess ||
+        keep_malloc(packed, sizeof(double) * (size_t)ntiles * TM * TM) != hipSuccess)
+      return AMG_ENOMEM;
+    // the rows and columns past n stay zero in both
+    AMGP_HIP(hipMemsetAsync(X[0], 0, bytes, s));
+    AMGP_HIP(hipMemsetAsync(X[1], 0, bytes, s));
+    hipLaunchKernelGGL(k_diagonal, dim3(grid_for(n)), dim3(kBlock), 0, s, (int)n, (int)np, minv, X[0]);
+    for (int k = 1; k < sweeps; ++k) {
+      hipLaunchKernelGGL(k_sweep_columns, dim3((unsigned)n, grid_for(n, 256)), dim3(256), 0, s, (int)n, (int)np, ptr, col,
+                         val, minv, (const double*)X[0], X[1]);
+      std::swap(X[0], X[1]);
+    }
+    hipLaunchKernelGGL(k_pack_tiles, dim3(ntiles), dim3(256), 0, s, (int)np, (const double*)X[0], *packed);
+    AMGP_HIP(hipGetLastError());
+    AMGP_HIP(hipStreamSynchronize(s));
+    return AMG_OK;
+  }();
+  if (rc != AMG_OK) hipStreamSynchronize(s);
+  dev_free(X[0]);
+  dev_free(X[1]);
   return rc;
 }
 

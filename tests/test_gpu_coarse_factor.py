@@ -53,3 +53,20 @@ def test_indefinite_coarsest_level_is_refused(amg, row):
         with hierarchy(A, max_coarse=10**6):
             pass
     assert e.value.code == amg.AMG_ENOTSPD
+
+
+@pytest.mark.parametrize("n,sweeps,nbatch", [(1, 30, 1), (63, 8, 1), (64, 30, 1), (65, 30, 1), (700, 30, 1),
+                                              (700, 7, 1), (700, 30, 2), (2048, 12, 1), (2049, 12, 1)])
+def test_coarse_sweeps_match_oracle(amg, n, sweeps, nbatch):
+    # the sweeps contract (every M^-1 A spectrum lies in (0, 1]): rounding adds up to at most
+    # sweeps * (nonzeros per row) * 2^-53 of the result, below 1e-12
+    from oracle import smoothers as S
+    A = W.stack_block_diagonal([W.poisson3d_7pt(n, 1, 1) if n > 700 else W.fv_diffusion(
+        np.exp(np.random.default_rng(n + p).standard_normal((1, 7 if n % 7 == 0 else 1, n // 7 if n % 7 == 0 else n))))
+        for p in range(nbatch)])
+    As = A.to_scipy()
+    b = np.random.default_rng(17).uniform(-1, 1, A.n)
+    with hierarchy(A, nbatch=nbatch, max_coarse=10**6, coarse_sweeps=sweeps) as h:
+        x = nan_vec(A.n)
+        amg.amg_coarse_solve(h, dev(b), x)
+        assert relerr(host(x), S.smooth(As, S.l1_diagonal(As), b, None, 0, sweeps)) <= 1e-12

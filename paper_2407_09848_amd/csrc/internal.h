@@ -46,15 +46,20 @@ constexpr int kQuadMinSteps = 16;
 // slice hold one common value or exactly +0, the slice is kept as a pattern, per step the offset,
 // the value and the mask of the lanes that hold it, and slices with equal patterns share one
 // copy.  A matrix of which at least half the slices are uniform has one descriptor per slice
-// (`desc`) in place of `sptr`: {beg, 16 * steps + kind}, beg in units of 64 stored values (dense
-// slices) or the first step of the pattern.  The values, their order and the zeros of the padding
+// (`desc`) in place of `sptr`: {beg, 16 * steps + kind}, beg the first step of a dense slice (in units
+// of a slice's rows) or of the pattern.  The slices of a large FP64 operator then have 128 rows, two per lane of
+// its kernels, dense ones with the rows' values of a step next to one another; a step whose offset
+// only one half of the rows uses is kept from the other half (the padding's zeros reach as far as in
+// slices of 64 rows, also to entries that are no number), its offset stored as 4 offset + the bits
+// of the halves.  All others keep 64 rows and the form above.  The values, their order and the zeros of the padding
 // are those of the dense form, so results are the same bits; a 27-point FP64 row needs no matrix
 // bytes of its own instead of 216.
 enum SliceKind {
   SLICE_DENSE = 0,
   SLICE_MASKED = 1,
   SLICE_FULL = 2,    // every lane holds every step
-  SLICE_TRIPLES = 4  // (with one of the two) the steps are triples of consecutive offsets, the rows consecutive
+  SLICE_TRIPLES = 4, // (with one of the two) the steps are triples of consecutive offsets, the rows consecutive
+  SLICE_HALVES = 8   // masked, 128 rows, and some offset is of one half alone: offsets with the bits of the halves
 };
 // Mirrored diagonals (large symmetric stencil matrices of varying coefficients): when the whole
 // matrix uses few offsets (7 or 27 of a stencil) and a_ij and a_ji are the same bits, only the entries of
@@ -69,6 +74,8 @@ struct MirrorStep {
   int32_t off, unused;
 };
 constexpr int kMirrorMaxSteps = 27;
+
+inline int64_t pattern_bytes(int64_t npat, int rpl) { return ((12 + 8 * rpl) * npat + 7) / 8 * 8; }
 
 template <typename T>
 struct Ell {
@@ -87,9 +94,11 @@ struct Ell {
   int astride = 1;
   // uniform slices (null: none)
   int2* desc = nullptr;          // [nslices] {beg, 16 * steps + kind}
-  unsigned long long* pat = nullptr;  // [npat] lane masks of the patterns' steps, then values (T, [npat]
-                                      // of 8 bytes), then offsets (int32): 20 npat bytes
+  // lane masks of the patterns' steps ([npat] of the first row of every lane, then of the second), then
+  // their values (T, in 8 npat bytes), then offsets (int32)
+  unsigned long long* pat = nullptr;
   int64_t npat = 0;
+  int rpl = 1;                   // rows per lane of a matrix with uniform slices
   int64_t dense = 0;             // stored values (dense slices); padded counts all slices' steps
   int64_t patterned = 0;         // slices kept as patterns
   MirrorStep* mir = nullptr;     // [nmir] steps of mirrored diagonals (null: none)
@@ -129,8 +138,10 @@ struct EllView {
   __host__ __device__ const unsigned long long* pmask() const {
     return reinterpret_cast<const unsigned long long*>(col);
   }
-  __host__ __device__ const T* pval() const { return reinterpret_cast<const T*>(pmask() + npat); }
-  __host__ __device__ const int32_t* poff() const { return reinterpret_cast<const int32_t*>(pmask() + 2 * (int64_t)npat); }
+  __host__ __device__ const T* pval(int rpl) const { return reinterpret_cast<const T*>(pmask() + rpl * (int64_t)npat); }
+  __host__ __device__ const int32_t* poff(int rpl) const {
+    return reinterpret_cast<const int32_t*>(pmask() + (rpl + 1) * (int64_t)npat);
+  }
 };
 
 template <typename T>
@@ -424,15 +435,16 @@ int launch_l1_diag(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* 
                    double* minv, int* flag);
 // ncols: number of columns (default n); padding entries use column i when i < ncols, else 0.
 // group: lanes per row (1, 4, 16 or 64); 0 chooses from the mean row length
+// pairs: two rows per lane allowed on large levels of uniform slices (no FP32 copy is taken)
 int build_ell64(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
-                Ell<double>* out, int64_t ncols = -1, int group = 1);
+                Ell<double>* out, int64_t ncols = -1, int group = 1, bool pairs = false);
 int build_ell32(hipStream_t s, const Ell<double>& a, Ell<float>* out);
 // offset-aligned slices (one row per lane) with the offsets taken against anchor[r * astride]
 // (null: the row r) and columns clamped into [0, ncols) (-1: n); AMG_EINVAL when a slice has more
 // than 64 offsets or (unless any_size) the layout is more than 10% larger than the packed one
 int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
                       Ell<double>* out, const int32_t* anchor = nullptr, int astride = 1, int64_t ncols = -1,
-                      bool any_size = false);
+                      bool any_size = false, bool pairs = false);
 // box aggregates of edge e; children (2x2x2 boxes only) may be null
 int launch_aggregates(hipStream_t s, int nx, int ny, int nz, int nbatch, int e, int32_t* agg, int32_t* children,
                       int* cnx, int* cny, int* cnz);

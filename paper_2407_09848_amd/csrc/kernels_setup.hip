@@ -122,8 +122,8 @@ __global__ void k_ell_fill(int64_t n, int64_t ncols, int64_t nslices, int G, con
   }
 }
 
-// Layout of every 64-row slice, one wavefront per slice, its lanes on consecutive entries of the
-// slice's rows (contiguous in CSR, so the loads coalesce; one row per lane instead read 20 KB a
+// Layout of every slice of 64 RPL rows (RPL rows per lane of the kernels), one wavefront per slice,
+// its lanes on consecutive entries of the slice's rows (contiguous in CSR, so the loads coalesce; one row per lane instead read 20 KB a
 // wavefront through its own cache lines, 33 ms against 5 ms for the kinds of the 27-point 320^3
 // matrix).  The slice's distinct column offsets (col - row, or col - anchor[row * astride]) go into
 // an LDS hash set.
@@ -134,13 +134,14 @@ __global__ void k_ell_fill(int64_t n, int64_t ncols, int64_t nslices, int G, con
 // and all of one value (zero included); a differing value ends the search (the first entries of
 // a matrix of varying coefficients).
 // TABLES = true (uniform slices alone): per step the value and the lane mask (all ones for a full
-// step), stride records per slice in vtab / mtab, and the hash of offsets, values and masks.
+// step; with two rows per lane of the even rows, then of the odd ones), stride records per slice in
+// vtab / mtab, and the hash of offsets, values and masks.
 constexpr int kOffHash = 256;
 constexpr int kOffEmpty = INT_MIN;
 
 __device__ __forceinline__ unsigned off_slot(int o) { return ((unsigned)o * 2654435761u) & (kOffHash - 1); }
 
-template <bool TABLES>
+template <bool TABLES, int RPL>
 __global__ __launch_bounds__(kWave) void k_slice_layout(
     int64_t n, const int32_t* __restrict__ ptr, const int32_t* __restrict__ col, const double* __restrict__ val,
     const int32_t* anchor, int astride, int32_t* __restrict__ offs, int32_t* __restrict__ width,
@@ -149,30 +150,33 @@ __global__ __launch_bounds__(kWave) void k_slice_layout(
   __shared__ int set[kOffHash];
   __shared__ int at[kOffHash];  // step of a set entry
   __shared__ int list[kWave];
-  __shared__ int rp[kWave + 1];
-  __shared__ int base[kWave];
-  __shared__ unsigned long long sval[kWave], spres[kWave], snz[kWave];
+  constexpr int kRows = kSlice * RPL;
+  __shared__ int rp[kRows + 1];
+  __shared__ int base[kRows];
+  __shared__ unsigned long long sval[kWave], spres[RPL][kWave], snz[RPL][kWave];
   __shared__ int cnt, differ;
   const int64_t s = blockIdx.x;
   const int lane = threadIdx.x;
   if (TABLES && kind[s] == SLICE_DENSE) return;
-  const int64_t r = s * kSlice + lane;
-  const int64_t rc = r < n ? r : n;
-  rp[lane] = ptr[rc];
-  if (lane == kWave - 1) rp[kWave] = ptr[r + 1 < n ? r + 1 : n];
-  base[lane] = r < n ? (anchor ? anchor[r * astride] : (int)r) : 0;
+  for (int k = lane; k < kRows; k += kWave) {
+    const int64_t r = s * kRows + k;
+    rp[k] = ptr[r < n ? r : n];
+    if (k == kRows - 1) rp[kRows] = ptr[r + 1 < n ? r + 1 : n];
+    base[k] = r < n ? (anchor ? anchor[r * astride] : (int)r) : 0;
+  }
   for (int t = lane; t < kOffHash; t += kWave) set[t] = kOffEmpty;
   if (lane == 0) {
     cnt = 0;
     differ = 0;
   }
-  sval[lane] = spres[lane] = snz[lane] = 0;
+  sval[lane] = 0;
+  for (int k = 0; k < RPL; ++k) spres[k][lane] = snz[k][lane] = 0;
   __syncthreads();
-  const int beg = rp[0], end = rp[kWave];
-  auto row_of = [&](int e) {  // the row (0..63) of entry e
+  const int beg = rp[0], end = rp[kRows];
+  auto row_of = [&](int e) {  // the row (of the slice) of entry e
     int lo = 0;
 #pragma unroll
-    for (int step = kWave / 2; step > 0; step >>= 1)
+    for (int step = kRows / 2; step > 0; step >>= 1)
       if (rp[lo + step] <= e) lo += step;
     return lo;
   };
@@ -201,7 +205,8 @@ __global__ __launch_bounds__(kWave) void k_slice_layout(
     }
     __syncthreads();
   } else {
-    int longest = rp[lane + 1] - rp[lane];
+    int longest = 0;
+    for (int k = lane; k < kRows; k += kWave) longest = max(longest, rp[k + 1] - rp[k]);
     for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off, kWave));
     if (lane == 0) lwidth[s] = longest;
     for (int e = beg + lane; e < end; e += kWave) {
@@ -250,10 +255,10 @@ __global__ __launch_bounds__(kWave) void k_slice_layout(
     while (set[h] != o) h = (h + 1) & (kOffHash - 1);
     const int t = at[h];
     const unsigned long long bits = (unsigned long long)__double_as_longlong(val[e]);
-    const unsigned long long bit = 1ull << row;
-    atomicOr(&spres[t], bit);
+    const unsigned long long bit = 1ull << (row / RPL);
+    atomicOr(&spres[row % RPL][t], bit);
     if (bits) {
-      atomicOr(&snz[t], bit);
+      atomicOr(&snz[row % RPL][t], bit);
       unsigned long long old = sval[t];
       if (old == 0) old = atomicCAS(&sval[t], 0ull, bits);
       if (old != 0 && old != bits) differ = 1;
@@ -264,15 +269,29 @@ __global__ __launch_bounds__(kWave) void k_slice_layout(
     if (lane == 0) kind[s] = SLICE_DENSE;
     return;
   }
-  const bool whole = spres[lane] == ~0ull && (snz[lane] == 0 || snz[lane] == ~0ull);
+  bool whole = true;
+  for (int k = 0; k < RPL; ++k)
+    whole = whole && spres[k][lane] == ~0ull && snz[k][lane] == snz[0][lane] &&
+            (snz[k][lane] == 0 || snz[k][lane] == ~0ull);
+  // the halves of 128 rows that use a step's offset
+  int bits = 3;
+  if constexpr (RPL == 2) {
+    const unsigned long long pres = spres[0][lane] | spres[1][lane];
+    bits = ((pres & 0xffffffffull) != 0) | ((pres >> 32) != 0) << 1;
+  }
+  const bool halves = __ballot(lane < c && bits != 3) != 0;
   if constexpr (TABLES) {
     unsigned long long h = 0;
     if (lane < c) {
-      const unsigned long long v = sval[lane], m = whole ? ~0ull : snz[lane];
+      if (halves) offs[s * kSlice + lane] = 4 * list[lane] + bits;
+      const unsigned long long v = sval[lane];
       vtab[s * stride + lane] = v;
-      mtab[s * stride + lane] = m;
-      h = graph::splitmix64(graph::splitmix64(((unsigned long long)lane << 32) + (unsigned)list[lane]) ^ v);
-      h = graph::splitmix64(h ^ m);
+      h = graph::splitmix64(graph::splitmix64(((unsigned long long)lane << 32) + (unsigned)list[lane] * 4 + bits) ^ v);
+      for (int k = 0; k < RPL; ++k) {
+        const unsigned long long m = whole ? ~0ull : snz[k][lane];
+        mtab[(s * RPL + k) * stride + lane] = m;
+        h = graph::splitmix64(h ^ m);
+      }
     }
     for (int off = 32; off > 0; off >>= 1) h += __shfl_xor(h, off, kWave);
     if (lane == 0) hash[s] = graph::splitmix64(h) | 1;  // 0 marks a free slot
@@ -280,8 +299,9 @@ __global__ __launch_bounds__(kWave) void k_slice_layout(
     const bool full = __ballot(lane < c && !whole) == 0;
     // triples: a whole slice of consecutive rows whose sorted offsets come in threes
     const bool third = lane < c && (lane % 3 == 0 || list[lane] == list[lane - 1] + 1);
-    const bool triples = !anchor && (s + 1) * kSlice <= n && c % 3 == 0 && __ballot(lane < c && !third) == 0;
-    if (lane == 0) kind[s] = (full ? SLICE_FULL : SLICE_MASKED) | (triples ? SLICE_TRIPLES : 0);
+    const bool triples = !anchor && (s + 1) * kRows <= n && c % 3 == 0 && __ballot(lane < c && !third) == 0;
+    if (lane == 0)
+      kind[s] = halves ? SLICE_HALVES : (full ? SLICE_FULL : SLICE_MASKED) | (triples ? SLICE_TRIPLES : 0);
   }
 }
 
@@ -309,7 +329,7 @@ __global__ void k_pattern_insert(int64_t nslices, const int32_t* __restrict__ ki
 __global__ void k_pattern_resolve(int64_t nslices, const int32_t* __restrict__ kind,
                                   const unsigned long long* __restrict__ hash, unsigned cap,
                                   const unsigned long long* __restrict__ keys, const int32_t* __restrict__ first,
-                                  const int32_t* __restrict__ offs, const int32_t* __restrict__ width, int stride,
+                                  const int32_t* __restrict__ offs, const int32_t* __restrict__ width, int rpl, int stride,
                                   const unsigned long long* __restrict__ vtab,
                                   const unsigned long long* __restrict__ mtab, int32_t* __restrict__ rep) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -324,13 +344,14 @@ __global__ void k_pattern_resolve(int64_t nslices, const int32_t* __restrict__ k
   bool same = kind[f] == kind[s] && width[f] == width[s];
   for (int t = 0; same && t < width[s]; ++t)
     same = offs[f * kSlice + t] == offs[s * kSlice + t] && vtab[f * stride + t] == vtab[s * stride + t] &&
-           mtab[f * stride + t] == mtab[s * stride + t];
+           mtab[f * rpl * stride + t] == mtab[s * rpl * stride + t] &&
+           mtab[(f * rpl + rpl - 1) * stride + t] == mtab[(s * rpl + rpl - 1) * stride + t];
   rep[s] = same ? (int32_t)f : (int32_t)s;
 }
 
 // The kept patterns' steps: one wavefront per slice, lane t writes step t.
 __global__ void k_pattern_write(int64_t nslices, const int32_t* __restrict__ rep, const int2* __restrict__ desc,
-                                const int32_t* __restrict__ offs, int stride,
+                                const int32_t* __restrict__ offs, int rpl, int stride,
                                 const unsigned long long* __restrict__ vtab,
                                 const unsigned long long* __restrict__ mtab, int npat,
                                 unsigned long long* __restrict__ pat) {
@@ -339,11 +360,11 @@ __global__ void k_pattern_write(int64_t nslices, const int32_t* __restrict__ rep
   if (s >= nslices || rep[s] != s) return;
   const int2 d = desc[s];
   const int t = (int)(g % kSlice);
-  if (t >= d.y >> 4) return;
+  if (t >= (d.y >> 4)) return;
   const int64_t q = d.x + t;
-  pat[q] = mtab[s * stride + t];
-  pat[npat + q] = vtab[s * stride + t];
-  reinterpret_cast<int32_t*>(pat + 2 * (int64_t)npat)[q] = offs[s * kSlice + t];
+  for (int k = 0; k < rpl; ++k) pat[(int64_t)k * npat + q] = mtab[(s * rpl + k) * stride + t];
+  pat[(int64_t)rpl * npat + q] = vtab[s * stride + t];
+  reinterpret_cast<int32_t*>(pat + (rpl + 1) * (int64_t)npat)[q] = offs[s * kSlice + t];
 }
 
 // Sums over the slices: steps of the aligned and of the packed layout, slices that fit no pattern
@@ -539,6 +560,32 @@ __global__ __launch_bounds__(kBlock) void k_mirror(int64_t n, const int32_t* __r
       atomicAdd(&differ[1], above);
       atomicAdd(&differ[2], below);
     }
+  }
+}
+
+// Dense slices of 128 rows (two rows per lane): step t of row k of the slice at 128 (beg + t) + k, its
+// offset with the bits of the halves that use it (doff zero before).  A wavefront serves one half.
+__global__ void k_ell_fill_pairs(int64_t n, const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+                                 const double* __restrict__ val, const int32_t* __restrict__ offs,
+                                 const int2* __restrict__ desc, double* __restrict__ eval,
+                                 int32_t* __restrict__ doff) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t s = r / (2 * kSlice);
+  const int k = (int)(r % (2 * kSlice));
+  if (s * 2 * kSlice >= n) return;
+  const int2 d = desc[s];
+  if ((d.y & 15) != SLICE_DENSE) return;
+  int p = r < n ? ptr[r] : 0;
+  const int pe = r < n ? ptr[r + 1] : 0;
+  for (int st = 0; st < (d.y >> 4); ++st) {
+    const int o = offs[s * kSlice + st];
+    double v = 0.0;
+    while (p < pe && col[p] < r + o) ++p;
+    const bool has = p < pe && col[p] == r + o;
+    if (has) v = val[p++];
+    eval[(int64_t)(d.x + st) * 2 * kSlice + k] = v;
+    const int half = k / kSlice, used = __ballot(has) != 0 ? 1 << half : 0;
+    if (k % kSlice == 0) atomicAdd(&doff[d.x + st], half == 0 ? 4 * o + used : used);
   }
 }
 
@@ -789,33 +836,93 @@ static int build_mirror(hipStream_t s, int64_t n, const int32_t* ptr, const int3
   return rc;
 }
 
+// Slices of 128 rows, two rows per lane, in FP64 hierarchies from this many rows on: where the vectors
+// come from HBM, half the gathers and loads of twice the width (degree-4 application: 27 points 240^3
+// 681 -> 537 us, 7 points 256^3 546 -> 492, 5 points 4000^2 506 -> 390; solve on the 27-point 320^3
+// matrix 158.8 -> 134.7 ms).  On smaller levels, whose vectors stay in the last-level cache, the
+// wavefronts count: 27 points 160^3 183 both, 128^3 92.3 -> 95.5, 7 points 160^3 113 -> 125.
+// With the FP32 hierarchy one row per lane is always the faster (27 points 240^3 304 against 353 us,
+// 7 points 256^3 252 against 354), and its FP64 fine level, which serves the products of the CG alone, keeps its form.
+constexpr int64_t kPairMinRows = 1 << 22;
+
+// Patterns of the uniform slices (64 rpl rows each) that k_slice_layout<false, rpl> found, and all
+// slices' descriptors.
+static int build_patterns(hipStream_t s, int rpl, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
+                          const int32_t* anchor, int astride, int64_t nslices, const int32_t* offs, int32_t* wd,
+                          int32_t* kind, int wmax, int64_t uniform, Ell<double>* e) {
+  unsigned cap = 64;
+  while (cap < 2 * nslices + 2) cap *= 2;  // its slices' room serves two scans of nslices + 1 later
+  // per slice and step the value and the masks, per slice the hash; the table's keys, then its slices, and rep
+  graph::DevBuf<unsigned long long> tab;
+  AMGP_TRY(tab.alloc(nslices * ((1 + rpl) * wmax + 1) + cap + (cap + nslices + 1) / 2));
+  unsigned long long *vtab = tab.p, *mtab = vtab + nslices * wmax, *hash = mtab + nslices * rpl * wmax,
+                     *keys = hash + nslices;
+  int32_t *first = reinterpret_cast<int32_t*>(keys + cap), *rep = first + cap;
+  const dim3 grid((unsigned)nslices), each(grid_for(nslices));
+  if (rpl == 1)
+    hipLaunchKernelGGL((k_slice_layout<true, 1>), grid, dim3(kWave), 0, s, n, ptr, col, val, anchor, astride,
+                       const_cast<int32_t*>(offs), wd, nullptr, kind, wmax, vtab, mtab, hash);
+  else
+    hipLaunchKernelGGL((k_slice_layout<true, 2>), grid, dim3(kWave), 0, s, n, ptr, col, val, anchor, astride,
+                       const_cast<int32_t*>(offs), wd, nullptr, kind, wmax, vtab, mtab, hash);
+  AMGP_HIP(hipMemsetAsync(keys, 0, sizeof(unsigned long long) * cap, s));
+  AMGP_HIP(hipMemsetAsync(first, 0x7f, sizeof(int32_t) * cap, s));
+  hipLaunchKernelGGL(k_pattern_insert, each, dim3(kBlock), 0, s, nslices, kind, hash, cap, keys, first);
+  hipLaunchKernelGGL(k_pattern_resolve, each, dim3(kBlock), 0, s, nslices, kind, hash, cap, keys, first, offs, wd, rpl,
+                     wmax, vtab, mtab, rep);
+  // where every slice begins among the stored values or the patterns' steps (the table's slices are
+  // done with)
+  int32_t *dbeg = first, *pbeg = first + nslices + 1;
+  hipLaunchKernelGGL(k_slice_store, each, dim3(kBlock), 0, s, nslices, wd, kind, rep, dbeg, pbeg);
+  int rc = AMG_OK;
+  e->dense = scan_ptr(s, nslices, dbeg, dbeg, &rc) * kSlice * rpl;
+  AMGP_TRY(rc);
+  e->npat = scan_ptr(s, nslices, pbeg, pbeg, &rc);
+  AMGP_TRY(rc);
+  e->patterned = uniform;
+  e->rpl = rpl;
+  if (keep_malloc(&e->desc, sizeof(int2) * nslices) != hipSuccess ||
+      keep_malloc(&e->pat, pattern_bytes(e->npat, rpl)) != hipSuccess)
+    return AMG_ENOMEM;
+  hipLaunchKernelGGL(k_slice_desc, each, dim3(kBlock), 0, s, nslices, wd, kind, rep, dbeg, pbeg, e->desc);
+  hipLaunchKernelGGL(k_pattern_write, dim3(grid_for(nslices * kSlice)), dim3(kBlock), 0, s, nslices, rep, e->desc, offs,
+                     rpl, wmax, vtab, mtab, (int)e->npat, e->pat);
+  AMGP_HIP(hipGetLastError());
+  AMGP_HIP(hipStreamSynchronize(s));  // tab leaves scope
+  return AMG_OK;
+}
+
+static int slice_stats(hipStream_t s, int64_t nslices, const int32_t* wd, const int32_t* lw, const int32_t* kind,
+                       unsigned long long (&st)[ST_COUNT]) {
+  graph::DevBuf<unsigned long long> stat;
+  AMGP_TRY(stat.alloc(ST_COUNT));
+  AMGP_HIP(hipMemsetAsync(stat.p, 0, sizeof(st), s));
+  hipLaunchKernelGGL(k_slice_stats, dim3(std::min(256u, grid_for(nslices))), dim3(kBlock), 0, s, nslices, wd, lw, kind,
+                     stat.p);
+  AMGP_HIP(hipMemcpyAsync(st, stat.p, sizeof(st), hipMemcpyDeviceToHost, s));
+  AMGP_HIP(hipStreamSynchronize(s));
+  return AMG_OK;
+}
+
 // Offset-aligned sliced ELL (one row per lane) when every slice has at most 64 distinct column
 // offsets and the layout is at most 10% larger than the packed one; AMG_EINVAL otherwise.
 int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
-                      Ell<double>* out, const int32_t* anchor, int astride, int64_t ncols, bool any_size) {
+                      Ell<double>* out, const int32_t* anchor, int astride, int64_t ncols, bool any_size,
+                      bool pairs) {
   using graph::DevBuf;
   const int64_t nslices = (n + kSlice - 1) / kSlice;
   // per slice: the sorted offsets (64), their count, the packed width, the kind
-  DevBuf<int32_t> buf;
+  DevBuf<int32_t> buf, buf2;
   AMGP_TRY(buf.alloc(nslices * (kSlice + 3)));
   int32_t *offs = buf.p, *wd = offs + nslices * kSlice, *lw = wd + nslices, *kind = lw + nslices;
   const bool try_uniform = n < kUniformMaxRows && (ncols < 0 ? n : ncols) < kUniformMaxRows;
-  hipLaunchKernelGGL(k_slice_layout<false>, dim3((unsigned)nslices), dim3(kWave), 0, s, n, ptr, col, val, anchor,
+  hipLaunchKernelGGL((k_slice_layout<false, 1>), dim3((unsigned)nslices), dim3(kWave), 0, s, n, ptr, col, val, anchor,
                      astride, offs, wd, lw, try_uniform ? kind : nullptr, 0, nullptr, nullptr, nullptr);
-  DevBuf<unsigned long long> stat;
-  AMGP_TRY(stat.alloc(ST_COUNT));
   unsigned long long st[ST_COUNT];
-  AMGP_HIP(hipMemsetAsync(stat.p, 0, sizeof(st), s));
-  hipLaunchKernelGGL(k_slice_stats, dim3(std::min(256u, grid_for(nslices))), dim3(kBlock), 0, s, nslices, wd, lw,
-                     try_uniform ? kind : nullptr, stat.p);
-  AMGP_HIP(hipMemcpyAsync(st, stat.p, sizeof(st), hipMemcpyDeviceToHost, s));
-  AMGP_HIP(hipStreamSynchronize(s));
+  AMGP_TRY(slice_stats(s, nslices, wd, lw, try_uniform ? kind : nullptr, st));
   if (st[ST_OVER]) return AMG_EINVAL;
   const int64_t aligned = (int64_t)st[ST_ALIGNED] * kSlice, packed = (int64_t)st[ST_PACKED] * kSlice;
-  const int64_t uniform = (int64_t)st[ST_UNIFORM];
-  const int wmax = std::max(1, (int)st[ST_WIDEST]);
   if ((!any_size && aligned > packed + packed / 10) || aligned >= (int64_t)INT32_MAX) return AMG_EINVAL;
-  const bool compact = 2 * uniform >= nslices;
   Ell<double> e;
   e.n = n;
   e.ncols = ncols < 0 ? n : ncols;
@@ -825,44 +932,39 @@ int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_
   e.nslices = nslices;
   e.padded = aligned;
   const int rc = [&]() -> int {
+    const bool square = !anchor && e.ncols == n;
+    const bool compact = 2 * (int64_t)st[ST_UNIFORM] >= nslices;
+    if (compact && square && pairs && n >= kPairMinRows) {
+      // the operator itself: slices of 128 rows, two rows per lane, where half of those are uniform too
+      // (not where every second slice of 64 rows has a line's end in it with a value of its own)
+      const int64_t ns = (n + 2 * kSlice - 1) / (2 * kSlice);
+      AMGP_TRY(buf2.alloc(ns * (kSlice + 3)));
+      int32_t *offs2 = buf2.p, *wd2 = offs2 + ns * kSlice, *lw2 = wd2 + ns, *kind2 = lw2 + ns;
+      hipLaunchKernelGGL((k_slice_layout<false, 2>), dim3((unsigned)ns), dim3(kWave), 0, s, n, ptr, col, val, anchor,
+                         astride, offs2, wd2, lw2, kind2, 0, nullptr, nullptr, nullptr);
+      unsigned long long st2[ST_COUNT];
+      AMGP_TRY(slice_stats(s, ns, wd2, lw2, kind2, st2));
+      if (!st2[ST_OVER] && 2 * (int64_t)st2[ST_UNIFORM] >= ns) {
+        e.nslices = ns;
+        AMGP_TRY(build_patterns(s, 2, n, ptr, col, val, anchor, astride, ns, offs2, wd2, kind2,
+                                std::max(1, (int)st2[ST_WIDEST]), (int64_t)st2[ST_UNIFORM], &e));
+        if (keep_malloc(&e.val, sizeof(double) * std::max<int64_t>(e.dense, 1)) != hipSuccess ||
+            keep_malloc(&e.doff, sizeof(int32_t) * std::max<int64_t>(e.dense / (2 * kSlice), 1)) != hipSuccess)
+          return AMG_ENOMEM;
+        AMGP_HIP(hipMemsetAsync(e.doff, 0, sizeof(int32_t) * (e.dense / (2 * kSlice)), s));
+        if (e.dense > 0)
+          hipLaunchKernelGGL(k_ell_fill_pairs, dim3(grid_for(ns * 2 * kSlice)), dim3(kBlock), 0, s, n, ptr, col, val,
+                             offs2, e.desc, e.val, e.doff);
+        AMGP_HIP(hipGetLastError());
+        AMGP_HIP(hipStreamSynchronize(s));
+        return AMG_OK;
+      }
+    }
     if (compact) {
-      unsigned cap = 64;
-      while (cap < 2 * nslices + 2) cap *= 2;  // its slices' room serves two scans of nslices + 1 later
-      // per slice and step the value and the mask, per slice the hash; the table's keys, then its slices, and rep
-      DevBuf<unsigned long long> tab;
-      AMGP_TRY(tab.alloc(nslices * (2 * wmax + 1) + cap + (cap + nslices + 1) / 2));
-      unsigned long long *vtab = tab.p, *mtab = vtab + nslices * wmax, *hash = mtab + nslices * wmax,
-                         *keys = hash + nslices;
-      int32_t *first = reinterpret_cast<int32_t*>(keys + cap), *rep = first + cap;
-      hipLaunchKernelGGL(k_slice_layout<true>, dim3((unsigned)nslices), dim3(kWave), 0, s, n, ptr, col, val, anchor,
-                         astride, offs, wd, nullptr, kind, wmax, vtab, mtab, hash);
-      AMGP_HIP(hipMemsetAsync(keys, 0, sizeof(unsigned long long) * cap, s));
-      AMGP_HIP(hipMemsetAsync(first, 0x7f, sizeof(int32_t) * cap, s));
-      hipLaunchKernelGGL(k_pattern_insert, dim3(grid_for(nslices)), dim3(kBlock), 0, s, nslices, kind, hash, cap, keys,
-                         first);
-      hipLaunchKernelGGL(k_pattern_resolve, dim3(grid_for(nslices)), dim3(kBlock), 0, s, nslices, kind, hash, cap, keys,
-                         first, offs, wd, wmax, vtab, mtab, rep);
-      // where every slice begins among the stored values or the patterns' steps (the packed widths and
-      // the table's slices are done with)
-      int32_t *dbeg = first, *pbeg = first + nslices + 1;
-      hipLaunchKernelGGL(k_slice_store, dim3(grid_for(nslices)), dim3(kBlock), 0, s, nslices, wd, kind, rep, dbeg, pbeg);
-      int rc2 = AMG_OK;
-      e.dense = scan_ptr(s, nslices, dbeg, dbeg, &rc2) * kSlice;
-      AMGP_TRY(rc2);
-      e.npat = scan_ptr(s, nslices, pbeg, pbeg, &rc2);
-      AMGP_TRY(rc2);
-      e.patterned = uniform;
-      if (keep_malloc(&e.desc, sizeof(int2) * nslices) != hipSuccess ||
-          keep_malloc(&e.pat, (20 * e.npat + 7) / 8 * 8) != hipSuccess)
-        return AMG_ENOMEM;
-      hipLaunchKernelGGL(k_slice_desc, dim3(grid_for(nslices)), dim3(kBlock), 0, s, nslices, wd, kind, rep, dbeg, pbeg,
-                         e.desc);
-      hipLaunchKernelGGL(k_pattern_write, dim3(grid_for(nslices * kSlice)), dim3(kBlock), 0, s, nslices, rep, e.desc,
-                         offs, wmax, vtab, mtab, (int)e.npat, e.pat);
-      AMGP_HIP(hipGetLastError());
-      AMGP_HIP(hipStreamSynchronize(s));  // tab leaves scope
+      AMGP_TRY(build_patterns(s, 1, n, ptr, col, val, anchor, astride, nslices, offs, wd, kind,
+                              std::max(1, (int)st[ST_WIDEST]), (int64_t)st[ST_UNIFORM], &e));
     } else {
-      if (!anchor && e.ncols == n && n >= kMirrorMinRows && n < kUniformMaxRows) {
+      if (square && n >= kMirrorMinRows && n < kUniformMaxRows) {
         AMGP_TRY(build_mirror(s, n, ptr, col, val, nslices, offs, wd, aligned, &e));
         if (e.mir) return AMG_OK;
       }
@@ -892,7 +994,7 @@ int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_
 }
 
 int build_ell64(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
-                Ell<double>* out, int64_t ncols, int group) {
+                Ell<double>* out, int64_t ncols, int group, bool pairs) {
   if (ncols < 0) ncols = n;
   if (group == 0) {
     // lanes per row from the mean row length: about four entries or more per lane
@@ -904,13 +1006,13 @@ int build_ell64(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col
     if (group == 4 && n >= kAlignedWideMinRows && ncols == n) {
       // a coarse stencil (27 points on Q1 boxes) on a large level: one row per lane without
       // column indices moves 4 bytes less per entry than four lanes per row with them
-      const int rc = build_ell_aligned(s, n, ptr, col, val, out);
+      const int rc = build_ell_aligned(s, n, ptr, col, val, out, nullptr, 1, -1, false, pairs);
       if (rc != AMG_EINVAL) return rc;
     }
   }
   if (group != 1 && group != 4 && group != 16 && group != 64) return AMG_EINVAL;
   if (group == 1 && ncols == n) {
-    const int rc = build_ell_aligned(s, n, ptr, col, val, out);
+    const int rc = build_ell_aligned(s, n, ptr, col, val, out, nullptr, 1, -1, false, pairs);
     if (rc != AMG_EINVAL) return rc;  // EINVAL: the slices are not offset-aligned; use the packed layout
   }
   const int R = kSlice / group;
@@ -969,13 +1071,13 @@ int build_ell32(hipStream_t s, const Ell<double>& a, Ell<float>* out) {
     AMGP_TRY(copy(&e.doff, a.doff, a.mir ? a.nslices : stored / kSlice));
     AMGP_TRY(copy(&e.mir, a.mir, a.nmir));
     AMGP_TRY(copy(&e.desc, a.desc, e.nslices));
-    AMGP_TRY(copy(&e.pat, a.pat, (20 * e.npat + 7) / 8));
+    AMGP_TRY(copy(&e.pat, a.pat, pattern_bytes(e.npat, 1) / 8));
     if (keep_malloc(&e.val, sizeof(float) * std::max<int64_t>(stored, 1)) != hipSuccess) return AMG_ENOMEM;
     if (a.desc) {
       const EllView<double> av = view(a);
       const EllView<float> ev = view(e);
-      hipLaunchKernelGGL(k_round_f32, dim3(grid_for(e.npat)), dim3(kBlock), 0, s, e.npat, av.pval(),
-                         const_cast<float*>(ev.pval()));
+      hipLaunchKernelGGL(k_round_f32, dim3(grid_for(e.npat)), dim3(kBlock), 0, s, e.npat, av.pval(1),
+                         const_cast<float*>(ev.pval(1)));
     }
     if (a.doff && !a.mir && stored > 0)
       hipLaunchKernelGGL(k_round_f32_aligned, dim3(grid_for(e.nslices * kSlice)), dim3(kBlock), 0, s, e.nslices,

@@ -343,9 +343,9 @@ __device__ __forceinline__ T pattern_sum(EllView<T> A, int beg, int w, int r, Gf
 #pragma unroll
     for (int u = 0; u < B; ++u) {
       const int q = beg + min(t + u, w - 1);
-      v[u] = A.pval()[q];
+      v[u] = A.pval(1)[q];
       if constexpr (!FULL) v[u] = __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q]) ? v[u] : T(0);
-      gv[u] = FULL ? g.at(A.poff()[q], r) : g(min(max(r + A.poff()[q], 0), A.last));
+      gv[u] = FULL ? g.at(A.poff(1)[q], r) : g(min(max(r + A.poff(1)[q], 0), A.last));
     }
 #pragma unroll
     for (int u = 0; u < B; ++u)
@@ -366,16 +366,16 @@ __device__ __forceinline__ T pattern_triples(EllView<T> A, int q, int lane, int 
   };
 #pragma unroll
   for (int u = 0; u < N; ++u) {
-    mid[u] = gather(A.poff()[q + 3 * u], 1);
+    mid[u] = gather(A.poff(1)[q + 3 * u], 1);
     end[u] = T(0);
   }
   if (((lane + 1) & (kWave - 2)) == 0) {  // lanes 0 and 63
     const int shift = lane == 0 ? 0 : 2;
 #pragma unroll
-    for (int u = 0; u < N; ++u) end[u] = gather(A.poff()[q + 3 * u], shift);
+    for (int u = 0; u < N; ++u) end[u] = gather(A.poff(1)[q + 3 * u], shift);
   }
   auto value = [&](int t) {
-    return FULL || __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q + t]) ? A.pval()[q + t] : T(0);
+    return FULL || __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q + t]) ? A.pval(1)[q + t] : T(0);
   };
 #pragma unroll
   for (int u = 0; u < N; ++u) {
@@ -938,8 +938,8 @@ __device__ __forceinline__ T ell_dot_any(EllView<T> A, int row, const T* __restr
     const int w = d.y >> 4;
     if ((d.y & 15) != SLICE_DENSE) {
       for (int t = d.x; t < d.x + w; ++t) {
-        const T v = (A.pmask()[t] >> (row & 63)) & 1 ? A.pval()[t] : T(0);
-        acc += v * x[min(max(row + A.poff()[t], 0), A.last)];
+        const T v = (A.pmask()[t] >> (row & 63)) & 1 ? A.pval(1)[t] : T(0);
+        acc += v * x[min(max(row + A.poff(1)[t], 0), A.last)];
       }
       return acc;
     }
@@ -1203,9 +1203,9 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t n, const double* _
 }
 
 // ---------------------------------------------------------------------------
-// Two rows per lane, for the levels of mirrored diagonals: a wavefront serves 128 consecutive rows,
-// lane l the rows 2 l and 2 l + 1 of them, so that values, row vectors and gathers of a pair come with
-// one load of twice the width.  Every row's products keep their order; partial sums of dot
+// Two rows per lane, for FP64 levels of mirrored diagonals and large ones of uniform slices: a
+// wavefront serves 128 consecutive rows, lane l the rows 2 l and 2 l + 1 of them, so that values, row
+// vectors and gathers of a pair come with one load of twice the width.  Every row's products keep their order; partial sums of dot
 // products cover 512 rows a block.
 // ---------------------------------------------------------------------------
 constexpr int kPair = 2;
@@ -1268,11 +1268,134 @@ __device__ __forceinline__ V2<T> mirror_pair_steps(EllView<T> A, unsigned presen
   return acc;
 }
 
-// (A g)_r and (A g)_{r + 1} for the even row r of this lane
+// Whether an offset that carries the bits of its halves is one of this lane's 64 rows (SLICE_HALVES).
+__device__ __forceinline__ bool in_half(int off) { return (off >> ((threadIdx.x >> 5) & 1)) & 1; }
+
+// The pair at columns c, c + 1 of a step with such an offset: zeros in the other half.
 template <typename T, typename Gf>
+__device__ __forceinline__ V2<T> half2(Gf g, int r, int off, int last) {
+  const V2<T> v = clamp2<T>(g, r + (off >> 2), last);
+  return in_half(off) ? v : V2<T>{T(0), T(0)};
+}
+
+// Patterns of uniform slices: as pattern_sum, with the even rows' masks and the odd rows'.
+template <int KIND, typename T, typename Gf>
+__device__ __forceinline__ V2<T> pair_pattern_sum(EllView<T> A, int beg, int w, int r, Gf g) {
+  constexpr int B = 8;
+  constexpr bool FULL = KIND == SLICE_FULL;
+  V2<T> acc{T(0), T(0)};
+  for (int t = 0; t < w; t += B) {
+    V2<T> gv[B];
+    T v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int q = beg + min(t + u, w - 1);
+      v[u] = A.pval(2)[q];
+      gv[u] = FULL ? g.at2(A.poff(2)[q], r)
+                   : KIND == SLICE_HALVES ? half2<T>(g, r, A.poff(2)[q], A.last) : clamp2<T>(g, r + A.poff(2)[q], A.last);
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      if (t + u >= w) continue;
+      const int q = beg + t + u;
+      acc.x += (FULL || __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q]) ? v[u] : T(0)) * gv[u].x;
+      acc.y += (FULL || __builtin_amdgcn_inverse_ballot_w64(A.pmask()[A.npat + q]) ? v[u] : T(0)) * gv[u].y;
+    }
+  }
+  return acc;
+}
+
+// N triples of steps at consecutive offsets from step q on: a triple costs one gather of the whole
+// wavefront (the pair of its middle step) and one of the two end lanes; the other left and right
+// neighbours are the pairs of the adjacent lanes (rows of consecutive lanes are consecutive, and so are
+// their clamped columns).  All 64 lanes are active, all 128 rows below n.
+template <int N, bool FULL, typename T, typename Gf>
+__device__ __forceinline__ V2<T> pair_triples(EllView<T> A, int q, int lane, int r, V2<T> acc, Gf g) {
+  V2<T> mid[N];
+  T end[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int off = A.poff(2)[q + 3 * u];
+    mid[u] = FULL ? g.at2(off + 1, r) : clamp2<T>(g, r + off + 1, A.last);
+    end[u] = T(0);
+  }
+  if (((lane + 1) & (kWave - 2)) == 0) {  // lanes 0 and 63: the columns before and behind the wavefront's
+    const int shift = lane == 0 ? 0 : 3;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int off = A.poff(2)[q + 3 * u];
+      end[u] = FULL ? g.at(off, r + shift) : g(min(max(r + off + shift, 0), A.last));
+    }
+  }
+  auto vx = [&](int t) {
+    return FULL || __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q + t]) ? A.pval(2)[q + t] : T(0);
+  };
+  auto vy = [&](int t) {
+    return FULL || __builtin_amdgcn_inverse_ballot_w64(A.pmask()[A.npat + q + t]) ? A.pval(2)[q + t] : T(0);
+  };
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    acc.x += vx(3 * u) * dpp_shift<kDppFromBelow>(end[u], mid[u].y);
+    acc.x += vx(3 * u + 1) * mid[u].x;
+    acc.x += vx(3 * u + 2) * mid[u].y;
+    acc.y += vy(3 * u) * mid[u].x;
+    acc.y += vy(3 * u + 1) * mid[u].y;
+    acc.y += vy(3 * u + 2) * dpp_shift<kDppFromAbove>(end[u], mid[u].x);
+  }
+  return acc;
+}
+
+template <bool FULL, typename T, typename Gf>
+__device__ __forceinline__ V2<T> pair_triples_sum(EllView<T> A, int beg, int w, int lane, int r, Gf g) {
+  V2<T> acc{T(0), T(0)};
+  int t = 0;
+  for (; t + 3 * kTripleBatch <= w; t += 3 * kTripleBatch)
+    acc = pair_triples<kTripleBatch, FULL>(A, beg + t, lane, r, acc, g);
+  for (; t < w; t += 3) acc = pair_triples<1, FULL>(A, beg + t, lane, r, acc, g);
+  return acc;
+}
+
+template <typename T, typename Gf>
+__device__ __forceinline__ V2<T> pair_dense_sum(EllView<T> A, int beg, int w, int lane, int r, Gf g) {
+  constexpr int B = 4;
+  V2<T> acc{T(0), T(0)};
+  const T* val = A.val + (int64_t)beg * kPair * kWave;
+  for (int t = 0; t < w; t += B) {
+    V2<T> gv[B], v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int q = min(t + u, w - 1);
+      v[u] = at_row2(val + (int64_t)q * kPair * kWave, kPair * lane);
+      gv[u] = half2<T>(g, r, A.doff[beg + q], A.last);
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      if (t + u >= w) continue;
+      acc.x += v[u].x * gv[u].x;
+      acc.y += v[u].y * gv[u].y;
+    }
+  }
+  return acc;
+}
+
+// (A g)_r and (A g)_{r + 1} for the even row r of this lane
+template <int V, typename T, typename Gf>
 __device__ __forceinline__ V2<T> pair_sum(EllView<T> A, int r, Gf g) {
   const int lane = threadIdx.x & (kWave - 1);
   const int r0 = __builtin_amdgcn_readfirstlane(r - kPair * lane);  // the wavefront's first row
+  if constexpr (V == V_UNIFORM) {
+    const int2 d = A.desc()[r0 >> 7];
+    const int b = __builtin_amdgcn_readfirstlane(d.x), info = __builtin_amdgcn_readfirstlane(d.y);
+    const int w = info >> 4;
+    if (info & SLICE_TRIPLES) {
+      if (info & SLICE_FULL) return pair_triples_sum<true>(A, b, w, lane, r, g);
+      return pair_triples_sum<false>(A, b, w, lane, r, g);
+    }
+    if (info & SLICE_FULL) return pair_pattern_sum<SLICE_FULL>(A, b, w, r, g);
+    if (info & SLICE_MASKED) return pair_pattern_sum<SLICE_MASKED>(A, b, w, r, g);
+    if (info & SLICE_HALVES) return pair_pattern_sum<SLICE_HALVES>(A, b, w, r, g);
+    return pair_dense_sum(A, b, w, lane, r, g);
+  }
   const MirrorStep* st = A.mir();
   const int s = r0 >> 6, s1 = min(s + 1, A.last >> 6);  // its two slices
   const unsigned p0 = __builtin_amdgcn_readfirstlane(A.doff[s]), p1 = __builtin_amdgcn_readfirstlane(A.doff[s1]);
@@ -1294,7 +1417,7 @@ __device__ __forceinline__ void for_pair(int64_t n, F&& f) {
     f(std::false_type(), r);
 }
 
-template <typename T, int MODE, bool STORE, bool NT, bool XUPD, bool WHOLE>
+template <typename T, int MODE, bool STORE, bool NT, bool XUPD, bool WHOLE, int V>
 __device__ __forceinline__ V2<T> pair_step(int64_t i, int64_t n, EllView<T> A, const T* __restrict__ minv,
                                            const T* __restrict__ gold, T* __restrict__ gnew, const T* rin, T* rout,
                                            T* __restrict__ x, T alpha, T c, T w, T wprev, Wt wv, Wt wpv, Prol<T> pr) {
@@ -1302,7 +1425,7 @@ __device__ __forceinline__ V2<T> pair_step(int64_t i, int64_t n, EllView<T> A, c
               ri = ld_pair<NT, WHOLE>(rin, i, n);
   V2<T> xi{T(0), T(0)};
   if constexpr (XUPD) xi = ld_pair<NT, WHOLE>((const T*)x, i, n);
-  const V2<T> ag = pair_sum(A, (int)i, GatherVec<T>{gold});
+  const V2<T> ag = pair_sum<V>(A, (int)i, GatherVec<T>{gold});
   V2<T> rn, gn, xn{T(0), T(0)};
   rn.x = (MODE == 0) ? ri.x - ag.x : ri.x - mi.x * ag.x;
   rn.y = (MODE == 0) ? ri.y - ag.y : ri.y - mi.y * ag.y;
@@ -1326,28 +1449,28 @@ __device__ __forceinline__ V2<T> pair_step(int64_t i, int64_t n, EllView<T> A, c
   return xn;
 }
 
-template <typename T, int MODE, bool STORE, bool NT>
+template <typename T, int MODE, bool STORE, bool NT, int V>
 __global__ __launch_bounds__(kBlock) void k_pair_fused(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                        const T* __restrict__ gold, T* __restrict__ gnew, const T* rin,
                                                        T* rout, T* __restrict__ x, T alpha, T c, T w, T wprev, Wt wv,
                                                        Wt wpv, Prol<T> pr) {
   for_pair(n, [&](auto whole, int64_t i) {
-    pair_step<T, MODE, STORE, NT, true, decltype(whole)::value>(i, n, A, minv, gold, gnew, rin, rout, x, alpha, c, w,
+    pair_step<T, MODE, STORE, NT, true, decltype(whole)::value, V>(i, n, A, minv, gold, gnew, rin, rout, x, alpha, c, w,
                                                                 wprev, wv, wpv, pr);
   });
 }
 
-template <typename T, int MODE, bool NT>
+template <typename T, int MODE, bool NT, int V>
 __global__ __launch_bounds__(kBlock) void k_pair_fused_keep_x(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                               const T* __restrict__ gold, T* __restrict__ gnew,
                                                               const T* rin, T* rout, T alpha, T c) {
   for_pair(n, [&](auto whole, int64_t i) {
-    pair_step<T, MODE, true, NT, false, decltype(whole)::value>(i, n, A, minv, gold, gnew, rin, rout, nullptr, alpha, c,
+    pair_step<T, MODE, true, NT, false, decltype(whole)::value, V>(i, n, A, minv, gold, gnew, rin, rout, nullptr, alpha, c,
                                                                 T(0), T(0), Wt(), Wt(), Prol<T>());
   });
 }
 
-template <typename T, int MODE, bool NT>
+template <typename T, int MODE, bool NT, int V>
 __global__ __launch_bounds__(kBlock) void k_pair_fused_dot(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                            const T* __restrict__ gold, const T* rin,
                                                            T* __restrict__ x, T alpha, T c, T w, T wprev, Wt wv,
@@ -1357,7 +1480,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_fused_dot(int64_t n, EllView<T>
   double v = 0.0, u = 0.0;
   for_pair(n, [&](auto whole, int64_t i) {
     constexpr bool WHOLE = decltype(whole)::value;
-    const V2<T> xn = pair_step<T, MODE, false, NT, true, WHOLE>(i, n, A, minv, gold, nullptr, rin, nullptr, x, alpha, c,
+    const V2<T> xn = pair_step<T, MODE, false, NT, true, WHOLE, V>(i, n, A, minv, gold, nullptr, rin, nullptr, x, alpha, c,
                                                                 w, wprev, wv, wpv, pr);
     const V2<double> d = ld_pair<NT, WHOLE>(dr, i, n);  // 0 past n
     v = d.x * (double)xn.x + d.y * (double)xn.y;
@@ -1375,7 +1498,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_fused_dot(int64_t n, EllView<T>
   }
 }
 
-template <typename T, int MODE, bool STORE, bool NT, bool U>
+template <typename T, int MODE, bool STORE, bool NT, bool U, int V>
 __global__ __launch_bounds__(kBlock) void k_pair_first2_zero(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                              const T* __restrict__ b, T* __restrict__ gnew,
                                                              T* __restrict__ r, T* __restrict__ x, T c1, T alpha, T c,
@@ -1383,7 +1506,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_first2_zero(int64_t n, EllView<
   for_pair(n, [&](auto whole, int64_t i) {
     constexpr bool WHOLE = decltype(whole)::value;
     const V2<T> mi = ld_pair<false, WHOLE>(minv, i, n), bi = ld_pair<false, WHOLE>(b, i, n);
-    const V2<T> ag = pair_sum(A, (int)i, FirstDir<T, MODE, U>{minv, b, u, c1});
+    const V2<T> ag = pair_sum<V>(A, (int)i, FirstDir<T, MODE, U>{minv, b, u, c1});
     auto row = [&](T m, T bb, T a, T u1, T u2, T& xo, T& ro, T& go) {
       if (MODE == 0) {
         const T g1 = c1 * (m * bb);
@@ -1410,7 +1533,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_first2_zero(int64_t n, EllView<
 }
 
 // PROL: on x + P x_c
-template <typename T, int MODE, bool NT, bool PROL>
+template <typename T, int MODE, bool NT, bool PROL, int V>
 __global__ __launch_bounds__(kBlock) void k_pair_first_res(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                            const T* __restrict__ b, const T* __restrict__ x,
                                                            Prol<T> pr, T* __restrict__ r, T* __restrict__ g, T c) {
@@ -1419,9 +1542,9 @@ __global__ __launch_bounds__(kBlock) void k_pair_first_res(int64_t n, EllView<T>
     const V2<T> bi = ld_pair<NT, WHOLE>(b, i, n), mi = ld_pair<NT, WHOLE>(minv, i, n);
     V2<T> ax;
     if constexpr (PROL)
-      ax = pair_sum(A, (int)i, GatherProl<T>{x, pr.agg, pr.xc});
+      ax = pair_sum<V>(A, (int)i, GatherProl<T>{x, pr.agg, pr.xc});
     else
-      ax = pair_sum(A, (int)i, GatherVec<T>{x});
+      ax = pair_sum<V>(A, (int)i, GatherVec<T>{x});
     V2<T> rn{bi.x - ax.x, bi.y - ax.y}, gn;
     if (MODE == 0) {
       gn = V2<T>{c * (mi.x * rn.x), c * (mi.y * rn.y)};
@@ -1435,12 +1558,12 @@ __global__ __launch_bounds__(kBlock) void k_pair_first_res(int64_t n, EllView<T>
 }
 
 // y = A x, or y = b - A x (b given)
-template <typename T, bool NT, bool RES>
+template <typename T, bool NT, bool RES, int V>
 __global__ __launch_bounds__(kBlock) void k_pair_spmv(int64_t n, EllView<T> A, const T* __restrict__ b,
                                                       const T* __restrict__ x, T* __restrict__ y) {
   for_pair(n, [&](auto whole, int64_t i) {
     constexpr bool WHOLE = decltype(whole)::value;
-    const V2<T> v = pair_sum(A, (int)i, GatherVec<T>{x});
+    const V2<T> v = pair_sum<V>(A, (int)i, GatherVec<T>{x});
     if constexpr (RES) {
       const V2<T> bi = ld_pair<NT, WHOLE>(b, i, n);
       st_pair<false, WHOLE>(y, i, n, V2<T>{bi.x - v.x, bi.y - v.y});
@@ -1450,20 +1573,20 @@ __global__ __launch_bounds__(kBlock) void k_pair_spmv(int64_t n, EllView<T> A, c
   });
 }
 
-template <typename T>
+template <typename T, int V>
 __global__ __launch_bounds__(kBlock) void k_pair_jacobi(int64_t n, EllView<T> A, const T* __restrict__ minv,
                                                         const T* __restrict__ b, const T* __restrict__ xold,
                                                         T* __restrict__ xnew) {
   for_pair(n, [&](auto whole, int64_t i) {
     constexpr bool WHOLE = decltype(whole)::value;
-    const V2<T> ax = pair_sum(A, (int)i, GatherVec<T>{xold});
+    const V2<T> ax = pair_sum<V>(A, (int)i, GatherVec<T>{xold});
     const V2<T> xo = ld_pair<false, WHOLE>(xold, i, n), mi = ld_pair<false, WHOLE>(minv, i, n),
                 bi = ld_pair<false, WHOLE>(b, i, n);
     st_pair<false, WHOLE>(xnew, i, n, V2<T>{xo.x + mi.x * (bi.x - ax.x), xo.y + mi.y * (bi.y - ax.y)});
   });
 }
 
-template <bool NT, typename TZ, bool PRE>
+template <bool NT, typename TZ, bool PRE, int V>
 __global__ __launch_bounds__(kBlock) void k_pair_spmv_dot_p(int64_t n, EllView<double> A,
                                                             const double* __restrict__ scal, const TZ* __restrict__ z,
                                                             const double* __restrict__ pold, double* pnew,
@@ -1475,7 +1598,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_spmv_dot_p(int64_t n, EllView<d
     constexpr bool WHOLE = decltype(whole)::value;
     V2<double> pi;
     if constexpr (PRE) pi = ld_pair<false, WHOLE>((const double*)pnew, i, n);
-    const V2<double> a = pair_sum(A, (int)i, Direction<TZ, PRE>{z, PRE ? pnew : pold, beta});
+    const V2<double> a = pair_sum<V>(A, (int)i, Direction<TZ, PRE>{z, PRE ? pnew : pold, beta});
     if constexpr (!PRE) {
       const V2<double> po = ld_pair<false, WHOLE>(pold, i, n);
       const V2<TZ> zi = ld_pair<false, WHOLE>(z, i, n);
@@ -1661,21 +1784,28 @@ void with_mode_store(int mode, bool store, F&& f) {
     f(M1(), std::false_type());
 }
 
-// Levels served by two rows per lane: f(NT) with the launch shape.
-template <typename T, typename F>
-int with_pairs(const Ell<T>& A, F&& f) {
+// Levels served by two rows per lane: f(NT, V, launch shape).
+template <typename F>
+int with_pairs(const Ell<double>& A, F&& f) {
   const dim3 gr((grid_for((A.n + 1) / 2) + kXcd - 1) / kXcd * kXcd);
-  if (streamed(xcd_grid(A.n)))
-    f(std::true_type(), gr);
+  auto go = [&](auto v) {
+    if (streamed(xcd_grid(A.n)))
+      f(std::true_type(), v, gr);
+    else
+      f(std::false_type(), v, gr);
+  };
+  if (A.mir)
+    go(std::integral_constant<int, V_MIRROR>());
   else
-    f(std::false_type(), gr);
-  return hipGetLastError() == hipSuccess ? AMG_OK : AMG_EHIP;
+    go(std::integral_constant<int, V_UNIFORM>());
+  return LAUNCH_OK();
 }
+
 // FP64 levels of mirrored diagonals: loads of 16 bytes instead of 8 for every stream of a row (256^3
 // solve 87.6 -> 79.1 ms, degree-5 application on 203x187x171 rows 515 -> 471 us).  With the FP32
 // hierarchy, whose pairs take 8 bytes, one row per lane is the faster (52.5 against 54.4 ms; 32 x 64^3
-// training step 6.15 against 6.65 ms).
-inline bool paired(const Ell<double>& A) { return A.mir != nullptr; }
+// training step 6.15 against 6.65 ms).  Uniform slices: see kPairMinRows.
+inline bool paired(const Ell<double>& A) { return A.mir || (A.desc && A.rpl == 2); }
 
 // The levels whose merged first two steps can read u = M^{-1} b instead of gathering M^{-1} and b
 bool first2_takes_u(const Ell<double>& A) { return streamed(xcd_grid(A.n)) && wide(A); }
@@ -1699,8 +1829,8 @@ int with_group(int group, F&& f) {
 template <typename T>
 int launch_spmv(hipStream_t s, const Ell<T>& A, const T* x, T* y) {
     if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
-      hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, false>), gr, dim3(kBlock), 0, s, A.n, view(A),
+    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
+      hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, false, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A),
                          (const T*)nullptr, x, y);
     });
   return with_group(A.group, [&](auto gc) {
@@ -1719,8 +1849,8 @@ int launch_spmv(hipStream_t s, const Ell<T>& A, const T* x, T* y) {
 template <typename T>
 int launch_residual(hipStream_t s, const Ell<T>& A, const T* b, const T* x, T* r) {
     if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
-      hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, true>), gr, dim3(kBlock), 0, s, A.n, view(A), b, x, r);
+    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
+      hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, true, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A), b, x, r);
     });
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
@@ -1784,10 +1914,10 @@ int launch_first2_zero(hipStream_t s, int mode, bool store, const Ell<T>& A, con
                        T* r, T* x, double c1, double alpha, double c, double w1, double w2, Wt w1v, Wt w2v,
                        const T* u) {
     if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
       auto go = [&](auto m, auto st, auto hu) {
         hipLaunchKernelGGL((k_pair_first2_zero<T, decltype(m)::value, decltype(st)::value, decltype(nt)::value,
-                                               decltype(hu)::value>),
+                                               decltype(hu)::value, decltype(v)::value>),
                            gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, gnew, r, x, (T)c1, (T)alpha, (T)c, (T)w1,
                            (T)w2, w1v, w2v, u);
       };
@@ -1836,9 +1966,9 @@ template <typename T>
 int launch_first_res(hipStream_t s, int mode, const Ell<T>& A, const T* minv, const T* b, const T* x, T* r,
                      T* g, double c, Prol<T> pr) {
     if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
       auto go = [&](auto m, auto prol) {
-        hipLaunchKernelGGL((k_pair_first_res<T, decltype(m)::value, decltype(nt)::value, decltype(prol)::value>), gr,
+        hipLaunchKernelGGL((k_pair_first_res<T, decltype(m)::value, decltype(nt)::value, decltype(prol)::value, decltype(v)::value>), gr,
                            dim3(kBlock), 0, s, A.n, view(A), minv, b, x, pr, r, g, (T)c);
       };
       with_mode_store(mode, pr.agg != nullptr, go);
@@ -1899,14 +2029,14 @@ int launch_fused(hipStream_t s, int mode, bool store, const Ell<T>& A, const T* 
                  const T* rin, T* rout, T* x, double alpha, double c, double w, double wprev, Wt wv, Wt wpv,
                  Prol<T> pr) {
     if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
       with_mode_store(mode, store, [&](auto m, auto st) {
         constexpr int MODE = decltype(m)::value;
         if (!x)  // a stored step that leaves x alone
-          hipLaunchKernelGGL((k_pair_fused_keep_x<T, MODE, decltype(nt)::value>), gr, dim3(kBlock), 0, s, A.n, view(A),
+          hipLaunchKernelGGL((k_pair_fused_keep_x<T, MODE, decltype(nt)::value, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A),
                              minv, gold, gnew, rin, rout, (T)alpha, (T)c);
         else
-          hipLaunchKernelGGL((k_pair_fused<T, MODE, decltype(st)::value, decltype(nt)::value>), gr, dim3(kBlock), 0, s,
+          hipLaunchKernelGGL((k_pair_fused<T, MODE, decltype(st)::value, decltype(nt)::value, decltype(v)::value>), gr, dim3(kBlock), 0, s,
                              A.n, view(A), minv, gold, gnew, rin, rout, x, (T)alpha, (T)c, (T)w, (T)wprev, wv, wpv, pr);
       });
     });
@@ -1930,9 +2060,9 @@ int launch_fused_dot(hipStream_t s, int mode, const Ell<T>& A, const T* minv, co
                      double alpha, double c, double w, double wprev, Wt wv, Wt wpv, Prol<T> pr, const double* dr,
                      const double* drold, double* partial, unsigned* nblocks) {
     if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, dim3 gr) {
+    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
       with_mode_store(mode, false, [&](auto m, auto) {
-        hipLaunchKernelGGL((k_pair_fused_dot<T, decltype(m)::value, decltype(nt)::value>), gr, dim3(kBlock), 0, s, A.n,
+        hipLaunchKernelGGL((k_pair_fused_dot<T, decltype(m)::value, decltype(nt)::value, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n,
                            view(A), minv, gold, rin, x, (T)alpha, (T)c, (T)w, (T)wprev, wv, wpv, pr, dr, drold,
                            partial);
       });
@@ -1963,8 +2093,8 @@ template int launch_fused_dot<float>(hipStream_t, int, const Ell<float>&, const 
 template <typename T>
 int launch_jacobi(hipStream_t s, const Ell<T>& A, const T* minv, const T* b, const T* xold, T* xnew) {
     if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto, dim3 gr) {
-      hipLaunchKernelGGL(k_pair_jacobi<T>, gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, xold, xnew);
+    if (paired(A)) return with_pairs(A, [&](auto, auto v, dim3 gr) {
+      hipLaunchKernelGGL((k_pair_jacobi<T, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, xold, xnew);
     });
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
@@ -2090,14 +2220,13 @@ template int launch_dot2<float>(hipStream_t, int64_t, const double*, const float
 template <typename TZ>
 int launch_spmv_dot_p(hipStream_t s, const Ell<double>& A, const double* scal, const TZ* z, const double* pold,
                       double* pnew, double* q, double* partial, double* x, unsigned* nblocks) {
-    if (paired(A))
-    return with_pairs(A, [&](auto nt, dim3 gr) {
+  if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
       constexpr bool NT = decltype(nt)::value;
       if constexpr (NT) {
         const unsigned g = xcd_grid(A.n);
         hipLaunchKernelGGL((k_form_p<true, TZ>), dim3(g), dim3(kBlock), 0, s, A.n, scal, z, pold, pnew, x);
       }
-      hipLaunchKernelGGL((k_pair_spmv_dot_p<NT, TZ, NT>), gr, dim3(kBlock), 0, s, A.n, view(A), scal, z, pold, pnew, q,
+      hipLaunchKernelGGL((k_pair_spmv_dot_p<NT, TZ, NT, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A), scal, z, pold, pnew, q,
                          partial, NT ? nullptr : x);
       *nblocks = gr.x;
     });

@@ -771,7 +771,8 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
     AMGP_TRY(read_flags(h, s, fl));
     if (fl[F_NOTSPD]) return AMG_ENOTSPD;
     // the fine level keeps one row per lane (the CG kernels read it); coarse levels choose
-    AMGP_TRY(build_ell64(s, L.n, L.csr_ptr, L.csr_col, L.csr_val, &L.A64, -1, h->lv.size() == 1 ? 1 : 0));
+    AMGP_TRY(build_ell64(s, L.n, L.csr_ptr, L.csr_col, L.csr_val, &L.A64, -1, h->lv.size() == 1 ? 1 : 0,
+                         h->precision == AMG_FP64));
     const int64_t per = L.n / h->nbatch;
     if (per <= h->max_coarse) break;
     if (h->aggregation == AMG_AGG_MATCHING) {
@@ -1138,7 +1139,7 @@ int amg_level_patterns(const amg_handle* h, int level, int restriction, int64_t*
   if (restriction && (L.general || !L.R64.val)) return AMG_EINVAL;
   const amgp::Ell<double>& A = restriction ? L.R64 : L.A64;
   if (h_values) *h_values = A.desc || A.mir ? A.dense : A.padded;
-  if (h_slices) *h_slices = A.patterned;
+  if (h_slices) *h_slices = std::min<int64_t>(A.patterned * A.rpl, (A.n + amgp::kSlice - 1) / amgp::kSlice);
   if (h_steps) *h_steps = A.npat;
   return AMG_OK;
 }

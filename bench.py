@@ -10,7 +10,7 @@ in HBM (setup excluded, reported separately).  A step is one such solve.
 value        = bytes one solve must move in the storage layouts the kernels use
                (summed from the per-kernel models below over the launches of one
                solve) / the solve's wall time, GB/s;
-roofline     = the fine-level fused recurrence step (k_fused<double,0,true,true,1,2>):
+roofline     = the fine-level fused recurrence step (k_pair_fused<double,0,true,true,2>):
                the bytes it must move per launch / its average duration, timed
                here with events on the launch stream (degree-5 minus degree-4
                and degree-7 minus degree-6 smoother applications from x = 0,
@@ -51,6 +51,7 @@ PEAK_HBM = 8000.0  # GB/s, MI355X HBM3E
 KIND_NAMES = {0: "l1jacobi", 1: "cheb4", 2: "optcheb4", 3: "optcheb1"}
 FUSED_PROLONG_MAX_ROWS = 1 << 20  # box levels up to this size carry the prolongation in the smoother
 STREAM_MIN_BLOCKS = 12288  # levels above this many 256-row blocks take the streaming kernels
+PAIR_MIN_ROWS = 1 << 22  # FP64 levels of uniform slices with this many rows are served two rows per lane
 WIDE_MIN_STEPS = 24  # streaming offset-aligned levels with this many stored steps per row take wide batches
 
 
@@ -208,8 +209,8 @@ def fused_step_time(amg, h, kind, bd, xs, stream, reps=10, apply=None):
     """Average duration (ms) of the fine level's stored fused step that updates x, from smoother
     applications on level 0 from x = 0 timed with events on the launch stream.  x is updated on
     every other step, so degree 5 minus degree 4 and degree 7 minus degree 6 each add one such
-    step (k_fused<...> in a kernel trace; the steps between them, which leave x alone, are
-    k_fused_keep_x).  apply: the smoother entry (smoother_apply, or smoother_apply_f32 with
+    step (k_fused<...> or k_pair_fused<...> in a kernel trace; the steps between them, which leave x alone, are
+    k_fused_keep_x or k_pair_fused_keep_x).  apply: the smoother entry (smoother_apply, or smoother_apply_f32 with
     float32 vectors on an FP32 hierarchy)."""
     apply = apply or amg.smoother_apply
 
@@ -575,6 +576,11 @@ def main():
     wide = streams and aligned and lanes == 1 and padded >= WIDE_MIN_STEPS * n0
     values, patterned, steps = amg.amg_level_patterns(h, 0)
     variant = 2 if patterned else int(wide)  # slices: narrow, wide, uniform
+    # large levels of uniform slices and mirrored diagonals are served two rows per lane
+    mirrored = aligned and not patterned and values < padded
+    pairs = mirrored or (patterned and n0 >= PAIR_MIN_ROWS)
+    kernel = (f"k_pair_fused<double,0,true,{str(streams).lower()},{3 if mirrored else 2}>" if pairs else
+              f"k_fused<double,0,true,{str(streams).lower()},1,{variant}>")
     u_path = wide and args.kind != 0 and args.degree >= 2
     value = solve_bytes(lv64, M0, 8, args.kind, args.degree, it, False, u_path) / (ms * 1e-3) / 1e9
 
@@ -589,8 +595,7 @@ def main():
     ceil = ceiling(amg, stream)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM, "unit": "GB/s",
                 "frac": round(achieved / PEAK_HBM, 4), "traffic": None,
-                "kernel": f"k_fused<double,0,true,{str(streams).lower()},1,{variant}> (fine level, "
-                          f"{args.workload} {args.size}^3)",
+                "kernel": f"{kernel} (fine level, {args.workload} {args.size}^3)",
                 "bytes_per_launch": int(step_bytes), "avg_launch_us": round(t_step * 1e3, 2),
                 "layout": {"entries": int(padded), "stored_entries": int(values), "uniform_slices": int(patterned),
                            "pattern_steps": int(steps), "lanes_per_row": lanes, "offset_aligned": aligned,
@@ -721,8 +726,8 @@ def measured_traffic(size):
         return None
     try:
         src = open(os.path.join(ROOT, "paper_2407_09848_amd", "csrc", "kernels_sparse.hip")).read()
-        a = src.index("\n", src.index("// BEGIN fused-step")) + 1
-        digest = hashlib.sha256(src[a:src.index("// END fused-step")].encode()).hexdigest()[:16]
+        regions = re.findall(r"// BEGIN fused-step[^\n]*\n(.*?)// END fused-step", src, re.S)
+        digest = hashlib.sha256("".join(regions).encode()).hexdigest()[:16]
         prof = open(path).read()
         if re.search(r"sha256 prefix: (\w+)", prof).group(1) != digest:
             return None

@@ -1202,6 +1202,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t n, const double* _
   if (threadIdx.x == 0) partial[logical_block()] = s;
 }
 
+// BEGIN fused-step (two rows per lane)
 // ---------------------------------------------------------------------------
 // Two rows per lane, for FP64 levels of mirrored diagonals and large ones of uniform slices: a
 // wavefront serves 128 consecutive rows, lane l the rows 2 l and 2 l + 1 of them, so that values, row
@@ -1459,6 +1460,8 @@ __global__ __launch_bounds__(kBlock) void k_pair_fused(int64_t n, EllView<T> A, 
                                                                 wprev, wv, wpv, pr);
   });
 }
+
+// END fused-step
 
 template <typename T, int MODE, bool NT, int V>
 __global__ __launch_bounds__(kBlock) void k_pair_fused_keep_x(int64_t n, EllView<T> A, const T* __restrict__ minv,

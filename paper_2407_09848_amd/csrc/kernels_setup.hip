@@ -123,8 +123,8 @@ __global__ void k_ell_fill(int64_t n, int64_t ncols, int64_t nslices, int G, con
 }
 
 // Layout of every slice of 64 RPL rows (RPL rows per lane of the kernels), one wavefront per slice,
-// its lanes on consecutive entries of the slice's rows (contiguous in CSR, so the loads coalesce; one row per lane instead read 20 KB a
-// wavefront through its own cache lines, 33 ms against 5 ms for the kinds of the 27-point 320^3
+// its lanes on consecutive entries of the slice's rows (contiguous in CSR, so the loads coalesce; one
+// row per lane instead read 20 KB a wavefront through its own cache lines, 33 ms against 5 ms for the kinds of the 27-point 320^3
 // matrix).  The slice's distinct column offsets (col - row, or col - anchor[row * astride]) go into
 // an LDS hash set.
 //
@@ -329,7 +329,8 @@ __global__ void k_pattern_insert(int64_t nslices, const int32_t* __restrict__ ki
 __global__ void k_pattern_resolve(int64_t nslices, const int32_t* __restrict__ kind,
                                   const unsigned long long* __restrict__ hash, unsigned cap,
                                   const unsigned long long* __restrict__ keys, const int32_t* __restrict__ first,
-                                  const int32_t* __restrict__ offs, const int32_t* __restrict__ width, int rpl, int stride,
+                                  const int32_t* __restrict__ offs, const int32_t* __restrict__ width, int rpl,
+                                  int stride,
                                   const unsigned long long* __restrict__ vtab,
                                   const unsigned long long* __restrict__ mtab, int32_t* __restrict__ rep) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

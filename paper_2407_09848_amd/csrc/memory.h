@@ -25,9 +25,14 @@ class Arena {
     }
     for (Slab& s : slabs_)
       if (s.size - s.used >= need) return take(s, p, need);
-    const size_t size = std::max(need, std::min(kMaxSlab, std::max(kMinSlab, total_)));
+    size_t size = std::max(need, std::min(kMaxSlab, std::max(kMinSlab, total_)));
     void* base = nullptr;
-    const hipError_t e = hipMalloc(&base, size);
+    hipError_t e = hipMalloc(&base, size);
+    if (e != hipSuccess && size > need) {  // no room for a whole slab
+      (void)hipGetLastError();
+      size = need;
+      e = hipMalloc(&base, size);
+    }
     if (e != hipSuccess) return e;
     total_ += size;
     slabs_.push_back(Slab{static_cast<char*>(base), size, 0});

@@ -84,7 +84,11 @@ class MemoryScope {
     return scope;
   }
 
-  hipError_t keep(void** p, size_t bytes) { return arena_->alloc(p, bytes); }
+  hipError_t keep(void** p, size_t bytes) {
+    hipError_t e = arena_->alloc(p, bytes);
+    if (e != hipSuccess && drop_idle()) e = arena_->alloc(p, bytes);
+    return e;
+  }
 
   hipError_t take(void** p, size_t bytes) {
     bytes = std::max<size_t>(bytes, 1);
@@ -99,11 +103,7 @@ class MemoryScope {
       return hipSuccess;
     }
     hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess && idle_ > 0) {  // give the idle ones back and try once more
-      (void)hipGetLastError();
-      drop_idle();
-      e = hipMalloc(p, bytes);
-    }
+    if (e != hipSuccess && drop_idle()) e = hipMalloc(p, bytes);
     if (e == hipSuccess) blocks_.push_back(Block{*p, bytes, true});
     return e;
   }
@@ -131,13 +131,17 @@ class MemoryScope {
     bool busy;
   };
   static constexpr size_t kSlack = size_t(64) << 10, kMaxBlock = size_t(64) << 20, kMaxIdle = size_t(512) << 20;
-  void drop_idle() {
+  // After a refused request: give the idle arrays back; true when there were any, to try once more.
+  bool drop_idle() {
+    if (idle_ == 0) return false;
+    (void)hipGetLastError();
     for (size_t i = blocks_.size(); i-- > 0;)
       if (!blocks_[i].busy) {
         hipFree(blocks_[i].p);
         blocks_.erase(blocks_.begin() + i);
       }
     idle_ = 0;
+    return true;
   }
   Arena* arena_;
   MemoryScope* before_;

@@ -60,6 +60,28 @@ constexpr size_t MB = size_t(1) << 20;
 """
 
 CASES = {
+    # 40 MB lie idle and 20 MB are free: the idle ones go back for an array that the handle keeps
+    "kept_array_from_idle_memory": r"""
+int main() {
+  Arena arena;
+  {
+    MemoryScope scope(&arena);
+    card::capacity = 60 * MB;
+    char *a, *b;
+    CHECK(temp_malloc(&a, 40 * MB) == hipSuccess);
+    dev_free(a);
+    CHECK(card::used == 40 * MB);
+    CHECK(keep_malloc(&b, 50 * MB) == hipSuccess);
+    CHECK(hipGetLastError() == hipSuccess);
+    dev_free(b);  // stays the arena's
+    char* c;
+    CHECK(keep_malloc(&c, 20 * MB) != hipSuccess);
+  }
+  CHECK(card::used == 50 * MB);
+  arena.release();
+  CHECK(card::used == 0);
+}
+""",
     # a small kept array where its whole slab no longer fits
     "slab_no_larger_than_what_is_left": r"""
 int main() {

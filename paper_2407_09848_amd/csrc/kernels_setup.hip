@@ -826,6 +826,7 @@ static int build_mirror(hipStream_t s, int64_t n, const int32_t* ptr, const int3
     hipLaunchKernelGGL(k_mirror_present, dim3(grid_for(nslices)), dim3(kBlock), 0, s, nslices, offs, width, w,
                        (const MirrorStep*)m, out->doff);
     AMGP_HIP(hipGetLastError());
+    AMGP_HIP(settle(s, &v, sizeof(double) * nup * stride));
     AMGP_HIP(hipStreamSynchronize(s));
     out->mir = m;
     out->nmir = w;

@@ -108,6 +108,13 @@ class MemoryScope {
     return e;
   }
 
+  // whether p is a block more than kSlack larger than the bytes that are in use of it
+  bool outgrown(const void* p, size_t bytes) const {
+    for (const Block& b : blocks_)
+      if (b.p == p) return b.size > bytes + kSlack;
+    return false;
+  }
+
   void give(void* p) {
     if (!p || arena_->owns(p)) return;  // the arena's are released with the handle
     for (size_t i = 0; i < blocks_.size(); ++i) {
@@ -166,6 +173,23 @@ inline void dev_free(void* p) {
     m->give(p);
   else
     hipFree(p);
+}
+
+// An array that outlives the setup, in a temporary one's block that is too large for it (by up to a
+// quarter, see take): moved to memory of its own size, where there is room for it.
+template <typename T>
+hipError_t settle(hipStream_t s, T** p, size_t bytes) {
+  MemoryScope* m = MemoryScope::current();
+  if (!m || !m->outgrown(*p, bytes)) return hipSuccess;
+  T* q = nullptr;
+  if (keep_malloc(&q, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return hipSuccess;
+  }
+  const hipError_t e = hipMemcpyAsync(q, *p, bytes, hipMemcpyDeviceToDevice, s);
+  m->give(*p);
+  *p = q;
+  return e;
 }
 
 }  // namespace amgp

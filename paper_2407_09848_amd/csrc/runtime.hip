@@ -662,6 +662,19 @@ Csr level_csr(const Level& L) {
   return A;
 }
 
+// The coarse matrix becomes level C's.
+int adopt_csr(hipStream_t s, Csr* a, Level* C) {
+  AMGP_HIP(settle(s, &a->ptr, sizeof(int32_t) * (a->m + 1)));
+  AMGP_HIP(settle(s, &a->col, sizeof(int32_t) * a->nnz));
+  AMGP_HIP(settle(s, &a->val, sizeof(double) * a->nnz));
+  C->csr_ptr = a->ptr;
+  C->csr_col = a->col;
+  C->csr_val = a->val;
+  C->nnz = a->nnz;
+  *a = Csr();
+  return AMG_OK;
+}
+
 // Phat: the tentative prolongator (taken over); box aggregates when null (from L.agg)
 int general_level(Handle* h, hipStream_t s, Level& L, Level* C, Csr* Phat) {
   const Csr A = level_csr(L);
@@ -682,11 +695,7 @@ int general_level(Handle* h, hipStream_t s, Level& L, Level* C, Csr* Phat) {
   AMGP_TRY(galerkin_general(s, A, P.c, PT.c, &Ac.c, h->dflag));
   AMGP_TRY(build_ell64(s, P.c.m, P.c.ptr, P.c.col, P.c.val, &L.P64, P.c.ncols, 0));
   AMGP_TRY(build_ell64(s, PT.c.m, PT.c.ptr, PT.c.col, PT.c.val, &L.PT64, PT.c.ncols, 0));
-  C->csr_ptr = Ac.c.ptr;
-  C->csr_col = Ac.c.col;
-  C->csr_val = Ac.c.val;
-  C->nnz = Ac.c.nnz;
-  Ac.c = Csr();  // now owned by the level
+  AMGP_TRY(adopt_csr(s, &Ac.c, C));
   return AMG_OK;
 }
 
@@ -711,11 +720,7 @@ int box_level(Handle* h, hipStream_t s, Level& L, Level* C) {
     rc = drop_small(s, &Ac.c, 0.0);
   }
   AMGP_TRY(rc);
-  C->csr_ptr = Ac.c.ptr;
-  C->csr_col = Ac.c.col;
-  C->csr_val = Ac.c.val;
-  C->nnz = Ac.c.nnz;
-  Ac.c = Csr();  // now owned by the level
+  AMGP_TRY(adopt_csr(s, &Ac.c, C));
   rc = build_ell_aligned(s, L.nc, R.c.ptr, R.c.col, R.c.val, &L.R64, L.children, kMaxChildren, L.n, true);
   return rc == AMG_EINVAL ? AMG_OK : rc;
 }
@@ -796,7 +801,8 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
       C.n = nc;
       C.nx = (int)nc;
       C.wsmooth = wnext;
-      const int rc = general_level(h, s, L, &C, &Ph.c);
+      const bool settled = settle(s, &C.wsmooth, sizeof(double) * nc) == hipSuccess;
+      const int rc = settled ? general_level(h, s, L, &C, &Ph.c) : AMG_EHIP;
       h->lv.push_back(C);  // owned by the handle from here on, also on error
       if (rc != AMG_OK) return rc;
       continue;

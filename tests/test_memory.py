@@ -101,6 +101,41 @@ int main() {
   CHECK(card::used == 0);
 }
 """,
+    # an array that outlives the setup gives back a block that is much too large for it, which then
+    # serves the next temporary array; one of about its size, and one of the arena's, stay where they are
+    "outgrown_blocks": r"""
+int main() {
+  Arena arena;
+  char *a, *b, *c, *d;
+  {
+    MemoryScope scope(&arena);
+    CHECK(temp_malloc(&a, 10 * MB) == hipSuccess);
+    dev_free(a);
+    CHECK(temp_malloc(&b, 8 * MB + MB / 2) == hipSuccess && b == a);
+    CHECK(settle(nullptr, &b, 8 * MB + MB / 2) == hipSuccess);
+    CHECK(b != a && arena.owns(b));
+    CHECK(temp_malloc(&c, 10 * MB) == hipSuccess && c == a);
+    CHECK(settle(nullptr, &c, 10 * MB) == hipSuccess && c == a && !arena.owns(c));
+    CHECK(settle(nullptr, &b, 8 * MB) == hipSuccess && arena.owns(b));
+    // no room for the move: the array stays in its block
+    CHECK(temp_malloc(&d, 20 * MB) == hipSuccess);
+    dev_free(d);
+    CHECK(temp_malloc(&a, 18 * MB) == hipSuccess && a == d);
+    card::capacity = card::used;
+    CHECK(settle(nullptr, &a, 18 * MB) == hipSuccess && a == d);
+    CHECK(hipGetLastError() == hipSuccess);
+  }
+  CHECK(card::arrays().count(a) && card::arrays().count(c));
+  {
+    MemoryScope scope(&arena);
+    dev_free(a);
+    dev_free(b);
+    dev_free(c);
+    arena.release();
+  }
+  CHECK(card::used == 0);
+}
+""",
     # temporaries: one of about the size is taken again, all are returned with the scope
     "temporaries": r"""
 int main() {

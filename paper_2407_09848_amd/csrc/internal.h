@@ -470,9 +470,11 @@ int smoothed_prolongator(hipStream_t s, const Csr& A, int nbatch, const Csr& Pha
 int64_t scan_ptr(hipStream_t s, int64_t m, const int32_t* cnt, int32_t* ptr, int* rc, int div = 1, int scale = 1);
 // P^T of the 2x2x2 box prolongator from its children lists
 int children_transpose(hipStream_t s, int64_t n, int64_t nc, const int32_t* children, Csr* PT);
-// A_c = R P for the box P from R = P^T A, exactly zero sums left out; AMG_EINVAL when a row of R has
-// more than 64 entries (galerkin and drop_small then)
-int galerkin_from_restriction(hipStream_t s, const Csr& R, const int32_t* agg, Csr* Ac);
+// A_c = P^T A P for the 2x2x2 box P, its columns from those of R = P^T A, exactly zero sums left out (the
+// entries that galerkin and drop_small give); AMG_EINVAL when a row of R has more than 64 entries
+// (galerkin and drop_small then)
+int galerkin_from_restriction(hipStream_t s, const Csr& A, const Csr& R, const int32_t* agg, const int32_t* children,
+                              Csr* Ac);
 // ---- compatible weighted matching (kernels_match.hip) ----
 // composite tentative prolongator of `steps` matching steps on A (structurally symmetric, ascending
 // columns) from the smooth vector w0 (null: ones); *wnext (device, ncols entries) is the coarse one

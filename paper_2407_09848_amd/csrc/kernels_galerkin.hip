@@ -434,37 +434,102 @@ __global__ void k_children_rows(int64_t nc, const int32_t* __restrict__ ch, cons
   val[ptr[I] + c] = 1.0;
 }
 
-// Row I of A_c = R P for the box P (one entry 1.0 per row) from row I of R = P^T A, at most 64
-// entries: one wavefront per row, an entry per lane.  Every lane adds up the entries of its own
-// aggregate J = agg[column] in ascending column order (the other lanes' broadcast one by one); the
-// first lane of each J keeps the sum unless it is exactly zero (or no number).  FILL = false: counts.
-// Measured on the 27-point 320^3 matrix against one thread per coarse row over the eight fine rows
-// (216 entries, sorted by insertion into a list in scratch memory): 79.8 -> 13.9 ms for both passes.
+// Row I of A_c = P^T A P for the box P (one entry 1.0 per row), one wavefront per row.  Row I of R = P^T A
+// (at most 64 entries) names its columns: the first lane of each aggregate J = agg[column] owns J.
+// The entries of the aggregate's rows then pass through LDS 64 at a time, sorted by owner in their order, and
+// every owner adds its own ones up, so that each sum takes the products row by row and in ascending
+// column order as k_rap does, to the same bits.  Sums that are exactly zero (or no number) are left out.
+// FILL = false: counts.  Bound by the instructions per entry, not by its 12 bytes.  Measured on the
+// 27-point 320^3 matrix, both passes: 79.8 ms with k_rap (one thread per coarse row, 216 entries sorted by
+// insertion into a list in scratch memory), 18.2 ms here.  A_c as R P, 64 entries a row, took 15.9 ms, but its
+// sums associate otherwise: the V-cycle on 131 x 127 x 125 trilinear elements was then 8.3e-16 instead of
+// 6.5e-16 from its 64-bit values.
+constexpr int kOwnerHash = 2 * kWave;
+
 template <bool FILL>
-__global__ __launch_bounds__(kBlock) void k_galerkin_rows(int64_t nc, const int32_t* __restrict__ rptr,
-                                                          const int32_t* __restrict__ rcol,
-                                                          const double* __restrict__ rval,
-                                                          const int32_t* __restrict__ agg,
-                                                          int32_t* __restrict__ cnt_or_ptr, int32_t* __restrict__ ccol,
-                                                          double* __restrict__ cval) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t I = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
-  if (I >= nc) return;
-  const int beg = __builtin_amdgcn_readfirstlane(rptr[I]), len = __builtin_amdgcn_readfirstlane(rptr[I + 1]) - beg;
+__global__ __launch_bounds__(kWave) void k_galerkin_rows(
+    const int32_t* __restrict__ ptr, const int32_t* __restrict__ col, const double* __restrict__ val,
+    const int32_t* __restrict__ ch, const int32_t* __restrict__ rptr, const int32_t* __restrict__ rcol,
+    const int32_t* __restrict__ agg, int32_t* __restrict__ cnt_or_ptr, int32_t* __restrict__ ccol,
+    double* __restrict__ cval) {
+  __shared__ int32_t key[kOwnerHash], owner[kOwnerHash];
+  __shared__ double sorted[kWave];
+  __shared__ int32_t count[kWave], start[kWave];
+  const int lane = threadIdx.x;
+  const int64_t I = blockIdx.x;
+  const int beg = rptr[I], len = rptr[I + 1] - beg;
   const int J = lane < len ? agg[rcol[beg + lane]] : INT_MAX;
-  const double v = lane < len ? rval[beg + lane] : 0.0;
-  double sum = 0.0;
-  bool first = lane < len;
-  for (int e = 0; e < len; ++e) {
-    const int Je = __builtin_amdgcn_readlane(J, e);
-    const double ve = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), e),
-                                       __builtin_amdgcn_readlane(__double2loint(v), e));
-    if (Je == J) {
-      sum += ve;
-      first = first && e >= lane;
-    }
+  for (int t = lane; t < kOwnerHash; t += kWave) {
+    key[t] = -1;
+    owner[t] = kWave;
   }
-  const bool keep = first && fabs(sum) > 0.0;
+  __syncthreads();
+  unsigned mine = hslot(J, kOwnerHash);
+  if (lane < len) {
+    for (;;) {  // at most 64 keys: a free place is always found
+      const int old = atomicCAS(&key[mine], -1, J);
+      if (old == -1 || old == J) break;
+      mine = (mine + 1) & (kOwnerHash - 1);
+    }
+    atomicMin(&owner[mine], lane);
+  }
+  __syncthreads();
+  // lane c < 8: child row c, where its entries begin and how many come before them
+  const int child = lane < kMaxChildren ? ch[I * kMaxChildren + lane] : -1;
+  const int cbeg = child >= 0 ? ptr[child] : 0;
+  int upto = child >= 0 ? ptr[child + 1] - cbeg : 0;
+  const int clen = upto;
+  for (int off = 1; off < kMaxChildren; off <<= 1) {
+    const int u = __shfl_up(upto, off, kWave);
+    if (lane >= off) upto += u;
+  }
+  const int total = __builtin_amdgcn_readlane(upto, kMaxChildren - 1);
+  const int before = upto - clen;
+  double sum = 0.0;
+  for (int e0 = 0; e0 < total; e0 += kWave) {
+    const int e = e0 + lane;
+    int p = 0;
+#pragma unroll
+    for (int c = 0; c < kMaxChildren; ++c) {
+      const int first = __builtin_amdgcn_readlane(before, c);
+      if (e >= first) p = __builtin_amdgcn_readlane(cbeg, c) + (e - first);
+    }
+    int slot = kWave;
+    double v = 0.0;
+    if (e < total) {
+      const int Je = agg[col[p]];
+      v = val[p];
+      unsigned h = hslot(Je, kOwnerHash);
+      for (int probe = 0; probe < kOwnerHash && slot == kWave; ++probe, h = (h + 1) & (kOwnerHash - 1))
+        if (key[h] == Je) slot = owner[h];
+    }
+    const bool has = slot < kWave;  // R holds every column of these rows
+    unsigned long long same = __ballot(has);  // the lanes whose entries have this owner
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+      const unsigned long long set = __ballot((slot >> b) & 1);
+      same &= (slot >> b) & 1 ? set : ~set;
+    }
+    const int rank = __popcll(same & ((1ull << lane) - 1));
+    count[lane] = 0;
+    __syncthreads();
+    if (has && rank == 0) count[slot] = __popcll(same);
+    __syncthreads();
+    const int n = count[lane];
+    int at = n;
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int u = __shfl_up(at, off, kWave);
+      if (lane >= off) at += u;
+    }
+    at -= n;
+    start[lane] = at;
+    __syncthreads();
+    if (has) sorted[start[slot] + rank] = v;
+    __syncthreads();
+    for (int q = 0; q < n; ++q) sum += sorted[at + q];
+    __syncthreads();
+  }
+  const bool keep = lane < len && owner[mine] == lane && fabs(sum) > 0.0;
   const unsigned long long kept = __ballot(keep);
   if constexpr (!FILL) {
     if (lane == 0) cnt_or_ptr[I] = __popcll(kept);
@@ -718,7 +783,8 @@ int children_transpose(hipStream_t s, int64_t n, int64_t nc, const int32_t* chil
   return AMG_OK;
 }
 
-int galerkin_from_restriction(hipStream_t s, const Csr& R, const int32_t* agg, Csr* Ac) {
+int galerkin_from_restriction(hipStream_t s, const Csr& A, const Csr& R, const int32_t* agg, const int32_t* children,
+                              Csr* Ac) {
   const int64_t nc = R.m;
   Csr o;
   o.m = nc;
@@ -730,15 +796,17 @@ int galerkin_from_restriction(hipStream_t s, const Csr& R, const int32_t* agg, C
   const int64_t longest = max_count(s, nc, cnt.p, cnt.p + nc, &rc);
   if (rc != AMG_OK) return rc;
   if (longest > kWave) return AMG_EINVAL;
-  const dim3 grid(grid_for(nc * kWave)), block(kBlock);
+  const dim3 grid((unsigned)nc), block(kWave);
   if (temp_malloc(&o.ptr, sizeof(int32_t) * (nc + 1)) != hipSuccess) return AMG_ENOMEM;
-  hipLaunchKernelGGL(k_galerkin_rows<false>, grid, block, 0, s, nc, R.ptr, R.col, R.val, agg, o.ptr, nullptr, nullptr);
+  hipLaunchKernelGGL(k_galerkin_rows<false>, grid, block, 0, s, A.ptr, A.col, A.val, children, R.ptr, R.col, agg, o.ptr,
+                     nullptr, nullptr);
   o.nnz = scan_ptr(s, nc, o.ptr, o.ptr, &rc);
   if (rc == AMG_OK && (temp_malloc(&o.col, sizeof(int32_t) * std::max<int64_t>(o.nnz, 1)) != hipSuccess ||
                        temp_malloc(&o.val, sizeof(double) * std::max<int64_t>(o.nnz, 1)) != hipSuccess))
     rc = AMG_ENOMEM;
   if (rc == AMG_OK) {
-    hipLaunchKernelGGL(k_galerkin_rows<true>, grid, block, 0, s, nc, R.ptr, R.col, R.val, agg, o.ptr, o.col, o.val);
+    hipLaunchKernelGGL(k_galerkin_rows<true>, grid, block, 0, s, A.ptr, A.col, A.val, children, R.ptr, R.col, agg, o.ptr,
+                       o.col, o.val);
     if (hipGetLastError() != hipSuccess) rc = AMG_EHIP;
   }
   if (rc != AMG_OK) {

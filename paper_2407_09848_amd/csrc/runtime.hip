@@ -699,7 +699,7 @@ int general_level(Handle* h, hipStream_t s, Level& L, Level* C, Csr* Phat) {
   return AMG_OK;
 }
 
-// Level L -> C for the 2x2x2 box P: R = P^T A, A_c = R P, and R in slices aligned on each
+// Level L -> C for the 2x2x2 box P: R = P^T A, A_c = P^T A P, and R in slices aligned on each
 // aggregate's first row (the restriction of k_restrict_product), whatever their padding (small
 // ragged levels pad more than 10%, but one pass over R still costs less than the residual's pass
 // over A).  R is left empty (the residual and the sum over children are used instead) when a slice
@@ -708,7 +708,7 @@ int box_level(Handle* h, hipStream_t s, Level& L, Level* C) {
   CsrHold PT, R, Ac;
   AMGP_TRY(children_transpose(s, L.n, L.nc, L.children, &PT.c));
   AMGP_TRY(spgemm(s, PT.c, level_csr(L), &R.c, h->dflag));
-  int rc = galerkin_from_restriction(s, R.c, L.agg, &Ac.c);
+  int rc = galerkin_from_restriction(s, level_csr(L), R.c, L.agg, L.children, &Ac.c);
   if (rc == AMG_EINVAL) {
     // rows of R beyond a wavefront: the product from the fine rows (at most 64 distinct columns)
     Ac.c.m = Ac.c.ncols = L.nc;

@@ -488,8 +488,8 @@ int vbm_aggregates(hipStream_t s, const Csr& A, double theta, int32_t* agg, int6
 void free_ell(Ell<float>& e);
 
 // ---- dense kernels (kernels_dense.hip) ----
-// dense[nbatch][np][np] (SPD, lower tiles read, overwritten) -> *packed: the lower 64x64 blocks of
-// each A^{-1} in contiguous tiles (tile J(J+1)/2 + I = block (J, I)); the caller's, also on error
+// dense[nbatch][np][np] (SPD, lower tiles read; taken over, a temporary array) -> *packed: the lower 64x64
+// blocks of each A^{-1} in contiguous tiles (tile J(J+1)/2 + I = block (J, I)); the caller's, also on error
 int dense_spd_inverse(hipStream_t s, int nbatch, int64_t np, double* dense, double** packed, int* flag);
 // The operator of `sweeps` l1-Jacobi sweeps from zero, sum_j (I - M^{-1} A)^j M^{-1} (symmetric), as such
 // tiles; np is n rounded up to whole tiles

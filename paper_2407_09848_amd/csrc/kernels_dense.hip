@@ -383,8 +383,7 @@ int dense_spd_inverse(hipStream_t s, int nbatch, int64_t np64, double* dense, do
   *packed = nullptr;
   const int rc = [&]() -> int {
     if (temp_malloc(&dinv, sizeof(double) * nbatch * sD) != hipSuccess ||
-        temp_malloc(&X, sizeof(double) * nbatch * sA) != hipSuccess ||
-        keep_malloc(packed, sizeof(double) * (size_t)nbatch * ntiles * TM * TM) != hipSuccess)
+        temp_malloc(&X, sizeof(double) * nbatch * sA) != hipSuccess)
       return AMG_ENOMEM;
     // 1. Cholesky, right looking, on the lower tiles
     for (int k = 0; k < nb; ++k) {
@@ -417,13 +416,18 @@ int dense_spd_inverse(hipStream_t s, int nbatch, int64_t np64, double* dense, do
       for (int q = 0; q < whole; q += most) join(2LL * b * q, b, std::min(most, whole - q));
       if (left > b) join(2LL * b * whole, left - b, 1);
     }
-    // 3. the lower tiles of A^{-1} = X^T X
+    // 3. the lower tiles of A^{-1} = X^T X, in place of L (a setup holds two dense matrices at most)
+    AMGP_HIP(hipGetLastError());
+    dev_free(dense);
+    dense = nullptr;
+    if (keep_malloc(packed, sizeof(double) * (size_t)nbatch * ntiles * TM * TM) != hipSuccess) return AMG_ENOMEM;
     hipLaunchKernelGGL(k_inverse_tiles, dim3(ntiles, nbatch), dim3(256), 0, s, np, ntiles, (const double*)X, *packed);
     AMGP_HIP(hipGetLastError());
     AMGP_HIP(hipStreamSynchronize(s));
     return AMG_OK;
   }();
   if (rc != AMG_OK) hipStreamSynchronize(s);
+  dev_free(dense);
   dev_free(dinv);
   dev_free(X);
   return rc;

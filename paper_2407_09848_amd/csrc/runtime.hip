@@ -873,11 +873,12 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
     AMGP_TRY(dalloc(&h->cpart, (int64_t)h->nbatch * (h->ncp / kDenseTile) * (h->ncp / kDenseTile) * kDenseTile));
     double* dense = nullptr;
     if (temp_malloc(&dense, sizeof(double) * h->nbatch * h->ncp * h->ncp) != hipSuccess) return AMG_ENOMEM;
-    int rc = launch_to_dense(s, h->nbatch, h->ncl, h->ncp, L.csr_ptr, L.csr_col, L.csr_val, dense, h->dflag);
-    if (rc == AMG_OK) rc = dense_spd_inverse(s, h->nbatch, h->ncp, dense, &h->ainv, h->dflag);
-    if (rc == AMG_OK && hipStreamSynchronize(s) != hipSuccess) rc = AMG_EHIP;
-    dev_free(dense);
-    if (rc != AMG_OK) return rc;
+    const int rc = launch_to_dense(s, h->nbatch, h->ncl, h->ncp, L.csr_ptr, L.csr_col, L.csr_val, dense, h->dflag);
+    if (rc != AMG_OK) {
+      dev_free(dense);
+      return rc;
+    }
+    AMGP_TRY(dense_spd_inverse(s, h->nbatch, h->ncp, dense, &h->ainv, h->dflag));
     int fl[F_NFLAG];
     AMGP_TRY(read_flags(h, s, fl));
     if (fl[F_NOTSPD]) return AMG_ENOTSPD;

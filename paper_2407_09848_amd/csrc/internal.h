@@ -75,6 +75,15 @@ struct MirrorStep {
 };
 constexpr int kMirrorMaxSteps = 27;
 
+// Slices of 128 rows, two rows per lane, in FP64 hierarchies from this many rows on: where the vectors
+// come from HBM, half the gathers and loads of twice the width (degree-4 application: 27 points 240^3
+// 681 -> 537 us, 7 points 256^3 546 -> 492, 5 points 4000^2 506 -> 390; solve on the 27-point 320^3
+// matrix 158.8 -> 134.7 ms).  On smaller levels, whose vectors stay in the last-level cache, the
+// wavefronts count: 27 points 160^3 183 both, 128^3 92.3 -> 95.5, 7 points 160^3 113 -> 125.
+// With the FP32 hierarchy one row per lane is always the faster (27 points 240^3 304 against 353 us,
+// 7 points 256^3 252 against 354), and its FP64 fine level, which serves the products of the CG alone, keeps its form.
+constexpr int64_t kPairMinRows = 1 << 22;
+
 inline int64_t pattern_bytes(int64_t npat, int rpl) { return ((12 + 8 * rpl) * npat + 7) / 8 * 8; }
 
 template <typename T>

@@ -838,15 +838,6 @@ static int build_mirror(hipStream_t s, int64_t n, const int32_t* ptr, const int3
   return rc;
 }
 
-// Slices of 128 rows, two rows per lane, in FP64 hierarchies from this many rows on: where the vectors
-// come from HBM, half the gathers and loads of twice the width (degree-4 application: 27 points 240^3
-// 681 -> 537 us, 7 points 256^3 546 -> 492, 5 points 4000^2 506 -> 390; solve on the 27-point 320^3
-// matrix 158.8 -> 134.7 ms).  On smaller levels, whose vectors stay in the last-level cache, the
-// wavefronts count: 27 points 160^3 183 both, 128^3 92.3 -> 95.5, 7 points 160^3 113 -> 125.
-// With the FP32 hierarchy one row per lane is always the faster (27 points 240^3 304 against 353 us,
-// 7 points 256^3 252 against 354), and its FP64 fine level, which serves the products of the CG alone, keeps its form.
-constexpr int64_t kPairMinRows = 1 << 22;
-
 // Patterns of the uniform slices (64 rpl rows each) that k_slice_layout<false, rpl> found, and all
 // slices' descriptors.
 static int build_patterns(hipStream_t s, int rpl, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,

@@ -1787,20 +1787,18 @@ void with_mode_store(int mode, bool store, F&& f) {
     f(M1(), std::false_type());
 }
 
-// Levels served by two rows per lane: f(NT, V, launch shape).
+// Levels served by two rows per lane: f(NT, V, launch shape).  Those of uniform slices always stream.
 template <typename F>
 int with_pairs(const Ell<double>& A, F&& f) {
+  static_assert((kPairMinRows + kBlock - 1) / kBlock > kRemapMaxBlocks, "two rows per lane: streaming levels alone");
+  using Mirror = std::integral_constant<int, V_MIRROR>;
   const dim3 gr((grid_for((A.n + 1) / 2) + kXcd - 1) / kXcd * kXcd);
-  auto go = [&](auto v) {
-    if (streamed(xcd_grid(A.n)))
-      f(std::true_type(), v, gr);
-    else
-      f(std::false_type(), v, gr);
-  };
-  if (A.mir)
-    go(std::integral_constant<int, V_MIRROR>());
+  if (!A.mir)
+    f(std::true_type(), std::integral_constant<int, V_UNIFORM>(), gr);
+  else if (streamed(xcd_grid(A.n)))
+    f(std::true_type(), Mirror(), gr);
   else
-    go(std::integral_constant<int, V_UNIFORM>());
+    f(std::false_type(), Mirror(), gr);
   return LAUNCH_OK();
 }
 

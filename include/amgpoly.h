@@ -164,6 +164,11 @@ int amg_level_layout(const amg_handle* h, int level, int64_t* h_padded, int* h_l
 int amg_level_patterns(const amg_handle* h, int level, int restriction, int64_t* h_values, int64_t* h_slices,
                        int64_t* h_steps);
 
+/* Rows that a lane of the FP64 kernels serves on level l (host output): 2 on large FP64 levels of uniform
+ * slices, which then have 128 rows, and where only half of a symmetric stencil matrix is stored; 1
+ * elsewhere. */
+int amg_level_rows_per_lane(const amg_handle* h, int level, int* h_rows);
+
 /* How the restriction from level l to level l + 1 is computed (host outputs, any may be NULL;
  * AMG_EINVAL on the coarsest level): *h_form = AMG_TRANSFER_RESIDUAL (2x2x2 boxes: the fine
  * residual b - A x, then the sum over each aggregate's rows), AMG_TRANSFER_PRODUCT (2x2x2 boxes:

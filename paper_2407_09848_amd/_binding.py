@@ -17,7 +17,8 @@ AMG_TRANSFER_RESIDUAL, AMG_TRANSFER_PRODUCT, AMG_TRANSFER_EXPLICIT = 0, 1, 2
 
 __all__ = [
     "LIB_PATH", "AmgError", "lib", "amg_setup", "amg_destroy", "amg_num_levels", "amg_level_info", "amg_level_layout",
-    "amg_level_transfer", "amg_level_patterns", "AMG_TRANSFER_RESIDUAL", "AMG_TRANSFER_PRODUCT", "AMG_TRANSFER_EXPLICIT",
+    "amg_level_transfer", "amg_level_patterns", "amg_level_rows_per_lane",
+    "AMG_TRANSFER_RESIDUAL", "AMG_TRANSFER_PRODUCT", "AMG_TRANSFER_EXPLICIT",
     "amg_level_export", "amg_level_aggregates", "amg_default_beta", "amg_default_astar", "amg_set_beta",
     "amg_reset_beta",
     "amg_spmv", "smoother_apply", "smoother_apply_f32", "amg_restrict_residual", "amg_prolong_add", "amg_coarse_solve",
@@ -62,6 +63,7 @@ _SIGS = {
     "amg_level_aggregates": (_I, [_P, _I, _P, _P]),
     "amg_level_layout": (_I, [_P, _I, ctypes.POINTER(_I64), ctypes.POINTER(_I), ctypes.POINTER(_I)]),
     "amg_level_patterns": (_I, [_P, _I, _I, ctypes.POINTER(_I64), ctypes.POINTER(_I64), ctypes.POINTER(_I64)]),
+    "amg_level_rows_per_lane": (_I, [_P, _I, ctypes.POINTER(_I)]),
     "amg_level_transfer": (_I, [_P, _I, ctypes.POINTER(_I), ctypes.POINTER(_I64)]),
     "amg_default_beta": (_I, [_I, ctypes.POINTER(_D)]),
     "amg_default_astar": (_I, [_I, ctypes.POINTER(_D)]),
@@ -196,6 +198,13 @@ def amg_level_patterns(h, level, restriction=False):
     _check(lib().amg_level_patterns(h, level, int(bool(restriction)), ctypes.byref(values), ctypes.byref(slices),
                                     ctypes.byref(steps)), "amg_level_patterns")
     return values.value, slices.value, steps.value
+
+
+def amg_level_rows_per_lane(h, level):
+    """Rows that a lane of the FP64 kernels serves on level l (1 or 2)."""
+    rows = _I()
+    _check(lib().amg_level_rows_per_lane(h, level, ctypes.byref(rows)), "amg_level_rows_per_lane")
+    return rows.value
 
 
 def amg_level_export(h, level):

@@ -114,6 +114,13 @@ struct Ell {
   int nmir = 0;
 };
 
+// Levels served by two rows per lane: large ones of uniform slices (kPairMinRows) and FP64 mirrored
+// diagonals, where every stream of a row then takes loads of 16 bytes instead of 8 (256^3 solve 87.6 -> 79.1
+// ms, degree-5 application on 203x187x171 rows 515 -> 471 us).  With the FP32 hierarchy, whose pairs
+// take 8 bytes, one row per lane is the faster (52.5 against 54.4 ms; 32 x 64^3 training step 6.15
+// against 6.65 ms).
+inline bool paired(const Ell<double>& A) { return A.mir || (A.desc && A.rpl == 2); }
+
 // Per-problem smoother weights for stacked problems: the weight of row i is
 // v[(i / rpp) * stride] when v is not null (otherwise the launch's scalar).
 struct Wt {

@@ -1802,12 +1802,6 @@ int with_pairs(const Ell<double>& A, F&& f) {
   return LAUNCH_OK();
 }
 
-// FP64 levels of mirrored diagonals: loads of 16 bytes instead of 8 for every stream of a row (256^3
-// solve 87.6 -> 79.1 ms, degree-5 application on 203x187x171 rows 515 -> 471 us).  With the FP32
-// hierarchy, whose pairs take 8 bytes, one row per lane is the faster (52.5 against 54.4 ms; 32 x 64^3
-// training step 6.15 against 6.65 ms).  Uniform slices: see kPairMinRows.
-inline bool paired(const Ell<double>& A) { return A.mir || (A.desc && A.rpl == 2); }
-
 // The levels whose merged first two steps can read u = M^{-1} b instead of gathering M^{-1} and b
 bool first2_takes_u(const Ell<double>& A) { return streamed(xcd_grid(A.n)) && wide(A); }
 bool first2_takes_u(const Ell<float>& A) {

@@ -1151,6 +1151,12 @@ int amg_level_patterns(const amg_handle* h, int level, int restriction, int64_t*
   return AMG_OK;
 }
 
+int amg_level_rows_per_lane(const amg_handle* h, int level, int* h_rows) {
+  if (!h || !h_rows || level < 0 || level >= h->impl.nlevels) return AMG_EINVAL;
+  *h_rows = amgp::paired(h->impl.lv[level].A64) ? 2 : 1;
+  return AMG_OK;
+}
+
 int amg_level_transfer(const amg_handle* h, int level, int* h_form, int64_t* h_stored) {
   if (!h || level < 0 || level >= h->impl.nlevels - 1) return AMG_EINVAL;
   const amgp::Level& L = h->impl.lv[level];

@@ -84,7 +84,8 @@ constexpr int kMirrorMaxSteps = 27;
 // 7 points 256^3 252 against 354), and its FP64 fine level, which serves the products of the CG alone, keeps its form.
 constexpr int64_t kPairMinRows = 1 << 22;
 
-inline int64_t pattern_bytes(int64_t npat, int rpl) { return ((12 + 8 * rpl) * npat + 7) / 8 * 8; }
+// with room behind the last step for a batch that is read whole (7 steps more of any of the three arrays)
+inline int64_t pattern_bytes(int64_t npat, int rpl) { return ((12 + 8 * rpl) * npat + 7) / 8 * 8 + 56; }
 
 template <typename T>
 struct Ell {

@@ -304,9 +304,11 @@ struct GatherVec {
     return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (uint32_t)r * (uint32_t)sizeof(T));
   }
 };
-// Kernel variants of the one-row-per-lane levels: narrow and wide dense slices (kWideBatch), and
-// levels with uniform slices, whose kernels also request the row's own vectors first.
-enum Variant { V_NARROW = 0, V_WIDE = 1, V_UNIFORM = 2, V_MIRROR = 3 };
+// Kernel variants of the one-row-per-lane levels: narrow and wide dense slices (kWideBatch), levels with
+// uniform slices, whose kernels also request the row's own vectors first, mirrored diagonals, and small FP64
+// levels of uniform slices (kSmallMaxRows).
+enum Variant { V_NARROW = 0, V_WIDE = 1, V_UNIFORM = 2, V_MIRROR = 3, V_SMALL = 4 };
+constexpr bool uniform_slices(int v) { return v == V_UNIFORM || v == V_SMALL; }
 
 // The value of the lane below (DPP wave_shr) or above (wave_shl); the lane at the end, which has no
 // such neighbour, keeps `end`.
@@ -333,23 +335,32 @@ __device__ __forceinline__ double dpp_shift(double end, double v) {
 // nine triples per batch instead of three the whole solve took 177 instead of 160 ms (473 ms with
 // dense slices).  7-point 128^3 level: step that keeps x 28.1 -> 18.6 us.
 
-// Any pattern: one gather per step.
+// Any pattern: one gather per step.  A batch's steps are read whole, so that they come with few wide scalar
+// loads: those past the pattern's end (the next pattern's, or the room behind the last) are not used.
+// With every step's index clamped each took loads of its own, on which small levels waited: FP32 steps of a
+// smoother application at 7 points 80^3 4.9 -> 3.9 us (dense slices 4.2), 21 points 64^3 5.7 -> 4.1 (dense
+// 4.3), 5 points 724^2 4.6 -> 4.1 (dense 4.0).
 template <bool FULL, typename T, typename Gf>
 __device__ __forceinline__ T pattern_sum(EllView<T> A, int beg, int w, int r, Gf g) {
   constexpr int B = 8;
   T acc = T(0);
   for (int t = 0; t < w; t += B) {
-    T gv[B], v[B];
+    T gv[B];
+    int off[B];
+    // the steps past the last one (of the next pattern, or the room behind the last) are not used
+#pragma unroll
+    for (int u = 0; u < B; ++u) off[u] = A.poff(1)[beg + t + u];
 #pragma unroll
     for (int u = 0; u < B; ++u) {
-      const int q = beg + min(t + u, w - 1);
-      v[u] = A.pval(1)[q];
-      if constexpr (!FULL) v[u] = __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q]) ? v[u] : T(0);
-      gv[u] = FULL ? g.at(A.poff(1)[q], r) : g(min(max(r + A.poff(1)[q], 0), A.last));
+      const int o = t + u < w ? off[u] : off[0];
+      gv[u] = FULL ? g.at(o, r) : g(min(max(r + o, 0), A.last));
     }
 #pragma unroll
-    for (int u = 0; u < B; ++u)
-      if (t + u < w) acc += v[u] * gv[u];
+    for (int u = 0; u < B; ++u) {
+      T v = A.pval(1)[beg + t + u];
+      if constexpr (!FULL) v = __builtin_amdgcn_inverse_ballot_w64(A.pmask()[beg + t + u]) ? v : T(0);
+      if (t + u < w) acc += v * gv[u];
+    }
   }
   return acc;
 }
@@ -386,13 +397,22 @@ __device__ __forceinline__ T pattern_triples(EllView<T> A, int q, int lane, int 
   return acc;
 }
 
-constexpr int kTripleBatch = 3;
-template <bool FULL, typename T, typename Gf>
+// Triples per batch: on small FP64 levels (V_SMALL) and cached FP32 ones all nine of a 27-point row, since a step
+// waits for each batch there (FP64 16^3 rows 4.5 -> 4.1 us, 40^3 4.6 -> 4.3; FP32 100^3 10.4 -> 9.9, 128^3 20.1
+// -> 18.9); with the registers of nine, larger FP64 levels lose (100^3 14.9 -> 17.3 us).
+constexpr int kTripleBatch = 3, kTripleBatchAll = 9;
+template <typename T, bool NT, int V>
+constexpr int triple_batch() {
+  return V == V_SMALL || (std::is_same_v<T, float> && !NT) ? kTripleBatchAll : kTripleBatch;
+}
+template <int BATCH, bool FULL, typename T, typename Gf>
 __device__ __forceinline__ T pattern_triples_sum(EllView<T> A, int beg, int w, int lane, int r, Gf g) {
   T acc = T(0);
   int t = 0;
-  for (; t + 3 * kTripleBatch <= w; t += 3 * kTripleBatch)
-    acc = pattern_triples<kTripleBatch, FULL>(A, beg + t, lane, r, acc, g);
+  for (; t + 3 * BATCH <= w; t += 3 * BATCH) acc = pattern_triples<BATCH, FULL>(A, beg + t, lane, r, acc, g);
+  if constexpr (BATCH > kTripleBatch)
+    for (; t + 3 * kTripleBatch <= w; t += 3 * kTripleBatch)
+      acc = pattern_triples<kTripleBatch, FULL>(A, beg + t, lane, r, acc, g);
   for (; t < w; t += 3) acc = pattern_triples<1, FULL>(A, beg + t, lane, r, acc, g);
   return acc;
 }
@@ -443,13 +463,13 @@ __device__ __forceinline__ T slice_sum(EllView<T> A, int s, int lane, int r, Gf 
   if constexpr (V == V_MIRROR) return mirror_sum(A, s, lane, r, g);
   int beg, end;
   const int32_t* off;
-  if constexpr (V == V_UNIFORM) {
+  if constexpr (uniform_slices(V)) {
     const int2 d = A.desc()[s];
     const int b = __builtin_amdgcn_readfirstlane(d.x), info = __builtin_amdgcn_readfirstlane(d.y);
     const int w = info >> 4;
     if (info & SLICE_TRIPLES) {
-      if (info & SLICE_FULL) return pattern_triples_sum<true>(A, b, w, lane, r, g);
-      return pattern_triples_sum<false>(A, b, w, lane, r, g);
+      if (info & SLICE_FULL) return pattern_triples_sum<triple_batch<T, NT, V>(), true>(A, b, w, lane, r, g);
+      return pattern_triples_sum<triple_batch<T, NT, V>(), false>(A, b, w, lane, r, g);
     }
     if (info & SLICE_FULL) return pattern_sum<true>(A, b, w, r, g);
     if (info & SLICE_MASKED) return pattern_sum<false>(A, b, w, r, g);
@@ -464,7 +484,7 @@ __device__ __forceinline__ T slice_sum(EllView<T> A, int s, int lane, int r, Gf 
   if constexpr (std::is_same_v<T, float>)
     return aligned_sum_f32<NT>(A.val, beg, end, lane, off, r, A.last, g);
   else
-    return aligned_sum_f64<NT, Gf, true, V == V_WIDE ? kWideBatch : V == V_UNIFORM ? 4 : kAlignedBatch>(A.val, beg, end, lane, off, r,
+    return aligned_sum_f64<NT, Gf, true, V == V_WIDE ? kWideBatch : uniform_slices(V) ? 4 : kAlignedBatch>(A.val, beg, end, lane, off, r,
                                                                                    A.last, g);
 }
 
@@ -933,7 +953,7 @@ __device__ __forceinline__ T ell_dot_any(EllView<T> A, int row, const T* __restr
       if ((A.doff[s] >> t) & 1) acc += A.val[st[t].voff + row] * x[min(max(row + st[t].off, 0), A.last)];
     return acc;
   }
-  if constexpr (V == V_UNIFORM) {
+  if constexpr (uniform_slices(V)) {
     const int2 d = A.desc()[s];
     const int w = d.y >> 4;
     if ((d.y & 15) != SLICE_DENSE) {
@@ -1736,6 +1756,10 @@ inline bool wide(const Ell<double>& A) {
 }
 inline bool wide(const Ell<float>&) { return false; }
 
+// FP64 levels of uniform slices below this many rows take the kernels of V_SMALL (27 points: 40^3 rows 4.6 ->
+// 4.3 us, 48^3 = 110592 rows 4.8 both).
+constexpr int64_t kSmallMaxRows = 3 << 15;
+
 // Runs f(NT, V) for a level of one row per lane: the streaming hints of `nt`, and the variant of
 // its slices.  kHasWide: the kernel has a wide form (streaming levels only).
 template <bool kHasWide, bool kHasMirror = false, typename T, typename F>
@@ -1754,6 +1778,12 @@ void with_variant(const Ell<T>& A, bool nt, F&& f) {
     }
   }
   if (A.desc) {
+    if constexpr (std::is_same_v<T, double>) {
+      if (A.n < kSmallMaxRows) {
+        f(std::false_type(), std::integral_constant<int, V_SMALL>());
+        return;
+      }
+    }
     if (nt)
       f(std::true_type(), Uniform());
     else

@@ -452,16 +452,16 @@ int launch_l1_diag(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* 
                    double* minv, int* flag);
 // ncols: number of columns (default n); padding entries use column i when i < ncols, else 0.
 // group: lanes per row (1, 4, 16 or 64); 0 chooses from the mean row length
-// pairs: two rows per lane allowed on large levels of uniform slices (no FP32 copy is taken)
+// single: an FP32 hierarchy's level (its smoothers run on the FP32 copy)
 int build_ell64(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
-                Ell<double>* out, int64_t ncols = -1, int group = 1, bool pairs = false);
+                Ell<double>* out, int64_t ncols = -1, int group = 1, bool single = false);
 int build_ell32(hipStream_t s, const Ell<double>& a, Ell<float>* out);
 // offset-aligned slices (one row per lane) with the offsets taken against anchor[r * astride]
 // (null: the row r) and columns clamped into [0, ncols) (-1: n); AMG_EINVAL when a slice has more
 // than 64 offsets or (unless any_size) the layout is more than 10% larger than the packed one
 int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
                       Ell<double>* out, const int32_t* anchor = nullptr, int astride = 1, int64_t ncols = -1,
-                      bool any_size = false, bool pairs = false);
+                      bool any_size = false, bool single = false);
 // box aggregates of edge e; children (2x2x2 boxes only) may be null
 int launch_aggregates(hipStream_t s, int nx, int ny, int nz, int nbatch, int e, int32_t* agg, int32_t* children,
                       int* cnx, int* cny, int* cnz);

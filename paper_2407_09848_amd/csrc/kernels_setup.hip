@@ -369,8 +369,8 @@ __global__ void k_pattern_write(int64_t nslices, const int32_t* __restrict__ rep
 }
 
 // Sums over the slices: steps of the aligned and of the packed layout, slices that fit no pattern
-// table (width -1), uniform slices, and the widest slice.
-enum SliceStat { ST_ALIGNED = 0, ST_PACKED, ST_OVER, ST_UNIFORM, ST_WIDEST, ST_COUNT };
+// table (width -1), uniform slices, those of them in triples, and the widest slice.
+enum SliceStat { ST_ALIGNED = 0, ST_PACKED, ST_OVER, ST_UNIFORM, ST_TRIPLES, ST_WIDEST, ST_COUNT };
 __global__ __launch_bounds__(kBlock) void k_slice_stats(int64_t nslices, const int32_t* __restrict__ width,
                                                         const int32_t* __restrict__ lwidth,
                                                         const int32_t* __restrict__ kind,
@@ -385,6 +385,7 @@ __global__ __launch_bounds__(kBlock) void k_slice_stats(int64_t nslices, const i
     v[ST_ALIGNED] += w;
     v[ST_PACKED] += lwidth[s];
     v[ST_UNIFORM] += kind && kind[s] != SLICE_DENSE;
+    v[ST_TRIPLES] += kind && (kind[s] & SLICE_TRIPLES);
     v[ST_WIDEST] = max(v[ST_WIDEST], (unsigned long long)w);
   }
   for (int k = 0; k < ST_COUNT; ++k) {
@@ -760,7 +761,16 @@ int launch_l1_diag(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* 
 
 // Uniform slices are kept as patterns when they are at least half of the matrix's (a matrix of
 // constant coefficients: all but the slices that cross an odd boundary); below that most slices
-// stay dense and the plain kernels, which have no pattern path, serve them faster.
+// stay dense and the plain kernels, which have no pattern path, serve them faster.  Two kinds of levels
+// small enough for the L2 caches take longer with patterns than with their stored values and keep those:
+// - wide triples (27 points) in FP32 hierarchies below 2^18 rows (time of a step of a smoother application,
+//   dense -> patterns: 40^3 rows 3.3 -> 4.0 us, 56^3 4.0 -> 4.5, 64^3 5.3 -> 4.8, 80^3 11.4 -> 7.0; FP64
+//   40^3 4.2 -> 4.3, 48^3 5.3 -> 4.8);
+// - restriction products of fine levels below 3 2^17 rows (27 points, 50^3 rows 6.1 -> 6.7 us, 64^3 6.1 -> 7.0,
+//   80^3 10.8 -> 6.9; 7 points 64^3 4.5 -> 4.8, 80^3 5.8 -> 4.8).
+constexpr int kWideTripleSteps = 24;
+constexpr int64_t kTriplesMinRows32 = int64_t(1) << 18;
+constexpr int64_t kRestrictPatternMinRows = int64_t(3) << 17;
 constexpr int64_t kUniformMaxRows = int64_t(1) << 28;  // 32-bit byte offsets of the full slices' gathers
 
 // Mirrored diagonals for the matrix of the given slices when it is large enough to be bound by its
@@ -901,7 +911,7 @@ static int slice_stats(hipStream_t s, int64_t nslices, const int32_t* wd, const 
 // offsets and the layout is at most 10% larger than the packed one; AMG_EINVAL otherwise.
 int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
                       Ell<double>* out, const int32_t* anchor, int astride, int64_t ncols, bool any_size,
-                      bool pairs) {
+                      bool single) {
   using graph::DevBuf;
   const int64_t nslices = (n + kSlice - 1) / kSlice;
   // per slice: the sorted offsets (64), their count, the packed width, the kind
@@ -926,8 +936,10 @@ int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_
   e.padded = aligned;
   const int rc = [&]() -> int {
     const bool square = !anchor && e.ncols == n;
-    const bool compact = 2 * (int64_t)st[ST_UNIFORM] >= nslices;
-    if (compact && square && pairs && n >= kPairMinRows) {
+    const bool wide_triples = aligned >= kWideTripleSteps * n && 2 * (int64_t)st[ST_TRIPLES] >= nslices;
+    const bool pays = square ? !(single && wide_triples && n < kTriplesMinRows32) : e.ncols >= kRestrictPatternMinRows;
+    const bool compact = pays && 2 * (int64_t)st[ST_UNIFORM] >= nslices;
+    if (compact && square && !single && n >= kPairMinRows) {
       // the operator itself: slices of 128 rows, two rows per lane, where half of those are uniform too
       // (not where every second slice of 64 rows has a line's end in it with a value of its own)
       const int64_t ns = (n + 2 * kSlice - 1) / (2 * kSlice);
@@ -987,7 +999,7 @@ int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_
 }
 
 int build_ell64(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
-                Ell<double>* out, int64_t ncols, int group, bool pairs) {
+                Ell<double>* out, int64_t ncols, int group, bool single) {
   if (ncols < 0) ncols = n;
   if (group == 0) {
     // lanes per row from the mean row length: about four entries or more per lane
@@ -999,13 +1011,13 @@ int build_ell64(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col
     if (group == 4 && n >= kAlignedWideMinRows && ncols == n) {
       // a coarse stencil (27 points on Q1 boxes) on a large level: one row per lane without
       // column indices moves 4 bytes less per entry than four lanes per row with them
-      const int rc = build_ell_aligned(s, n, ptr, col, val, out, nullptr, 1, -1, false, pairs);
+      const int rc = build_ell_aligned(s, n, ptr, col, val, out, nullptr, 1, -1, false, single);
       if (rc != AMG_EINVAL) return rc;
     }
   }
   if (group != 1 && group != 4 && group != 16 && group != 64) return AMG_EINVAL;
   if (group == 1 && ncols == n) {
-    const int rc = build_ell_aligned(s, n, ptr, col, val, out, nullptr, 1, -1, false, pairs);
+    const int rc = build_ell_aligned(s, n, ptr, col, val, out, nullptr, 1, -1, false, single);
     if (rc != AMG_EINVAL) return rc;  // EINVAL: the slices are not offset-aligned; use the packed layout
   }
   const int R = kSlice / group;

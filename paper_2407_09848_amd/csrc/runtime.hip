@@ -777,7 +777,7 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
     if (fl[F_NOTSPD]) return AMG_ENOTSPD;
     // the fine level keeps one row per lane (the CG kernels read it); coarse levels choose
     AMGP_TRY(build_ell64(s, L.n, L.csr_ptr, L.csr_col, L.csr_val, &L.A64, -1, h->lv.size() == 1 ? 1 : 0,
-                         h->precision == AMG_FP64));
+                         h->precision == AMG_FP32));
     const int64_t per = L.n / h->nbatch;
     if (per <= h->max_coarse) break;
     if (h->aggregation == AMG_AGG_MATCHING) {

@@ -241,7 +241,7 @@ struct AdjVecs {
 };
 
 struct Handle {
-  Arena arena;  // the arrays kept from setup on
+  Arena arena;  // the arrays kept from setup on, and the training workspace
   int nlevels = 0;
   // per-problem weights for AMG_OPTCHEB4 while a differentiable V-cycle runs:
   // dbeta[(p * nlevels + l) * dbeta_k + j - 1], else null (host table used)

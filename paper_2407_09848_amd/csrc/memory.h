@@ -43,10 +43,24 @@ class Arena {
       if (p >= s.base && p < s.base + s.size) return true;
     return false;
   }
-  void release() {
-    for (Slab& s : slabs_) hipFree(s.base);
-    slabs_.clear();
+  void release() { rewind({}); }
+
+  // How far the slabs are in use, and the return to that: later arrays are given back.
+  std::vector<size_t> mark() const {
+    std::vector<size_t> used;
+    for (const Slab& s : slabs_) used.push_back(s.used);
+    return used;
+  }
+  void rewind(const std::vector<size_t>& used) {
+    while (slabs_.size() > used.size()) {
+      hipFree(slabs_.back().base);
+      slabs_.pop_back();
+    }
     total_ = 0;
+    for (size_t i = 0; i < slabs_.size(); ++i) {
+      slabs_[i].used = used[i];
+      if (slabs_[i].size <= kMaxSlab) total_ += slabs_[i].size;
+    }
   }
 
  private:

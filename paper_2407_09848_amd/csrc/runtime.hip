@@ -57,9 +57,6 @@ void free_vecs(Vecs<T>& v, bool own_bx) {
   v = Vecs<T>();
 }
 
-template <typename T>
-void free_adj(std::vector<AdjVecs<T>>& adj);
-
 void drop_graphs(Handle* h) {
   if (h->graphs.empty()) return;
   hipDeviceSynchronize();  // no cached graph may still be executing when it is destroyed
@@ -108,12 +105,6 @@ void release(Handle* h) {
   dev_free(h->cg_q);
   dev_free(h->cg_rold);
   dev_free(h->cg_u);
-  free_adj(h->adj64);
-  free_adj(h->adj32);
-  dev_free(h->tr_buf);
-  dev_free(h->tr_sq);
-  dev_free(h->tr_loss);
-  dev_free(h->tr_partial);
   h->arena.release();
   *h = Handle();
 }
@@ -448,34 +439,11 @@ int alloc_adj(Handle* h, std::vector<AdjVecs<T>>& adj) {
   return AMG_OK;
 }
 
-template <typename T>
-void free_adj(std::vector<AdjVecs<T>>& adj) {
-  for (auto& a : adj) {
-    dev_free(a.u);
-    dev_free(a.xmid);
-    dev_free(a.xpre);
-    dev_free(a.res);
-    dev_free(a.xin);
-    dev_free(a.bout);
-  }
-  adj.clear();
-}
-
-void train_release(Handle* h) {
-  free_adj(h->adj64);
-  free_adj(h->adj32);
-  dev_free(h->tr_buf);
-  dev_free(h->tr_sq);
-  dev_free(h->tr_loss);
-  dev_free(h->tr_partial);
-  h->tr_buf = nullptr;
-  h->tr_sq = nullptr;
-  h->tr_loss = nullptr;
-  h->tr_partial = nullptr;
-}
-
 int train_prepare(Handle* h) {
   if (h->train_ready) return AMG_OK;
+  // from the room that the setup left in the handle's slabs, as far as it goes
+  MemoryScope scope(&h->arena);
+  const std::vector<size_t> before = h->arena.mark();
   h->ck_off.assign(h->nlevels, 0);
   int64_t off = 0;
   for (int l = 0; l < h->nlevels - 1; ++l) {
@@ -488,7 +456,7 @@ int train_prepare(Handle* h) {
   int rc = h->precision == AMG_FP32 ? alloc_adj<float>(h, h->adj32) : alloc_adj<double>(h, h->adj64);
   // driver: r0, z, r1, r2, g, t (6 x n0) + two checkpoints
   if (rc == AMG_OK &&
-      hipMalloc(&h->tr_buf, w * (size_t)(6 * n0 + 2 * std::max<int64_t>(h->ck_count, 1))) != hipSuccess) {
+      keep_malloc(&h->tr_buf, w * (size_t)(6 * n0 + 2 * std::max<int64_t>(h->ck_count, 1))) != hipSuccess) {
     h->tr_buf = nullptr;
     rc = AMG_ENOMEM;
   }
@@ -496,7 +464,12 @@ int train_prepare(Handle* h) {
   if (rc == AMG_OK) rc = dalloc(&h->tr_loss, 1 + h->nbatch);
   if (rc == AMG_OK) rc = dalloc(&h->tr_partial, 64 * (int64_t)std::max(2 * h->nbatch, 8));
   if (rc != AMG_OK) {  // nothing half-allocated is kept: a later call starts over
-    train_release(h);
+    h->adj64.clear();
+    h->adj32.clear();
+    h->tr_buf = nullptr;
+    h->tr_sq = h->tr_loss = nullptr;
+    h->tr_partial = nullptr;
+    h->arena.rewind(before);
     return rc;
   }
   h->train_ready = true;

@@ -136,6 +136,26 @@ int main() {
   CHECK(card::used == 0);
 }
 """,
+    # arrays taken after a mark are given back, the room behind it is used again
+    "marks": r"""
+int main() {
+  Arena arena;
+  char *a, *b, *c, *d;
+  {
+    MemoryScope scope(&arena);
+    CHECK(keep_malloc(&a, MB) == hipSuccess);
+    const size_t held = card::used;
+    const std::vector<size_t> mark = arena.mark();
+    CHECK(keep_malloc(&b, MB / 2) == hipSuccess && card::used == held);
+    CHECK(keep_malloc(&c, 30 * MB) == hipSuccess && card::used == held + 30 * MB);
+    arena.rewind(mark);
+    CHECK(card::used == held && arena.owns(a) && !arena.owns(c));
+    CHECK(keep_malloc(&d, MB / 2) == hipSuccess && d == b);
+  }
+  arena.release();
+  CHECK(card::used == 0);
+}
+""",
     # temporaries: one of about the size is taken again, all are returned with the scope
     "temporaries": r"""
 int main() {

@@ -51,7 +51,6 @@ PEAK_HBM = 8000.0  # GB/s, MI355X HBM3E
 KIND_NAMES = {0: "l1jacobi", 1: "cheb4", 2: "optcheb4", 3: "optcheb1"}
 FUSED_PROLONG_MAX_ROWS = 1 << 20  # box levels up to this size carry the prolongation in the smoother
 STREAM_MIN_BLOCKS = 12288  # levels above this many 256-row blocks take the streaming kernels
-PAIR_MIN_ROWS = 1 << 22  # FP64 levels of uniform slices with this many rows are served two rows per lane
 WIDE_MIN_STEPS = 24  # streaming offset-aligned levels with this many stored steps per row take wide batches
 
 
@@ -59,18 +58,25 @@ WIDE_MIN_STEPS = 24  # streaming offset-aligned levels with this many stored ste
 # Byte models: the bytes each kernel must move in the layout it reads (values of w bytes,
 # int32 indices, gathered vectors counted once).  M is the matrix's bytes in its layout:
 # offset-aligned slices w per stored entry plus a 4-byte offset per 64, packed slices w + 4; with
-# uniform slices an 8-byte descriptor per slice, w + 12 per pattern step, and only the dense
-# slices' entries.
+# uniform slices an 8-byte descriptor per slice of 64 rows per row of a lane, per pattern step a
+# value, an 8-byte mask per row of a lane and an offset, and only the dense slices' entries; of mirrored
+# diagonals the stored half and 4 bytes per 64 rows.
 # ---------------------------------------------------------------------------
-def slice_bytes(n, w, values, patterned, steps):
-    tot = values * w + 4 * (values // 64)
-    return tot + 8 * ((n + 63) // 64) + (w + 12) * steps if patterned else tot
+def slice_bytes(n, w, values, patterned, steps, rows=1):
+    if patterned:
+        return values * w + 4 * (values // (64 * rows)) + 8 * -(-n // (64 * rows)) + (w + 4 + 8 * rows) * steps
+    return values * w + 4 * (values // 64)
 
 
 def matrix_bytes(amg, h, level, w):
     padded, _, aligned = amg.amg_level_layout(h, level)
     n, _ = amg.amg_level_info(h, level)
-    return slice_bytes(n, w, *amg.amg_level_patterns(h, level)) if aligned else padded * (w + 4)
+    if not aligned:
+        return padded * (w + 4)
+    values, patterned, steps = amg.amg_level_patterns(h, level)
+    if not patterned and values < padded:
+        return values * w + 4 * -(-n // 64)
+    return slice_bytes(n, w, values, patterned, steps, amg.amg_level_rows_per_lane(h, level))
 
 
 def level_table(amg, h, w):
@@ -576,10 +582,9 @@ def main():
     wide = streams and aligned and lanes == 1 and padded >= WIDE_MIN_STEPS * n0
     values, patterned, steps = amg.amg_level_patterns(h, 0)
     variant = 2 if patterned else int(wide)  # slices: narrow, wide, uniform
-    # large levels of uniform slices and mirrored diagonals are served two rows per lane
     mirrored = aligned and not patterned and values < padded
-    pairs = mirrored or (patterned and n0 >= PAIR_MIN_ROWS)
-    kernel = (f"k_pair_fused<double,0,true,{str(streams).lower()},{3 if mirrored else 2}>" if pairs else
+    rows = amg.amg_level_rows_per_lane(h, 0)
+    kernel = (f"k_pair_fused<double,0,true,{str(streams).lower()},{3 if mirrored else 2}>" if rows == 2 else
               f"k_fused<double,0,true,{str(streams).lower()},1,{variant}>")
     u_path = wide and args.kind != 0 and args.degree >= 2
     value = solve_bytes(lv64, M0, 8, args.kind, args.degree, it, False, u_path) / (ms * 1e-3) / 1e9
@@ -598,9 +603,10 @@ def main():
                 "kernel": f"{kernel} (fine level, {args.workload} {args.size}^3)",
                 "bytes_per_launch": int(step_bytes), "avg_launch_us": round(t_step * 1e3, 2),
                 "layout": {"entries": int(padded), "stored_entries": int(values), "uniform_slices": int(patterned),
-                           "pattern_steps": int(steps), "lanes_per_row": lanes, "offset_aligned": aligned,
-                           "bytes_per_launch": "8 per stored entry + 4 per 64, 8 per slice and 20 per pattern step "
-                                               "where slices are uniform, + 56 per row"},
+                           "pattern_steps": int(steps), "lanes_per_row": lanes, "rows_per_lane": rows,
+                           "offset_aligned": aligned,
+                           "bytes_per_launch": "8 per stored entry + 4 per 64 rows' step; where slices are uniform, 8 "
+                                               f"per {64 * rows} rows and {12 + 8 * rows} per pattern step; + 56 per row"},
                 "csr_model": {"bytes_per_launch": int(csr_bytes), "formula": "12 nnz + 60 n",
                               "GBps": round(csr_bytes / (t_step * 1e-3) / 1e9, 1),
                               "note": "counts column indices and row pointers the offset-aligned layout "

@@ -448,8 +448,8 @@ int sweep_operator(hipStream_t s, int64_t n, int64_t np, const int32_t* ptr, con
     AMGP_HIP(hipMemsetAsync(X[1], 0, bytes, s));
     hipLaunchKernelGGL(k_diagonal, dim3(grid_for(n)), dim3(kBlock), 0, s, (int)n, (int)np, minv, X[0]);
     for (int k = 1; k < sweeps; ++k) {
-      hipLaunchKernelGGL(k_sweep_columns, dim3((unsigned)n, grid_for(n, 256)), dim3(256), 0, s, (int)n, (int)np, ptr, col,
-                         val, minv, (const double*)X[0], X[1]);
+      hipLaunchKernelGGL(k_sweep_columns, dim3((unsigned)n, grid_for(n, 256)), dim3(256), 0, s, (int)n, (int)np, ptr,
+                         col, val, minv, (const double*)X[0], X[1]);
       std::swap(X[0], X[1]);
     }
     hipLaunchKernelGGL(k_pack_tiles, dim3(ntiles), dim3(256), 0, s, (int)np, (const double*)X[0], *packed);

@@ -805,8 +805,8 @@ int galerkin_from_restriction(hipStream_t s, const Csr& A, const Csr& R, const i
                        temp_malloc(&o.val, sizeof(double) * std::max<int64_t>(o.nnz, 1)) != hipSuccess))
     rc = AMG_ENOMEM;
   if (rc == AMG_OK) {
-    hipLaunchKernelGGL(k_galerkin_rows<true>, grid, block, 0, s, A.ptr, A.col, A.val, children, R.ptr, R.col, agg, o.ptr,
-                       o.col, o.val);
+    hipLaunchKernelGGL(k_galerkin_rows<true>, grid, block, 0, s, A.ptr, A.col, A.val, children, R.ptr, R.col, agg,
+                       o.ptr, o.col, o.val);
     if (hipGetLastError() != hipSuccess) rc = AMG_EHIP;
   }
   if (rc != AMG_OK) {

@@ -124,9 +124,9 @@ __global__ void k_ell_fill(int64_t n, int64_t ncols, int64_t nslices, int G, con
 
 // Layout of every slice of 64 RPL rows (RPL rows per lane of the kernels), one wavefront per slice,
 // its lanes on consecutive entries of the slice's rows (contiguous in CSR, so the loads coalesce; one
-// row per lane instead read 20 KB a wavefront through its own cache lines, 33 ms against 5 ms for the kinds of the 27-point 320^3
-// matrix).  The slice's distinct column offsets (col - row, or col - anchor[row * astride]) go into
-// an LDS hash set.
+// row per lane instead read 20 KB a wavefront through its own cache lines, 33 ms against 5 ms for the
+// kinds of the 27-point 320^3 matrix).  The slice's distinct column offsets (col - row, or col -
+// anchor[row * astride]) go into an LDS hash set.
 //
 // TABLES = false: the offsets, sorted, offs[s * 64 + t], their count width[s] (-1 when there are more
 // than 64), the longest row lwidth[s], and with kind given the kind of the slice (see Ell): per step

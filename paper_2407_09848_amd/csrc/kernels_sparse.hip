@@ -2,7 +2,8 @@
 // recurrence steps, grid transfers and the CG vector updates with
 // deterministic two-stage reductions.
 //
-// Layout and launch shape: one row per lane, 256-thread blocks (4 waves), the
+// Layout and launch shape: one row per lane (two on large FP64 levels of uniform slices and on mirrored
+// diagonals, 4 to 64 lanes per row on levels of long rows), 256-thread blocks (4 waves), the
 // matrix in sliced ELL with 64-row slices so that every load of val/col by a
 // wavefront is one contiguous 512 B (float64) segment.  On levels of up to
 // 3.1M rows, blocks are remapped so that each of the 8 XCDs (which receive
@@ -484,8 +485,8 @@ __device__ __forceinline__ T slice_sum(EllView<T> A, int s, int lane, int r, Gf 
   if constexpr (std::is_same_v<T, float>)
     return aligned_sum_f32<NT>(A.val, beg, end, lane, off, r, A.last, g);
   else
-    return aligned_sum_f64<NT, Gf, true, V == V_WIDE ? kWideBatch : uniform_slices(V) ? 4 : kAlignedBatch>(A.val, beg, end, lane, off, r,
-                                                                                   A.last, g);
+    return aligned_sum_f64<NT, Gf, true, V == V_WIDE ? kWideBatch : uniform_slices(V) ? 4 : kAlignedBatch>(
+        A.val, beg, end, lane, off, r, A.last, g);
 }
 
 // Rows with G lanes each (Ell::group): thread t of the grid serves row t / G, and a
@@ -1226,8 +1227,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(int64_t n, const double* _
 // ---------------------------------------------------------------------------
 // Two rows per lane, for FP64 levels of mirrored diagonals and large ones of uniform slices: a
 // wavefront serves 128 consecutive rows, lane l the rows 2 l and 2 l + 1 of them, so that values, row
-// vectors and gathers of a pair come with one load of twice the width.  Every row's products keep their order; partial sums of dot
-// products cover 512 rows a block.
+// vectors and gathers of a pair come with one load of twice the width.  Every row's products keep their
+// order; partial sums of dot products cover 512 rows a block.
 // ---------------------------------------------------------------------------
 constexpr int kPair = 2;
 
@@ -1312,8 +1313,8 @@ __device__ __forceinline__ V2<T> pair_pattern_sum(EllView<T> A, int beg, int w, 
     for (int u = 0; u < B; ++u) {
       const int q = beg + min(t + u, w - 1);
       v[u] = A.pval(2)[q];
-      gv[u] = FULL ? g.at2(A.poff(2)[q], r)
-                   : KIND == SLICE_HALVES ? half2<T>(g, r, A.poff(2)[q], A.last) : clamp2<T>(g, r + A.poff(2)[q], A.last);
+      const int off = A.poff(2)[q];
+      gv[u] = FULL ? g.at2(off, r) : KIND == SLICE_HALVES ? half2<T>(g, r, off, A.last) : clamp2<T>(g, r + off, A.last);
     }
 #pragma unroll
     for (int u = 0; u < B; ++u) {
@@ -1488,8 +1489,8 @@ __global__ __launch_bounds__(kBlock) void k_pair_fused_keep_x(int64_t n, EllView
                                                               const T* __restrict__ gold, T* __restrict__ gnew,
                                                               const T* rin, T* rout, T alpha, T c) {
   for_pair(n, [&](auto whole, int64_t i) {
-    pair_step<T, MODE, true, NT, false, decltype(whole)::value, V>(i, n, A, minv, gold, gnew, rin, rout, nullptr, alpha, c,
-                                                                T(0), T(0), Wt(), Wt(), Prol<T>());
+    pair_step<T, MODE, true, NT, false, decltype(whole)::value, V>(i, n, A, minv, gold, gnew, rin, rout, nullptr, alpha,
+                                                                   c, T(0), T(0), Wt(), Wt(), Prol<T>());
   });
 }
 
@@ -1503,8 +1504,8 @@ __global__ __launch_bounds__(kBlock) void k_pair_fused_dot(int64_t n, EllView<T>
   double v = 0.0, u = 0.0;
   for_pair(n, [&](auto whole, int64_t i) {
     constexpr bool WHOLE = decltype(whole)::value;
-    const V2<T> xn = pair_step<T, MODE, false, NT, true, WHOLE, V>(i, n, A, minv, gold, nullptr, rin, nullptr, x, alpha, c,
-                                                                w, wprev, wv, wpv, pr);
+    const V2<T> xn = pair_step<T, MODE, false, NT, true, WHOLE, V>(i, n, A, minv, gold, nullptr, rin, nullptr, x, alpha,
+                                                                   c, w, wprev, wv, wpv, pr);
     const V2<double> d = ld_pair<NT, WHOLE>(dr, i, n);  // 0 past n
     v = d.x * (double)xn.x + d.y * (double)xn.y;
     if (drold) {
@@ -1853,11 +1854,13 @@ int with_group(int group, F&& f) {
 
 template <typename T>
 int launch_spmv(hipStream_t s, const Ell<T>& A, const T* x, T* y) {
-    if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
-      hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, false, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A),
-                         (const T*)nullptr, x, y);
-    });
+  if constexpr (std::is_same_v<T, double>) {
+    if (paired(A))
+      return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
+        hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, false, decltype(v)::value>), gr, dim3(kBlock), 0, s,
+                           A.n, view(A), (const T*)nullptr, x, y);
+      });
+  }
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const unsigned g = xcd_grid(A.n * G);
@@ -1873,10 +1876,13 @@ int launch_spmv(hipStream_t s, const Ell<T>& A, const T* x, T* y) {
 
 template <typename T>
 int launch_residual(hipStream_t s, const Ell<T>& A, const T* b, const T* x, T* r) {
-    if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
-      hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, true, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A), b, x, r);
-    });
+  if constexpr (std::is_same_v<T, double>) {
+    if (paired(A))
+      return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
+        hipLaunchKernelGGL((k_pair_spmv<T, decltype(nt)::value, true, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n,
+                           view(A), b, x, r);
+      });
+  }
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const unsigned g = xcd_grid(A.n * G);
@@ -1938,21 +1944,23 @@ template <typename T>
 int launch_first2_zero(hipStream_t s, int mode, bool store, const Ell<T>& A, const T* minv, const T* b, T* gnew,
                        T* r, T* x, double c1, double alpha, double c, double w1, double w2, Wt w1v, Wt w2v,
                        const T* u) {
-    if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
-      auto go = [&](auto m, auto st, auto hu) {
-        hipLaunchKernelGGL((k_pair_first2_zero<T, decltype(m)::value, decltype(st)::value, decltype(nt)::value,
-                                               decltype(hu)::value, decltype(v)::value>),
-                           gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, gnew, r, x, (T)c1, (T)alpha, (T)c, (T)w1,
-                           (T)w2, w1v, w2v, u);
-      };
-      with_mode_store(mode, store, [&](auto m, auto st) {
-        if (u)
-          go(m, st, std::true_type());
-        else
-          go(m, st, std::false_type());
+  if constexpr (std::is_same_v<T, double>) {
+    if (paired(A))
+      return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
+        auto go = [&](auto m, auto st, auto hu) {
+          hipLaunchKernelGGL((k_pair_first2_zero<T, decltype(m)::value, decltype(st)::value, decltype(nt)::value,
+                                                 decltype(hu)::value, decltype(v)::value>),
+                             gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, gnew, r, x, (T)c1, (T)alpha, (T)c, (T)w1,
+                             (T)w2, w1v, w2v, u);
+        };
+        with_mode_store(mode, store, [&](auto m, auto st) {
+          if (u)
+            go(m, st, std::true_type());
+          else
+            go(m, st, std::false_type());
+        });
       });
-    });
+  }
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const dim3 gr(xcd_grid(A.n * G));
@@ -1990,14 +1998,17 @@ void go_first_res(dim3 gr, hipStream_t s, int mode, EllView<T> A, int64_t n, con
 template <typename T>
 int launch_first_res(hipStream_t s, int mode, const Ell<T>& A, const T* minv, const T* b, const T* x, T* r,
                      T* g, double c, Prol<T> pr) {
-    if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
-      auto go = [&](auto m, auto prol) {
-        hipLaunchKernelGGL((k_pair_first_res<T, decltype(m)::value, decltype(nt)::value, decltype(prol)::value, decltype(v)::value>), gr,
-                           dim3(kBlock), 0, s, A.n, view(A), minv, b, x, pr, r, g, (T)c);
-      };
-      with_mode_store(mode, pr.agg != nullptr, go);
-    });
+  if constexpr (std::is_same_v<T, double>) {
+    if (paired(A))
+      return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
+        auto go = [&](auto m, auto prol) {
+          hipLaunchKernelGGL((k_pair_first_res<T, decltype(m)::value, decltype(nt)::value, decltype(prol)::value,
+                                               decltype(v)::value>),
+                             gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, x, pr, r, g, (T)c);
+        };
+        with_mode_store(mode, pr.agg != nullptr, go);
+      });
+  }
   if (pr.agg) {
     if (A.group != 1) return AMG_EINVAL;
     const dim3 gr(xcd_grid(A.n)), bl(kBlock);
@@ -2053,18 +2064,21 @@ template <typename T>
 int launch_fused(hipStream_t s, int mode, bool store, const Ell<T>& A, const T* minv, const T* gold, T* gnew,
                  const T* rin, T* rout, T* x, double alpha, double c, double w, double wprev, Wt wv, Wt wpv,
                  Prol<T> pr) {
-    if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
-      with_mode_store(mode, store, [&](auto m, auto st) {
-        constexpr int MODE = decltype(m)::value;
-        if (!x)  // a stored step that leaves x alone
-          hipLaunchKernelGGL((k_pair_fused_keep_x<T, MODE, decltype(nt)::value, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A),
-                             minv, gold, gnew, rin, rout, (T)alpha, (T)c);
-        else
-          hipLaunchKernelGGL((k_pair_fused<T, MODE, decltype(st)::value, decltype(nt)::value, decltype(v)::value>), gr, dim3(kBlock), 0, s,
-                             A.n, view(A), minv, gold, gnew, rin, rout, x, (T)alpha, (T)c, (T)w, (T)wprev, wv, wpv, pr);
+  if constexpr (std::is_same_v<T, double>) {
+    if (paired(A))
+      return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
+        with_mode_store(mode, store, [&](auto m, auto st) {
+          constexpr int MODE = decltype(m)::value;
+          if (!x)  // a stored step that leaves x alone
+            hipLaunchKernelGGL((k_pair_fused_keep_x<T, MODE, decltype(nt)::value, decltype(v)::value>), gr,
+                               dim3(kBlock), 0, s, A.n, view(A), minv, gold, gnew, rin, rout, (T)alpha, (T)c);
+          else
+            hipLaunchKernelGGL((k_pair_fused<T, MODE, decltype(st)::value, decltype(nt)::value, decltype(v)::value>),
+                               gr, dim3(kBlock), 0, s, A.n, view(A), minv, gold, gnew, rin, rout, x, (T)alpha, (T)c,
+                               (T)w, (T)wprev, wv, wpv, pr);
+        });
       });
-    });
+  }
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const dim3 gr(xcd_grid(A.n * G));
@@ -2084,15 +2098,17 @@ template <typename T>
 int launch_fused_dot(hipStream_t s, int mode, const Ell<T>& A, const T* minv, const T* gold, const T* rin, T* x,
                      double alpha, double c, double w, double wprev, Wt wv, Wt wpv, Prol<T> pr, const double* dr,
                      const double* drold, double* partial, unsigned* nblocks) {
-    if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
-      with_mode_store(mode, false, [&](auto m, auto) {
-        hipLaunchKernelGGL((k_pair_fused_dot<T, decltype(m)::value, decltype(nt)::value, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n,
-                           view(A), minv, gold, rin, x, (T)alpha, (T)c, (T)w, (T)wprev, wv, wpv, pr, dr, drold,
-                           partial);
+  if constexpr (std::is_same_v<T, double>) {
+    if (paired(A))
+      return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
+        with_mode_store(mode, false, [&](auto m, auto) {
+          hipLaunchKernelGGL((k_pair_fused_dot<T, decltype(m)::value, decltype(nt)::value, decltype(v)::value>), gr,
+                             dim3(kBlock), 0, s, A.n, view(A), minv, gold, rin, x, (T)alpha, (T)c, (T)w, (T)wprev, wv,
+                             wpv, pr, dr, drold, partial);
+        });
+        *nblocks = gr.x;
       });
-      *nblocks = gr.x;
-    });
+  }
   if (A.group != 1) return AMG_EINVAL;
   const dim3 gr(xcd_grid(A.n)), bl(kBlock);
   with_variant<true>(A, streamed(gr.x), [&](auto nt, auto v) {
@@ -2117,10 +2133,13 @@ template int launch_fused_dot<float>(hipStream_t, int, const Ell<float>&, const 
 
 template <typename T>
 int launch_jacobi(hipStream_t s, const Ell<T>& A, const T* minv, const T* b, const T* xold, T* xnew) {
-    if constexpr (std::is_same_v<T, double>)
-    if (paired(A)) return with_pairs(A, [&](auto, auto v, dim3 gr) {
-      hipLaunchKernelGGL((k_pair_jacobi<T, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, xold, xnew);
-    });
+  if constexpr (std::is_same_v<T, double>) {
+    if (paired(A))
+      return with_pairs(A, [&](auto, auto v, dim3 gr) {
+        hipLaunchKernelGGL((k_pair_jacobi<T, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A), minv, b, xold,
+                           xnew);
+      });
+  }
   return with_group(A.group, [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     const dim3 gr(xcd_grid(A.n * G)), bl(kBlock);
@@ -2245,14 +2264,15 @@ template int launch_dot2<float>(hipStream_t, int64_t, const double*, const float
 template <typename TZ>
 int launch_spmv_dot_p(hipStream_t s, const Ell<double>& A, const double* scal, const TZ* z, const double* pold,
                       double* pnew, double* q, double* partial, double* x, unsigned* nblocks) {
-  if (paired(A)) return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
+  if (paired(A))
+    return with_pairs(A, [&](auto nt, auto v, dim3 gr) {
       constexpr bool NT = decltype(nt)::value;
       if constexpr (NT) {
         const unsigned g = xcd_grid(A.n);
         hipLaunchKernelGGL((k_form_p<true, TZ>), dim3(g), dim3(kBlock), 0, s, A.n, scal, z, pold, pnew, x);
       }
-      hipLaunchKernelGGL((k_pair_spmv_dot_p<NT, TZ, NT, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A), scal, z, pold, pnew, q,
-                         partial, NT ? nullptr : x);
+      hipLaunchKernelGGL((k_pair_spmv_dot_p<NT, TZ, NT, decltype(v)::value>), gr, dim3(kBlock), 0, s, A.n, view(A),
+                         scal, z, pold, pnew, q, partial, NT ? nullptr : x);
       *nblocks = gr.x;
     });
   const unsigned g = xcd_grid(A.n);

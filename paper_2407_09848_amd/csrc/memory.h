@@ -1,7 +1,8 @@
-// Device memory of a hierarchy.  A setup makes some 130 allocations and as many releases, at 25-40
-// us each in the runtime (a third of the time of a 1.1M-row setup and its destruction).  The arrays
-// a handle keeps therefore come from slabs that the handle owns, and the setup's temporary arrays
-// are reused within that setup.
+// Device memory of a hierarchy.  A setup makes some 130 allocations and as many releases.  Each costs 1 us
+// where the runtime holds a freed piece of that size, 10 to 40 us where it maps one again and about 250 us
+// where the device's memory is new to the process (a third of the time of a 1.1M-row setup and its
+// destruction).  The arrays a handle keeps therefore come from slabs that the handle owns, and the
+// setup's temporary arrays are reused within that setup.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -748,7 +748,7 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
     int fl[F_NFLAG];
     AMGP_TRY(read_flags(h, s, fl));
     if (fl[F_NOTSPD]) return AMG_ENOTSPD;
-    // the fine level keeps one row per lane (the CG kernels read it); coarse levels choose
+    // the fine level takes no lanes per row above one (the CG kernels read it); coarse levels choose
     AMGP_TRY(build_ell64(s, L.n, L.csr_ptr, L.csr_col, L.csr_val, &L.A64, -1, h->lv.size() == 1 ? 1 : 0,
                          h->precision == AMG_FP32));
     const int64_t per = L.n / h->nbatch;
@@ -825,10 +825,14 @@ int setup(Handle* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32
   }
   h->nlevels = (int)h->lv.size();
   // The coarsest level's sweeps from zero are one symmetric operator: on few rows it is formed here,
-  // by the same sweeps on the unit vectors, and applied as one dense product.  Measured on 1.05M rows of
-  // the anisotropic problem (VBM, 1.5k coarsest rows, 30 sweeps, 111 iterations): 34.0 -> 23.9 ms
-  // per solve for 1.5 ms more setup, 13 us instead of 30 launches of 3.8 us.  Above 2048 rows
-  // forming it costs more than a solve gains; a few sweeps are as fast as the product's two launches.
+  // by the same sweeps on the unit vectors, and applied as one dense product of two launches.  Measured on
+  // 1.05M rows of the anisotropic problem (VBM, 1.5k coarsest rows, 30 sweeps, 111 iterations): 34.0 -> 23.9
+  // ms per solve for 1.5 ms more setup.  By itself (27-point rows, sweeps -> product, and what forming it adds
+  // to the setup): 2048 rows, 4 sweeps 24 -> 20 us, 0.3 ms; 8 sweeps 40 -> 20 us, 0.6 ms; 30 sweeps 137 -> 19 us,
+  // 1.7 ms.  4096 rows, 8 sweeps 40 -> 24 us, 2.3 ms; 30 sweeps 138 -> 24 us, 6.6 ms.  So with fewer than 8
+  // sweeps, or above 2048 rows, it takes some 60 to 140 applications to come out ahead, more than the cycles of
+  // many a solve, and 14 to 28 in between.  FP32 hierarchies, whose sweeps run in FP32, keep these (8 sweeps on 2048
+  // rows 41 us, 30 sweeps 130 us; the product would take 25).
   if (h->coarse_sweeps >= kDenseSweepsMin && h->precision == AMG_FP64 && h->nbatch == 1 &&
       h->lv.back().n <= kDenseSweepsMaxRows) {
     Level& L = h->lv.back();

@@ -458,10 +458,11 @@ int build_ell64(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col
 int build_ell32(hipStream_t s, const Ell<double>& a, Ell<float>* out);
 // offset-aligned slices (one row per lane) with the offsets taken against anchor[r * astride]
 // (null: the row r) and columns clamped into [0, ncols) (-1: n); AMG_EINVAL when a slice has more
-// than 64 offsets or (unless any_size) the layout is more than 10% larger than the packed one
+// than 64 offsets or (unless any_size) the layout is more than 10% larger than the packed one; patterns:
+// uniform slices may be kept as such
 int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
                       Ell<double>* out, const int32_t* anchor = nullptr, int astride = 1, int64_t ncols = -1,
-                      bool any_size = false, bool single = false);
+                      bool any_size = false, bool single = false, bool patterns = true);
 // box aggregates of edge e; children (2x2x2 boxes only) may be null
 int launch_aggregates(hipStream_t s, int nx, int ny, int nz, int nbatch, int e, int32_t* agg, int32_t* children,
                       int* cnx, int* cny, int* cnz);

@@ -761,16 +761,12 @@ int launch_l1_diag(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* 
 
 // Uniform slices are kept as patterns when they are at least half of the matrix's (a matrix of
 // constant coefficients: all but the slices that cross an odd boundary); below that most slices
-// stay dense and the plain kernels, which have no pattern path, serve them faster.  Two kinds of levels
-// small enough for the L2 caches take longer with patterns than with their stored values and keep those:
-// - wide triples (27 points) in FP32 hierarchies below 2^18 rows (time of a step of a smoother application,
-//   dense -> patterns: 40^3 rows 3.3 -> 4.0 us, 56^3 4.0 -> 4.5, 64^3 5.3 -> 4.8, 80^3 11.4 -> 7.0; FP64
-//   40^3 4.2 -> 4.3, 48^3 5.3 -> 4.8);
-// - restriction products of fine levels below 3 2^17 rows (27 points, 50^3 rows 6.1 -> 6.7 us, 64^3 6.1 -> 7.0,
-//   80^3 10.8 -> 6.9; 7 points 64^3 4.5 -> 4.8, 80^3 5.8 -> 4.8).
+// stay dense and the plain kernels, which have no pattern path, serve them faster.  Wide triples (27
+// points) in FP32 hierarchies below 2^18 rows keep their values too, which the L2 caches hold (time of a step
+// of a smoother application, values -> patterns: 40^3 rows 3.3 -> 4.0 us, 56^3 4.0 -> 4.5, 64^3 5.3 -> 4.8,
+// 80^3 11.4 -> 7.0; FP64 40^3 4.2 -> 4.3, 48^3 5.3 -> 4.8).
 constexpr int kWideTripleSteps = 24;
 constexpr int64_t kTriplesMinRows32 = int64_t(1) << 18;
-constexpr int64_t kRestrictPatternMinRows = int64_t(3) << 17;
 constexpr int64_t kUniformMaxRows = int64_t(1) << 28;  // 32-bit byte offsets of the full slices' gathers
 
 // Mirrored diagonals for the matrix of the given slices when it is large enough to be bound by its
@@ -911,7 +907,7 @@ static int slice_stats(hipStream_t s, int64_t nslices, const int32_t* wd, const 
 // offsets and the layout is at most 10% larger than the packed one; AMG_EINVAL otherwise.
 int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_t* col, const double* val,
                       Ell<double>* out, const int32_t* anchor, int astride, int64_t ncols, bool any_size,
-                      bool single) {
+                      bool single, bool patterns) {
   using graph::DevBuf;
   const int64_t nslices = (n + kSlice - 1) / kSlice;
   // per slice: the sorted offsets (64), their count, the packed width, the kind
@@ -937,8 +933,8 @@ int build_ell_aligned(hipStream_t s, int64_t n, const int32_t* ptr, const int32_
   const int rc = [&]() -> int {
     const bool square = !anchor && e.ncols == n;
     const bool wide_triples = aligned >= kWideTripleSteps * n && 2 * (int64_t)st[ST_TRIPLES] >= nslices;
-    const bool pays = square ? !(single && wide_triples && n < kTriplesMinRows32) : e.ncols >= kRestrictPatternMinRows;
-    const bool compact = pays && 2 * (int64_t)st[ST_UNIFORM] >= nslices;
+    const bool compact = patterns && !(single && wide_triples && n < kTriplesMinRows32) &&
+                         2 * (int64_t)st[ST_UNIFORM] >= nslices;
     if (compact && square && !single && n >= kPairMinRows) {
       // the operator itself: slices of 128 rows, two rows per lane, where half of those are uniform too
       // (not where every second slice of 64 rows has a line's end in it with a value of its own)

@@ -336,32 +336,47 @@ __device__ __forceinline__ double dpp_shift(double end, double v) {
 // nine triples per batch instead of three the whole solve took 177 instead of 160 ms (473 ms with
 // dense slices).  7-point 128^3 level: step that keeps x 28.1 -> 18.6 us.
 
-// Any pattern: one gather per step.  A batch's steps are read whole, so that they come with few wide scalar
-// loads: those past the pattern's end (the next pattern's, or the room behind the last) are not used.
-// With every step's index clamped each took loads of its own, on which small levels waited: FP32 steps of a
-// smoother application at 7 points 80^3 4.9 -> 3.9 us (dense slices 4.2), 21 points 64^3 5.7 -> 4.1 (dense
-// 4.3), 5 points 724^2 4.6 -> 4.1 (dense 4.0).
+// Any pattern: one gather per step.  FP32 batches are read whole, so that a batch comes with few wide scalar
+// loads: the steps past the pattern's end (the next pattern's, or the room behind the last) are not used.
+// With every step's index clamped each takes loads of its own, on which cached FP32 levels waited (a step of
+// a smoother application at 7 points 80^3 4.9 -> 4.0 us, stored values 4.3; 21 points 64^3 5.7 -> 4.2,
+// 4.3; 5 points 724^2 4.6 -> 3.9, 4.0).  FP64 batches keep the clamp: their values and masks take twice the
+// scalar registers (27 points 80^3 8.9 -> 9.5 us, restriction products of evicted levels 10.7 -> 13).
 template <bool FULL, typename T, typename Gf>
 __device__ __forceinline__ T pattern_sum(EllView<T> A, int beg, int w, int r, Gf g) {
   constexpr int B = 8;
   T acc = T(0);
   for (int t = 0; t < w; t += B) {
-    T gv[B];
-    int off[B];
-    // the steps past the last one (of the next pattern, or the room behind the last) are not used
+    T gv[B], v[B];
+    // the value as loaded, then masked: a load under the mask would be one per lane
+    auto masked = [&](T x, int q) {
+      if constexpr (FULL) return x; else return __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q]) ? x : T(0);
+    };
+    if constexpr (std::is_same_v<T, float>) {
+      int off[B];
 #pragma unroll
-    for (int u = 0; u < B; ++u) off[u] = A.poff(1)[beg + t + u];
+      for (int u = 0; u < B; ++u) {
+        off[u] = A.poff(1)[beg + t + u];
+        v[u] = A.pval(1)[beg + t + u];
+        v[u] = masked(v[u], beg + t + u);
+      }
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const int o = t + u < w ? off[u] : off[0];
-      gv[u] = FULL ? g.at(o, r) : g(min(max(r + o, 0), A.last));
+      for (int u = 0; u < B; ++u) {
+        const int o = t + u < w ? off[u] : off[0];
+        gv[u] = FULL ? g.at(o, r) : g(min(max(r + o, 0), A.last));
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int q = beg + min(t + u, w - 1);
+        v[u] = A.pval(1)[q];
+        v[u] = masked(v[u], q);
+        gv[u] = FULL ? g.at(A.poff(1)[q], r) : g(min(max(r + A.poff(1)[q], 0), A.last));
+      }
     }
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      T v = A.pval(1)[beg + t + u];
-      if constexpr (!FULL) v = __builtin_amdgcn_inverse_ballot_w64(A.pmask()[beg + t + u]) ? v : T(0);
-      if (t + u < w) acc += v * gv[u];
-    }
+    for (int u = 0; u < B; ++u)
+      if (t + u < w) acc += v[u] * gv[u];
   }
   return acc;
 }
@@ -398,13 +413,13 @@ __device__ __forceinline__ T pattern_triples(EllView<T> A, int q, int lane, int 
   return acc;
 }
 
-// Triples per batch: on small FP64 levels (V_SMALL) and cached FP32 ones all nine of a 27-point row, since a step
-// waits for each batch there (FP64 16^3 rows 4.5 -> 4.1 us, 40^3 4.6 -> 4.3; FP32 100^3 10.4 -> 9.9, 128^3 20.1
-// -> 18.9); with the registers of nine, larger FP64 levels lose (100^3 14.9 -> 17.3 us).
+// Triples per batch: on small FP64 levels (V_SMALL) all nine of a 27-point row, since a step waits for each
+// batch there (16^3 rows 4.5 -> 4.1 us, 40^3 4.6 -> 4.3); with the registers of nine, larger levels lose
+// (100^3 14.9 -> 17.3 us; FP32 9-point levels 3%).
 constexpr int kTripleBatch = 3, kTripleBatchAll = 9;
-template <typename T, bool NT, int V>
+template <int V>
 constexpr int triple_batch() {
-  return V == V_SMALL || (std::is_same_v<T, float> && !NT) ? kTripleBatchAll : kTripleBatch;
+  return V == V_SMALL ? kTripleBatchAll : kTripleBatch;
 }
 template <int BATCH, bool FULL, typename T, typename Gf>
 __device__ __forceinline__ T pattern_triples_sum(EllView<T> A, int beg, int w, int lane, int r, Gf g) {
@@ -469,8 +484,8 @@ __device__ __forceinline__ T slice_sum(EllView<T> A, int s, int lane, int r, Gf 
     const int b = __builtin_amdgcn_readfirstlane(d.x), info = __builtin_amdgcn_readfirstlane(d.y);
     const int w = info >> 4;
     if (info & SLICE_TRIPLES) {
-      if (info & SLICE_FULL) return pattern_triples_sum<triple_batch<T, NT, V>(), true>(A, b, w, lane, r, g);
-      return pattern_triples_sum<triple_batch<T, NT, V>(), false>(A, b, w, lane, r, g);
+      if (info & SLICE_FULL) return pattern_triples_sum<triple_batch<V>(), true>(A, b, w, lane, r, g);
+      return pattern_triples_sum<triple_batch<V>(), false>(A, b, w, lane, r, g);
     }
     if (info & SLICE_FULL) return pattern_sum<true>(A, b, w, r, g);
     if (info & SLICE_MASKED) return pattern_sum<false>(A, b, w, r, g);
@@ -1757,8 +1772,8 @@ inline bool wide(const Ell<double>& A) {
 }
 inline bool wide(const Ell<float>&) { return false; }
 
-// FP64 levels of uniform slices below this many rows take the kernels of V_SMALL (27 points: 40^3 rows 4.6 ->
-// 4.3 us, 48^3 = 110592 rows 4.8 both).
+// FP64 levels of wide uniform slices below this many rows take the kernels of V_SMALL (27 points: 40^3 rows
+// 4.6 -> 4.3 us, 48^3 = 110592 rows 4.8 both).
 constexpr int64_t kSmallMaxRows = 3 << 15;
 
 // Runs f(NT, V) for a level of one row per lane: the streaming hints of `nt`, and the variant of
@@ -1780,7 +1795,7 @@ void with_variant(const Ell<T>& A, bool nt, F&& f) {
   }
   if (A.desc) {
     if constexpr (std::is_same_v<T, double>) {
-      if (A.n < kSmallMaxRows) {
+      if (A.n < kSmallMaxRows && wide(A) && !A.anchor) {
         f(std::false_type(), std::integral_constant<int, V_SMALL>());
         return;
       }

@@ -672,6 +672,11 @@ int general_level(Handle* h, hipStream_t s, Level& L, Level* C, Csr* Phat) {
   return AMG_OK;
 }
 
+// R keeps its values where the whole hierarchy lies in the caches (fine levels of 27 points, R with values ->
+// patterns: 50^3 rows 6.1 -> 6.7 us, 64^3 6.1 -> 7.0, 80^3 10.8 -> 6.9; 7 points 64^3 4.5 -> 4.8, 80^3 5.8 ->
+// 4.8); the small levels below a large one find them evicted (40^3 rows below 320^3: 13.3 -> 10.7 us).
+constexpr int64_t kRestrictPatternMinRows = int64_t(3) << 17;
+
 // Level L -> C for the 2x2x2 box P: R = P^T A, A_c = P^T A P, and R in slices aligned on each
 // aggregate's first row (the restriction of k_restrict_product), whatever their padding (small
 // ragged levels pad more than 10%, but one pass over R still costs less than the residual's pass
@@ -694,7 +699,8 @@ int box_level(Handle* h, hipStream_t s, Level& L, Level* C) {
   }
   AMGP_TRY(rc);
   AMGP_TRY(adopt_csr(s, &Ac.c, C));
-  rc = build_ell_aligned(s, L.nc, R.c.ptr, R.c.col, R.c.val, &L.R64, L.children, kMaxChildren, L.n, true);
+  rc = build_ell_aligned(s, L.nc, R.c.ptr, R.c.col, R.c.val, &L.R64, L.children, kMaxChildren, L.n, true, false,
+                         h->lv.front().n >= kRestrictPatternMinRows);
   return rc == AMG_EINVAL ? AMG_OK : rc;
 }
 

@@ -336,13 +336,14 @@ __device__ __forceinline__ double dpp_shift(double end, double v) {
 // nine triples per batch instead of three the whole solve took 177 instead of 160 ms (473 ms with
 // dense slices).  7-point 128^3 level: step that keeps x 28.1 -> 18.6 us.
 
-// Any pattern: one gather per step.  FP32 batches are read whole, so that a batch comes with few wide scalar
-// loads: the steps past the pattern's end (the next pattern's, or the room behind the last) are not used.
+// Any pattern: one gather per step.  Batches of cached FP32 levels are read whole, so that they come with few wide
+// scalar loads: the steps past the pattern's end (the next pattern's, or the room behind the last) are not used.
 // With every step's index clamped each takes loads of its own, on which cached FP32 levels waited (a step of
 // a smoother application at 7 points 80^3 4.9 -> 4.0 us, stored values 4.3; 21 points 64^3 5.7 -> 4.2,
 // 4.3; 5 points 724^2 4.6 -> 3.9, 4.0).  FP64 batches keep the clamp: their values and masks take twice the
-// scalar registers (27 points 80^3 8.9 -> 9.5 us, restriction products of evicted levels 10.7 -> 13).
-template <bool FULL, typename T, typename Gf>
+// scalar registers (27 points 80^3 8.9 -> 9.5 us, restriction products of evicted levels 10.7 -> 13), and so
+// do streaming FP32 ones, whose occupancy the registers cost (the 320^3 level's last step 363 -> 400 us).
+template <bool NT, bool FULL, typename T, typename Gf>
 __device__ __forceinline__ T pattern_sum(EllView<T> A, int beg, int w, int r, Gf g) {
   constexpr int B = 8;
   T acc = T(0);
@@ -352,7 +353,7 @@ __device__ __forceinline__ T pattern_sum(EllView<T> A, int beg, int w, int r, Gf
     auto masked = [&](T x, int q) {
       if constexpr (FULL) return x; else return __builtin_amdgcn_inverse_ballot_w64(A.pmask()[q]) ? x : T(0);
     };
-    if constexpr (std::is_same_v<T, float>) {
+    if constexpr (std::is_same_v<T, float> && !NT) {
       int off[B];
 #pragma unroll
       for (int u = 0; u < B; ++u) {
@@ -487,8 +488,8 @@ __device__ __forceinline__ T slice_sum(EllView<T> A, int s, int lane, int r, Gf 
       if (info & SLICE_FULL) return pattern_triples_sum<triple_batch<V>(), true>(A, b, w, lane, r, g);
       return pattern_triples_sum<triple_batch<V>(), false>(A, b, w, lane, r, g);
     }
-    if (info & SLICE_FULL) return pattern_sum<true>(A, b, w, r, g);
-    if (info & SLICE_MASKED) return pattern_sum<false>(A, b, w, r, g);
+    if (info & SLICE_FULL) return pattern_sum<NT, true>(A, b, w, r, g);
+    if (info & SLICE_MASKED) return pattern_sum<NT, false>(A, b, w, r, g);
     beg = b << 6;
     end = (b + w) << 6;
     off = A.doff + b;
@@ -1777,8 +1778,9 @@ inline bool wide(const Ell<float>&) { return false; }
 constexpr int64_t kSmallMaxRows = 3 << 15;
 
 // Runs f(NT, V) for a level of one row per lane: the streaming hints of `nt`, and the variant of
-// its slices.  kHasWide: the kernel has a wide form (streaming levels only).
-template <bool kHasWide, bool kHasMirror = false, typename T, typename F>
+// its slices.  kHasWide: the kernel has a wide form (streaming levels only); kHasSmall: its matrix can be an
+// operator of wide uniform slices, not only a restriction product.
+template <bool kHasWide, bool kHasMirror = false, bool kHasSmall = true, typename T, typename F>
 void with_variant(const Ell<T>& A, bool nt, F&& f) {
   using Narrow = std::integral_constant<int, V_NARROW>;
   using Wide = std::integral_constant<int, V_WIDE>;
@@ -1794,8 +1796,8 @@ void with_variant(const Ell<T>& A, bool nt, F&& f) {
     }
   }
   if (A.desc) {
-    if constexpr (std::is_same_v<T, double>) {
-      if (A.n < kSmallMaxRows && wide(A) && !A.anchor) {
+    if constexpr (kHasSmall && std::is_same_v<T, double>) {
+      if (A.n < kSmallMaxRows && wide(A)) {
         f(std::false_type(), std::integral_constant<int, V_SMALL>());
         return;
       }
@@ -2195,7 +2197,7 @@ int launch_restrict_product(hipStream_t s, const Ell<T>& R, const int32_t* child
                             T* bc) {
   // streaming loads when the fine level streams
   const unsigned g = xcd_grid(R.n);
-  with_variant<false>(R, streamed(xcd_grid(R.ncols)), [&](auto nt, auto v) {
+  with_variant<false, false, false>(R, streamed(xcd_grid(R.ncols)), [&](auto nt, auto v) {
     hipLaunchKernelGGL((k_restrict_product<T, decltype(nt)::value, decltype(v)::value>), dim3(g), dim3(kBlock), 0, s,
                        R.n, view(R), children, b, x, bc);
   });
